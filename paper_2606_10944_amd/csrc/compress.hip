@@ -405,78 +405,85 @@ __device__ __forceinline__ void frag_pair_terms(const uint4* fk, const uint4* fv
 // add it to alpha.  E is float32; alpha accumulates in float64.
 //
 // Score layout of one bucket (BR = 16 RT rows = BP pairs per block, NT =
-// ceil(N/16) row tiles): panel B (the block's BP pairs as i) holds one tile
-// per column tile jt = B RT .. NT-1, each tile 8 columns p x BP rows i,
-// column-major ([p][i]), so a column's BP scores are contiguous.  Panel B
-// starts panel_tiles(B) tiles into the bucket's array.
+// ceil(N/16) row tiles): panel B (the block's BP pairs as i) holds every pair
+// p of the column tiles jt = B RT .. NT-1 (8 pairs each), as two half-planes:
+// pairs i = 0..15 of the block, then i = 16..31, each [p][16 i], so a pair's
+// scores are two runs of 64 bytes and a wave of the score kernel, which forms
+// the scores of one half-block against 16 pairs at a time, writes 1 KiB in a
+// row with one 16-byte store per lane.  Panel B starts panel_tiles(B) KiB
+// into the bucket's array.
 // ---------------------------------------------------------------------------
 __host__ __device__ inline int64_t panel_tiles(int64_t B, int64_t NT, int64_t RT) {
   return B * NT - RT * B * (B - 1) / 2;
 }
 
+// Floats of one half-plane of panel B.
+__host__ __device__ inline int64_t half_plane(int64_t B, int64_t NT, int64_t RT) {
+  return (NT - B * RT) * 8 * 16;
+}
+
 // Work decomposition of pair_scores_kernel.  A group is BLOCKS = W / 2
 // consecutive decision blocks (64 rows each) of one bucket; each of the
-// group's W waves holds one half-block (32 rows) of it as MFMA fragments
-// (HB = 1 half-block per wave).  W = 8 where a half-block's fragments take at
-// most four words per lane (bf16, and fp32 up to d = 64: about 128 registers
-// per wave, four waves per SIMD, two workgroups per CU, whose latencies hide
-// each other's), else W = 4 (fp32, d = 128).  Every launch of a bucket size
-// uses the same W, so own and streamed chunks share their groups.  (Four
-// waves of two half-blocks each, the two slots software-pipelined, needed
-// 253 registers: two waves per SIMD, and the streamed rounds of the long
-// workload ran 4-7 % slower.)  A workgroup handles one (bucket, group,
-// chunk): chunk 0 covers the group's own column tiles, which the owning
-// waves write to LDS from their registers (so the bucket's rows are read
-// from HBM once); chunk c >= 1 covers kScoreChunk column tiles after the
-// group (kScoreChunkLong in launches of many workgroups, fewer in launches of
-// few), streamed from global memory through registers DEPTH tiles ahead.
-#ifndef SCORE_DEPTH
-#define SCORE_DEPTH 3
-#endif
-constexpr int kScoreStages = 3;
-constexpr int kScoreChunk = 32;
-constexpr int kScoreChunkLong = 48;
+// group's W waves holds one half-block (32 rows) of it as MFMA fragments.
+// W = 8 where a half-block's fragments take at most four words per lane and
+// row tile (bf16, and fp32 up to d = 64: at most 128 registers per wave, four
+// waves per SIMD, two workgroups per CU, whose latencies hide each other's),
+// else W = 4 (fp32, d = 128).  Every launch of a bucket size uses the same W,
+// so own and streamed chunks share their groups.  A workgroup handles one
+// (bucket, group, chunk): chunk 0 covers the group's own column tiles, which
+// the owning waves write to LDS from their registers (so the bucket's rows
+// are read from HBM once); chunk c >= 1 covers kScoreChunk column tiles of 32
+// rows after the group (kScoreChunkLong in launches of many workgroups, fewer
+// in launches of few), copied from global memory straight into LDS.
+//   What bounds it: in the tile loop the vector ALU (about 75 instructions and
+// 16 exponentials per wave and 32-row tile) and the matrix cores (32 MFMAs)
+// are both about 80 % busy (2700 cycles per tile for the four waves of a SIMD,
+// 65536 rows x 32 slices); a workgroup's row loads before the loop take about
+// a quarter of its time.  Tiles of 32 columns with one barrier each, copied
+// straight to LDS, and scores stored from the registers, against tiles of 16
+// columns staged through registers with the scores turned in LDS: score
+// launches of 65536 rows x 32 slices (d = 128, bf16) 3.40 -> 3.04 ms, of 16384
+// rows x 64 slices 455 -> 383 us.
+constexpr int kScoreChunk = 16;
+constexpr int kScoreChunkLong = 24;
 #ifndef SCORE_MIN_WGS
 #define SCORE_MIN_WGS 128
 #endif
 constexpr int64_t kScoreMinWorkgroups = SCORE_MIN_WGS;  // half the CUs
 constexpr int64_t kScoreLongWorkgroups = 1024;         // four per CU
-// Streamed rows whose indices a workgroup stages: its chunk (at most
-// kScoreChunkLong), rounded up to whole ring turns, plus the ring's
-// look-ahead and the one tile whose index is read ahead of its load.
-constexpr int kScoreRowsStaged = (kScoreChunkLong + 2 * SCORE_DEPTH + 2) * 16;
-// A score tile (8 column pairs x 32 row pairs) in LDS: column stride 36
-// floats, so the scattered single-float writes of a half-wave hit 32
-// different banks.
+constexpr int kScoreRowsStaged = kScoreChunkLong * 32;  // rows of a streamed chunk, at most
+// A score tile (8 column pairs x 32 row pairs) in the local kernel's LDS:
+// column stride 36 floats, so that the decisions' reads of whole columns by
+// consecutive lanes fall in different banks.
 constexpr int kETileStride = 36;
 constexpr int kETileLds = 8 * kETileStride;
 
 template <typename T, int D, int W>
 struct ScoreShape {
   static constexpr int NV = Frag<T, D>::NV;
-  static constexpr int HB = 1;                 // half-blocks per wave
-  static constexpr int BLOCKS = W * HB / 2;    // decision blocks per group
+  static constexpr int BLOCKS = W / 2;         // decision blocks per group
   static constexpr int GT = 4 * BLOCKS;        // 16-row tiles per group
-  static constexpr int CHUNKS = 2 * NV;        // 1 KB fragment chunks per tile (K, then V)
-  static constexpr int LPT = (CHUNKS + W - 1) / W;
-  // stages, score tile buffers, pair scale exponents of the group's rows,
-  // row scale exponents of the stages, the half-blocks' largest row scales,
-  // row indices of the streamed rows
-  static constexpr int LDS = kScoreStages * CHUNKS * 1024 + kScoreStages * BLOCKS * kETileLds * 4 +
-                             GT * 16 * 4 + kScoreStages * 16 * 4 + 2 * BLOCKS * 4 +
-                             kScoreRowsStaged * 8;
+  static constexpr int CHUNKS = 2 * NV;        // 1 KB fragment chunks per 16-row tile (K, then V)
+  // own chunks: a ring of 16-row tiles, one ahead of the other's readers
+  static constexpr int OWN_STAGES = 3;
+  static constexpr int OWN_RING = OWN_STAGES * CHUNKS * 1024;
+  // streamed chunks: a ring of 32-row tiles; three where two workgroups per
+  // CU have room for them, else two (and one more barrier per tile)
+  static constexpr int STAGES = 6 * CHUNKS <= 48 ? 3 : 2;
+  static constexpr int STAGE = 2 * CHUNKS * 1024;
+  static constexpr int LPT = (2 * CHUNKS + W - 1) / W;  // copies per wave and tile
+  // ring, scales of the column rows per block, column row indices, the
+  // half-blocks' largest row scales
+  static constexpr int LDS_STREAM = STAGES * STAGE + kScoreRowsStaged * 4 * (BLOCKS + 1) + 2 * BLOCKS * 4;
+  // ring, pair scale exponents of the group's rows, the half-blocks' maxima
+  static constexpr int LDS_OWN = OWN_RING + GT * 16 * 4 + 2 * BLOCKS * 4;
+  static constexpr int LDS = LDS_STREAM > LDS_OWN ? LDS_STREAM : LDS_OWN;
 };
 
 // Waves of every score launch and of the local kernel (see above).
 template <typename T, int D>
 constexpr int score_waves() {
   return Frag<T, D>::NV < 8 ? 8 : 4;
-}
-
-// Block (group-local) and half of the half-block of wave w.
-__device__ __forceinline__ void half_block(int w, int& b, int& half) {
-  b = w >> 1;
-  half = w & 1;
 }
 
 // The decisions of one block of 32 pairs (lane p: pair p of the block, with
@@ -564,8 +571,86 @@ __device__ __forceinline__ double block_threshold(float lbt, float h2, float u, 
   return thr;
 }
 
-// Target of the stores of a streamed chunk's padding tiles (never read).
-__device__ __align__(16) float g_score_sink[256];
+// 64 lanes x 16 bytes from global memory straight into LDS: lane l's 16 bytes
+// at g go to LDS byte lds + 16 l (lds uniform over the wave).  Counted in
+// vmcnt, which the caller waits on: the compiler does not see the copy.  (m0
+// holds the LDS address; nothing else in these kernels uses it.)
+__device__ __forceinline__ void copy16_to_lds(const void* g, uint32_t lds) {
+  asm volatile(
+      "s_mov_b32 m0, %0\n\t"
+      "s_nop 0\n\t"
+      "global_load_lds_dwordx4 %1, off"
+      :
+      : "s"(lds), "v"(g)
+      : "memory");
+}
+__device__ __forceinline__ uint32_t lds_offset(const void* p) {
+  return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void*)p;
+}
+// s_waitcnt vmcnt(N), the other counters untouched.
+template <int N>
+__device__ __forceinline__ void wait_vmcnt() {
+  static_assert(N >= 0 && N < 64, "vmcnt has six bits");
+  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+}
+
+// Row of a half-block's (or column tile's) 32 rows that lane m16 of 16-row
+// tile rt holds.  MFMA outputs put rows 4g..4g+3 of a tile in lane group g;
+// with this order the group holds eight consecutive rows over both tiles,
+// i.e. four consecutive pairs, whose scores against one pair it can store as
+// 16 bytes.  Pairs stay in adjacent lanes.
+__device__ __forceinline__ int frag_row(int rt, int m16) {
+  return 8 * (m16 >> 2) + 4 * rt + (m16 & 3);
+}
+
+// F = kappa(y'_i, x) - kappa(y_i, x) of the wave's 16 pairs i against the
+// column rows x of one 16-row tile, whose fragments (CHUNKS KiB) start at st:
+// lane (g, m16) gets f[k] for the pairs i = 4g + k against row m16, at the
+// scale 2^-he of that row.  The column fragments are read word by word beside
+// the MFMAs that use them.
+template <typename T, int NV>
+__device__ __forceinline__ void score_f(const uint4 (&Ak)[2][NV], const uint4 (&Av)[2][NV],
+                                        const unsigned char* st, int lane, float vm2f, float c2,
+                                        float he, float* f) {
+  floatx4_t gk[2], gv[2];
+#pragma unroll
+  for (int rt = 0; rt < 2; ++rt) {
+    gk[rt] = (floatx4_t){0.f, 0.f, 0.f, 0.f};
+    gv[rt] = (floatx4_t){vm2f, vm2f, vm2f, vm2f};  // <v,v'> + v_max^2
+  }
+#pragma unroll
+  for (int v = 0; v < NV; ++v) {
+    const uint4 bk = reinterpret_cast<const uint4*>(st + v * 1024)[lane];
+    const uint4 bv = reinterpret_cast<const uint4*>(st + (NV + v) * 1024)[lane];
+#pragma unroll
+    for (int rt = 0; rt < 2; ++rt) {
+      gk[rt] = mma_word<T>(Ak[rt][v], bk, gk[rt]);
+      gv[rt] = mma_word<T>(Av[rt][v], bv, gv[rt]);
+    }
+  }
+#pragma unroll
+  for (int rt = 0; rt < 2; ++rt) {
+    float kap[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      kap[e] = __builtin_amdgcn_exp2f(gk[rt][e] * c2 - he) * gv[rt][e];
+    f[2 * rt] = kap[1] - kap[0];
+    f[2 * rt + 1] = kap[3] - kap[2];
+  }
+}
+// E(i, p) = F(i, y_p) - F(i, y'_p) of the four pairs i = 4g + k: the even lane
+// of a pair of lanes takes the pair p of the first 16-row column tile (f0),
+// the odd lane that of the second (f1); each gets the partner's F of its p.
+__device__ __forceinline__ float4 score_e(const float* f0, const float* f1, bool odd) {
+  float e[4];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const float mine = odd ? f1[k] : f0[k];
+    const float other = from_partner(odd ? f0[k] : f1[k]);
+    e[k] = odd ? other - mine : mine - other;
+  }
+  return make_float4(e[0], e[1], e[2], e[3]);
+}
 
 // LOCAL: the whole round for buckets of at most GT*16 rows in one launch:
 // one workgroup per bucket computes the bucket's scores into LDS (its own
@@ -574,16 +659,10 @@ __device__ __align__(16) float g_score_sink[256];
 // OWN_ONLY: a launch of own chunks only (an instantiation without the
 // streamed code, which needs fewer registers).
 template <typename T, int D, bool LOCAL, bool OWN_ONLY, int W>
-__global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2)))
+__global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(W == 8 ? 4 : 2)))
 void pair_scores_kernel(HalveArgs a) {
   using SS = ScoreShape<T, D, W>;
-  constexpr int NV = SS::NV, HB = SS::HB, NBW = SS::BLOCKS, GT = SS::GT;
-  constexpr int CH = SS::CHUNKS, LPT = SS::LPT;
-  constexpr int BP = 32;
-  constexpr int TILE = 8 * BP;
-  constexpr int DEPTH = SCORE_DEPTH;
-  constexpr int NS = kScoreStages;
-  static_assert(DEPTH % NS == 0, "the unrolled ring keeps stage indices static");
+  constexpr int NV = SS::NV, NBW = SS::BLOCKS, GT = SS::GT, CH = SS::CHUNKS;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int m16 = lane & 15;
@@ -592,6 +671,7 @@ void pair_scores_kernel(HalveArgs a) {
   const int N = a.N;
   const int P = N >> 1;
   const int NT = (N + 15) >> 4;
+  const int NC = (N + 31) >> 5;  // 32-row column tiles
   const int nb = (N + 63) >> 6;
   // Workgroup -> (bucket, group, chunk).  Workgroups are dealt to the eight
   // XCDs in turn (linear id mod 8); XCD x takes buckets x, x+8, ... in sets
@@ -613,7 +693,7 @@ void pair_scores_kernel(HalveArgs a) {
     if (bl >= a.nbk) return;
     int item = r_ / a.il;
     for (int g_ = 0; g_ < a.ngrp; ++g_) {
-      const int rest_ = NT - (g_ + 1) * GT;
+      const int rest_ = NC - (g_ + 1) * (GT / 2);
       const int nsc_ = rest_ > 0 ? (rest_ + a.ch - 1) / a.ch : 0;  // streamed chunks
       const int cnt_ = max(0, min(a.chunk0 + a.nz, 1 + nsc_) - a.chunk0);
       if (item < cnt_) {
@@ -627,13 +707,12 @@ void pair_scores_kernel(HalveArgs a) {
   const int64_t bucket = a.b0 + bl;
   const int64_t s = bucket / a.G;
   const int64_t t = bucket % a.G;
-  const int gt0 = grp * GT;  // the group's first tile
-  if (gt0 >= NT) return;
+  const int jg = grp * (GT / 2);  // the group's first column tile
+  if (jg >= NC) return;
   const bool own = OWN_ONLY || chunk == 0;
-  const int jt0 = own ? gt0 : gt0 + GT + (chunk - 1) * a.ch;
-  if (jt0 >= NT) return;
-  const int jt1 = min(jt0 + (own ? GT : a.ch), NT);
-  const int ntile = jt1 - jt0;
+  const int jc0 = own ? jg : jg + GT / 2 + (chunk - 1) * a.ch;
+  if (jc0 >= NC) return;
+  const int ntile = min(jc0 + (own ? GT / 2 : a.ch), NC) - jc0;
 
   const T* K = reinterpret_cast<const T*>(a.K) + s * a.ld * D;
   const T* V = reinterpret_cast<const T*>(a.V) + s * a.ld * D;
@@ -646,86 +725,87 @@ void pair_scores_kernel(HalveArgs a) {
   const float c2 = (float)(kLog2e * inv_sqrt_d);
 
   extern __shared__ __align__(16) unsigned char smem[];
-  // [NS][NBW] tile buffers, or (LOCAL) every score tile of the bucket
-  float* s_e = reinterpret_cast<float*>(smem + NS * CH * 1024);
-  float* s_h2 = s_e + (LOCAL ? (int)panel_tiles(nb, NT, 4) : NS * NBW) * kETileLds;  // [GT * 16]
-  float* s_hst = s_h2 + GT * 16;                                     // [NS * 16], staged rows
-  float* s_mh = s_hst + NS * 16;  // [2 * NBW]: largest row scale of each half-block
-  int64_t* s_rows = reinterpret_cast<int64_t*>(s_mh + 2 * NBW);
-  float* s_lbt = s_mh + 2 * NBW;  // LOCAL: pair terms [P] and [P] (no staged rows there)
+  // own chunks: ring | (LOCAL) every score tile of the bucket | pair scales of
+  // the group's rows [GT * 16] | half-blocks' largest row scales | (LOCAL)
+  // pair terms and the decisions' state
+  float* s_e = reinterpret_cast<float*>(smem + SS::OWN_RING);
+  float* s_h2 = s_e + (LOCAL ? (int)panel_tiles(nb, NT, 4) : 0) * kETileLds;
+  float* s_mh = own ? s_h2 + GT * 16
+                    : reinterpret_cast<float*>(smem + SS::STAGES * SS::STAGE) +
+                          kScoreRowsStaged * (NBW + 1);  // [2 * NBW]
+  float* s_lbt = s_mh + 2 * NBW;  // LOCAL: pair terms [P] and [P]
   float* s_h2p = s_lbt + P;
   // LOCAL decisions: per block and lane the threshold and the bulk alpha of
   // the earlier blocks but the last ([NBW][64] each), and each block's mask
   double* s_thr = reinterpret_cast<double*>((reinterpret_cast<uintptr_t>(s_h2p + P) + 7) & ~(uintptr_t)7);
   double* s_alpha = s_thr + 64 * NBW;
   uint32_t* s_mask = reinterpret_cast<uint32_t*>(s_alpha + 64 * NBW);
+  // streamed chunks: ring | scale exponents of the column rows for each of
+  // the group's blocks [NBW][kScoreRowsStaged] | column row indices
+  float* s_he = reinterpret_cast<float*>(smem + SS::STAGES * SS::STAGE);
+  int32_t* s_row = reinterpret_cast<int32_t*>(s_he + kScoreRowsStaged * NBW);
 
-  // ---- this wave's half-blocks: fragments and, in chunk 0, pair terms ----
-  int hb_blk[HB], hb_half[HB];
-  bool hb_ok[HB];
-#pragma unroll
-  for (int h = 0; h < HB; ++h) {
-    int b, half;
-    half_block(wave, b, half);
-    hb_blk[h] = grp * NBW + b;
-    hb_half[h] = half;
-    hb_ok[h] = hb_blk[h] < nb;
-  }
-  // Streamed chunk: the row indices of its column rows are requested first,
-  // so that their latency and the fragments' overlap (the index loads are
-  // the older ones, and staging them in LDS waits for them only).
+  // ---- this wave's half-block: rows, fragments and, in chunk 0, pair terms ----
+  const int lblk = wave >> 1, half = wave & 1;
+  const int blk = grp * NBW + lblk;
+  const bool hb_ok = blk < nb;
+  const bool odd = (m16 & 1) != 0;
+  // Streamed chunk: column row o of the chunk in fragment order (tile o / 32,
+  // 16-row half o / 16 & 1, lane o % 16); this thread's are o = threadIdx.x +
+  // 64 W k.  Their indices are requested first, then their scale exponents
+  // from the per-row table, then the fragments, so that each wait covers only
+  // what it needs.
   constexpr int RPT = (kScoreRowsStaged + 64 * W - 1) / (64 * W);
-  const int j_end = own ? 0 : min(N, (jt1 + 2 * DEPTH + 2) * 16);
-  int64_t ridx[RPT];
+  int32_t ridx[RPT];
+  float rh[RPT];
   if (!own) {
 #pragma unroll
     for (int k = 0; k < RPT; ++k) {
-      const int j = jt0 * 16 + (int)threadIdx.x + k * 64 * W;
-      ridx[k] = j < j_end ? (rows_in ? (int64_t)rows_in[j] : row_base + j) : 0;
+      const int o = (int)threadIdx.x + k * 64 * W;
+      const int j = min((jc0 + (o >> 5)) * 32 + frag_row((o >> 4) & 1, o & 15), N - 1);
+      ridx[k] = o < 32 * ntile ? (rows_in ? rows_in[j] : (int32_t)(row_base + j)) : 0;
     }
   }
-  // This wave's rows; a streamed chunk also reads their scale exponents
-  // from the per-row table (requested before the fragments, so that waiting
-  // for them does not wait for the fragments).
-  int64_t ar[HB][2];
-  float arh[HB][2];
+  int64_t ar[2];
+  float arh[2];
 #pragma unroll
-  for (int h = 0; h < HB; ++h)
+  for (int rt = 0; rt < 2; ++rt) {
+    const int j = blk * 64 + half * 32 + frag_row(rt, m16);
+    const bool valid = hb_ok && j < N;
+    ar[rt] = valid ? (rows_in ? (int64_t)rows_in[j] : row_base + j) : -1;
+    arh[rt] = (!own && valid) ? a.rowh2[s * a.n + ar[rt]] : 0.0f;
+  }
+  if (!own) {
 #pragma unroll
-    for (int rt = 0; rt < 2; ++rt) {
-      const int j = hb_blk[h] * 64 + hb_half[h] * 32 + rt * 16 + m16;
-      const bool valid = hb_ok[h] && j < N;
-      ar[h][rt] = valid ? (rows_in ? (int64_t)rows_in[j] : row_base + j) : -1;
-      arh[h][rt] = (!own && valid) ? a.rowh2[s * a.n + ar[h][rt]] : 0.0f;
+    for (int k = 0; k < RPT; ++k) {
+      const int o = (int)threadIdx.x + k * 64 * W;
+      rh[k] = o < 32 * ntile ? a.rowh2[s * a.n + ridx[k]] : 0.0f;
     }
+  }
   __builtin_amdgcn_sched_barrier(0);
-  uint4 Ak[HB][2][NV], Av[HB][2][NV];
+  uint4 Ak[2][NV], Av[2][NV];
 #pragma unroll
-  for (int h = 0; h < HB; ++h)
-#pragma unroll
-    for (int rt = 0; rt < 2; ++rt) {
-      const bool valid = ar[h][rt] >= 0;
-      const int64_t r = valid ? ar[h][rt] : 0;
-      load_frag<T, D>(K, r, g, valid, Ak[h][rt]);
-      load_frag<T, D>(V, r, g, valid, Av[h][rt]);
-    }
+  for (int rt = 0; rt < 2; ++rt) {
+    const bool valid = ar[rt] >= 0;
+    const int64_t r = valid ? ar[rt] : 0;
+    load_frag<T, D>(K, r, g, valid, Ak[rt]);
+    load_frag<T, D>(V, r, g, valid, Av[rt]);
+  }
   if (own) {
     // Wait for the fragments here (vmcnt(0)).  Otherwise the first use sits
     // in the tile loop, whose wait then also covers the score stores of
     // earlier tiles on every iteration (stores count in vmcnt on this
-    // architecture).  Streamed chunks first use them in the peeled ring turn.
+    // architecture).
     __builtin_amdgcn_s_waitcnt(0x0F70);
     const int64_t pb = s * (a.n_r >> 1) + t * (int64_t)P;
-#pragma unroll
-    for (int h = 0; h < HB; ++h) {
-      if (!hb_ok[h]) continue;
+    if (hb_ok) {
 #pragma unroll
       for (int rt = 0; rt < 2; ++rt) {
         float rh2, h2f, lbt;
-        frag_pair_terms<T, D>(Ak[h][rt], Av[h][rt], vm2d, inv_sqrt_d, rh2, h2f, lbt);
-        arh[h][rt] = ar[h][rt] >= 0 ? rh2 : 0.0f;
-        const int j = hb_blk[h] * 64 + hb_half[h] * 32 + rt * 16 + m16;
-        if (g == 0) s_h2[((hb_blk[h] - grp * NBW) * 4 + hb_half[h] * 2 + rt) * 16 + m16] = h2f;
+        frag_pair_terms<T, D>(Ak[rt], Av[rt], vm2d, inv_sqrt_d, rh2, h2f, lbt);
+        arh[rt] = ar[rt] >= 0 ? rh2 : 0.0f;
+        const int j = blk * 64 + half * 32 + frag_row(rt, m16);
+        if (g == 0) s_h2[(2 * wave + rt) * 16 + m16] = j < N ? h2f : 0.0f;
         if (g == 0 && j < N && (j & 1) == 0) {
           if (LOCAL) {
             s_h2p[j >> 1] = h2f;
@@ -735,187 +815,34 @@ void pair_scores_kernel(HalveArgs a) {
             a.lbt[pb + (j >> 1)] = lbt;
           }
         }
-        if (a.rowh2_write && g == 0 && j < N)
-          a.rowh2[s * a.n + (rows_in ? (int64_t)rows_in[j] : row_base + j)] = rh2;
+        if (a.rowh2_write && g == 0 && j < N) a.rowh2[s * a.n + ar[rt]] = rh2;
       }
     }
   } else {
-    // row indices of every streamed column row, staged in LDS before the
-    // ring starts: a data load then never waits on an index load issued
-    // behind the ring's loads
 #pragma unroll
     for (int k = 0; k < RPT; ++k) {
-      const int j = jt0 * 16 + (int)threadIdx.x + k * 64 * W;
-      if (j < j_end) s_rows[j - jt0 * 16] = ridx[k];
+      const int o = (int)threadIdx.x + k * 64 * W;
+      if (o < 32 * ntile) s_row[o] = ridx[k];
     }
   }
   // the largest row scale of each half-block (rows past the bucket: 0, and
   // every row scale is >= 0), published in LDS before the tile loop's first
-  // barrier; hb_m[h] = the largest of slot h's block, read after it
-#pragma unroll
-  for (int h = 0; h < HB; ++h) {
-    const float mh = wave_max_f(fmaxf(arh[h][0], arh[h][1]));
-    if (lane == 0) s_mh[(hb_blk[h] - grp * NBW) * 2 + hb_half[h]] = mh;
+  // barrier
+  {
+    const float mh = wave_max_f(fmaxf(arh[0], arh[1]));
+    if (lane == 0) s_mh[2 * lblk + half] = mh;
   }
-  float hb_m[HB];
+  // This wave's scores against 16 pairs (one column tile jc) of its block's
+  // panel: pair q of the tile (of this lane), then pairs i = 4g .. 4g+3 of
+  // the half-block.  The panel ends after 8 pairs of the last tile when NT is
+  // odd.
+  const int q = 4 * (m16 >> 2) + 2 * (odd ? 1 : 0) + ((m16 >> 1) & 1);
+  float* ew = nullptr;
+  if constexpr (!LOCAL)
+    ew = a.E + (bl * a.e_tiles + panel_tiles(blk, NT, 4)) * 256 + half * half_plane(blk, NT, 4) -
+         (int64_t)blk * 512 + q * 16 + 4 * g;
+  auto in_panel = [&](int jc) { return 2 * jc + (q >> 3) < NT; };
 
-  // ---- column tiles ----
-  // Streamed chunk c of tile jt: lane l holds row jt*16 + l%16 (clamped to
-  // the bucket; rows past the end are never read back), word 4(c%NV) + l/16,
-  // of K (c < NV) or V.  Own tiles are the owners' fragments, same layout.
-  // Streamed rows also bring their scale exponents from the per-row table
-  // (written by the first round's own chunks), staged in LDS with the rows.
-  // Tiles are issued in order, and each one reads the next one's row index
-  // from LDS (rnx), so that no issue waits for an LDS read.
-  u32x4 stg[DEPTH][LPT];
-  float hst[DEPTH];
-  int64_t rnx = 0;
-#define SCORE_ISSUE(JT, SLOT)                                                        \
-  do {                                                                               \
-    const int64_t row_ = rnx;                                                        \
-    rnx = s_rows[min(((JT) + 1) * 16 + m16, N - 1) - jt0 * 16];                      \
-    hst[SLOT] = a.rowh2[s * a.n + row_];                                             \
-    _Pragma("unroll") for (int k_ = 0; k_ < LPT; ++k_) {                             \
-      const int c_ = min(wave + k_ * W, CH - 1);                                     \
-      const T* src_ = c_ < NV ? K : V;                                               \
-      stg[SLOT][k_] = reinterpret_cast<const u32x4*>(src_ + row_ * D)[4 * (c_ % NV) + g]; \
-    }                                                                                \
-  } while (0)
-#define SCORE_COMMIT(STAGE, SLOT)                                                    \
-  do {                                                                               \
-    if (wave == 0 && g == 0) s_hst[(STAGE) * 16 + m16] = hst[SLOT];                  \
-    _Pragma("unroll") for (int k_ = 0; k_ < LPT; ++k_) {                             \
-      const int c_ = wave + k_ * W;                                                  \
-      if (c_ < CH) reinterpret_cast<u32x4*>(smem + ((STAGE) * CH + c_) * 1024)[lane] = stg[SLOT][k_]; \
-    }                                                                                \
-  } while (0)
-#define SCORE_OWN_WRITE(STAGE, H, RT)                                                \
-  do {                                                                               \
-    _Pragma("unroll") for (int v_ = 0; v_ < NV; ++v_) {                              \
-      reinterpret_cast<uint4*>(smem + ((STAGE) * CH + v_) * 1024)[lane] = Ak[H][RT][v_]; \
-      reinterpret_cast<uint4*>(smem + ((STAGE) * CH + NV + v_) * 1024)[lane] = Av[H][RT][v_]; \
-    }                                                                                \
-  } while (0)
-  // own tile TL (group-local) into a stage, by the wave holding it
-#define SCORE_OWN_COMMIT(STAGE, TL)                                                  \
-  do {                                                                               \
-    const int b_ = (TL) >> 2, half_ = ((TL) >> 1) & 1, rt_ = (TL) & 1;              \
-    if (wave == 2 * b_ + half_) {                                                    \
-      if (rt_ == 0) SCORE_OWN_WRITE(STAGE, 0, 0); else SCORE_OWN_WRITE(STAGE, 0, 1);   \
-    }                                                                                \
-  } while (0)
-
-  // Gram accumulators; a half-block slot h takes part in tile jt from its
-  // block's diagonal on (always, in a streamed chunk).  (Two waves per SIMD
-  // overlap one wave's MFMAs with the other's exp epilogue; double-buffered
-  // accumulators would not fit.)
-  floatx4_t gk[1][HB][2], gv[1][HB][2];
-  uint4 bk_[NV], bv_[NV];
-#define SCORE_ACTIVE(OWN, H, JT) (!(OWN) || (hb_ok[H] && (JT) >= hb_blk[H] * 4))
-#define SCORE_BFRAG(STAGE)                                                              \
-  do {                                                                                 \
-    _Pragma("unroll") for (int v_ = 0; v_ < NV; ++v_) {                                \
-      bk_[v_] = reinterpret_cast<const uint4*>(smem + ((STAGE) * CH + v_) * 1024)[lane]; \
-      bv_[v_] = reinterpret_cast<const uint4*>(smem + ((STAGE) * CH + NV + v_) * 1024)[lane]; \
-    }                                                                                  \
-  } while (0)
-#define SCORE_MMA_H(H)                                                                  \
-  do {                                                                                 \
-    _Pragma("unroll") for (int rt_ = 0; rt_ < 2; ++rt_) {                              \
-      gk[0][H][rt_] = (floatx4_t){0.f, 0.f, 0.f, 0.f};                                 \
-      gv[0][H][rt_] = (floatx4_t){vm2f, vm2f, vm2f, vm2f}; /* <v,v'> + v_max^2 */      \
-    }                                                                                  \
-    _Pragma("unroll") for (int v_ = 0; v_ < NV; ++v_)                                  \
-      _Pragma("unroll") for (int rt_ = 0; rt_ < 2; ++rt_) {                            \
-        gk[0][H][rt_] = mma_word<T>(Ak[H][rt_][v_], bk_[v_], gk[0][H][rt_]);           \
-        gv[0][H][rt_] = mma_word<T>(Av[H][rt_][v_], bv_[v_], gv[0][H][rt_]);           \
-      }                                                                                \
-  } while (0)
-  // Scores of slot H into the tile buffer BUF.  Lane (g, m16) holds
-  // kappa(A row 4g+e, column row m16) for e = 0..3, i.e. A pairs 2g and 2g+1
-  // of the row tile against column row m16.  With F = kappa(y'_i, .) -
-  // kappa(y_i, .), the even lane of a column pair forms E(2g, p) =
-  // F0 - F0(partner) and the odd lane E(2g+1, p) = F1(partner) - F1.
-  const int epi_lane = (m16 >> 1) * kETileStride + 2 * g + (m16 & 1);
-#define SCORE_EPI_H(H, H2, BUF)                                                         \
-  do {                                                                                 \
-    float* eb_ = LOCAL ? s_e + (panel_tiles(hb_blk[H], NT, 4) + jt_ - 4 * hb_blk[H]) * kETileLds \
-                       : s_e + ((BUF) * NBW + hb_blk[H] - grp * NBW) * kETileLds;      \
-    const float he_ = (H2) + scale_shift(hb_m[H], (H2));                               \
-    _Pragma("unroll") for (int rt = 0; rt < 2; ++rt) {                                 \
-      float kap[4];                                                                    \
-      _Pragma("unroll") for (int e = 0; e < 4; ++e)                                    \
-        kap[e] = __builtin_amdgcn_exp2f(gk[0][H][rt][e] * c2 - he_) * gv[0][H][rt][e]; \
-      const float F0 = kap[1] - kap[0];                                                \
-      const float F1 = kap[3] - kap[2];                                                \
-      const float mine_ = odd ? F1 : F0;                                               \
-      const float other_ = from_partner(odd ? F0 : F1);                                \
-      eb_[epi_lane + hb_half[H] * 16 + rt * 8] =                                       \
-          odd ? other_ - mine_ : mine_ - other_;                                       \
-    }                                                                                  \
-  } while (0)
-  // Wave w < NBW writes block w's completed tile IF (buffer BUF) to the score
-  // array: 16 bytes per lane, 128 contiguous bytes per column pair.  A
-  // streamed chunk's padding tiles go to the sink.
-#define SCORE_FLUSH(OWN, IF, BUF)                                                       \
-  do {                                                                                 \
-    if (!LOCAL && (NBW == W || wave < NBW)) {                                          \
-      const int bw_ = grp * NBW + wave;                                                \
-      const int jtf_ = jt0 + (IF);                                                     \
-      if (!(OWN) || (bw_ < nb && jtf_ >= 4 * bw_)) {                                   \
-        float* dst_ = (OWN) || (IF) < ntile                                            \
-            ? a.E + (bl * a.e_tiles + panel_tiles(bw_, NT, 4) + jtf_ - 4 * bw_) * (int64_t)TILE \
-            : g_score_sink;                                                            \
-        const float4 v_ = *reinterpret_cast<const float4*>(                            \
-            s_e + ((BUF) * NBW + wave) * kETileLds + (lane >> 3) * kETileStride + (lane & 7) * 4); \
-        *reinterpret_cast<float4*>(dst_ + (lane >> 3) * BP + (lane & 7) * 4) = v_;     \
-      }                                                                                \
-    }                                                                                  \
-  } while (0)
-  // Streamed tiles: the column fragments are read from the stage word by
-  // word beside the MFMAs that use them (all of them at once would take 32
-  // more registers, past the 128 that four waves per SIMD allow)
-#define SCORE_MMA_LDS(H, STAGE)                                                         \
-  do {                                                                                 \
-    _Pragma("unroll") for (int rt_ = 0; rt_ < 2; ++rt_) {                              \
-      gk[0][H][rt_] = (floatx4_t){0.f, 0.f, 0.f, 0.f};                                 \
-      gv[0][H][rt_] = (floatx4_t){vm2f, vm2f, vm2f, vm2f};                             \
-    }                                                                                  \
-    _Pragma("unroll") for (int v_ = 0; v_ < NV; ++v_) {                                \
-      const uint4 bk1_ = reinterpret_cast<const uint4*>(smem + ((STAGE) * CH + v_) * 1024)[lane]; \
-      const uint4 bv1_ = reinterpret_cast<const uint4*>(smem + ((STAGE) * CH + NV + v_) * 1024)[lane]; \
-      _Pragma("unroll") for (int rt_ = 0; rt_ < 2; ++rt_) {                            \
-        gk[0][H][rt_] = mma_word<T>(Ak[H][rt_][v_], bk1_, gk[0][H][rt_]);              \
-        gv[0][H][rt_] = mma_word<T>(Av[H][rt_][v_], bv1_, gv[0][H][rt_]);              \
-      }                                                                                \
-    }                                                                                  \
-  } while (0)
-
-  // One column tile (tile I of the chunk, ring position U = I mod 3): tile
-  // I+2 staged (and, streamed, tile I+2+DEPTH loaded), Grams and scores of
-  // tile I, then the previous tile written out (its LDS read after this
-  // tile's work, so that it waits at the barrier's wait only).
-#define SCORE_TILE(OWN, I, U)                                                           \
-  do {                                                                                 \
-    const int i_ = (I);                                                                \
-    const int jt_ = jt0 + i_;                                                          \
-    if (OWN) {                                                                         \
-      if (i_ + 2 < ntile) SCORE_OWN_COMMIT(((U) + 2) % NS, i_ + 2);                    \
-    } else {                                                                           \
-      SCORE_COMMIT(((U) + 2) % NS, ((U) + 2) % DEPTH);                                 \
-      SCORE_ISSUE(jt_ + 2 + DEPTH, ((U) + 2) % DEPTH);                                 \
-    }                                                                                  \
-    if (OWN) SCORE_BFRAG((U) % NS);                                                    \
-    const float h2_ = jt_ * 16 + m16 >= N ? 0.0f                                       \
-                      : (OWN) ? s_h2[i_ * 16 + m16] : pair_h2f(s_hst[((U) % NS) * 16 + m16]);        \
-    _Pragma("unroll") for (int h = 0; h < HB; ++h) {                                   \
-      if (!SCORE_ACTIVE(OWN, h, jt_)) continue;                                        \
-      if (OWN) SCORE_MMA_H(h); else SCORE_MMA_LDS(h, (U) % NS);                        \
-      SCORE_EPI_H(h, h2_, (U) % NS);                                                   \
-    }                                                                                  \
-    if (i_ > 0) SCORE_FLUSH(OWN, i_ - 1, ((U) + NS - 1) % NS);                         \
-    __syncthreads();                                                                   \
-  } while (0)
   // LOCAL: the decisions of the bucket's P <= 32 NBW pairs from the scores
   // in LDS, with the arithmetic of halve_pass_kernel: block m's thresholds,
   // then alpha = the float32 signed sums of every earlier block added in
@@ -988,65 +915,131 @@ void pair_scores_kernel(HalveArgs a) {
     }
   };
 
-  const bool odd = (m16 & 1) != 0;
   __syncthreads();
-#pragma unroll
-  for (int h = 0; h < HB; ++h) {
-    const int lb = hb_blk[h] - grp * NBW;
-    hb_m[h] = fmaxf(s_mh[2 * lb], s_mh[2 * lb + 1]);
-  }
-  // the decision pass reads each block's largest row scale from here
-  if (!LOCAL && own && (int)threadIdx.x < NBW && grp * NBW + (int)threadIdx.x < nb)
-    a.mB[bucket * nb + grp * NBW + threadIdx.x] =
-        fmaxf(s_mh[2 * threadIdx.x], s_mh[2 * threadIdx.x + 1]);
   if (own) {
-    SCORE_OWN_COMMIT(0, 0);
-    if (ntile > 1) SCORE_OWN_COMMIT(1, 1);
-    __syncthreads();
-    for (int ib = 0; ib < ntile; ib += DEPTH) {
+    const float mB = fmaxf(s_mh[2 * lblk], s_mh[2 * lblk + 1]);
+    // the decision pass reads each block's largest row scale from here
+    if (!LOCAL && (int)threadIdx.x < NBW && grp * NBW + (int)threadIdx.x < nb)
+      a.mB[bucket * nb + grp * NBW + threadIdx.x] =
+          fmaxf(s_mh[2 * threadIdx.x], s_mh[2 * threadIdx.x + 1]);
+    // 16-row tile i (of wave i / 2's fragments) into stage i mod 3
+    auto commit = [&](int i, int stage) {
+      if (wave == (i >> 1)) {
+        unsigned char* st = smem + stage * CH * 1024;
 #pragma unroll
-      for (int u = 0; u < DEPTH; ++u)
-        if (ib + u < ntile) SCORE_TILE(true, ib + u, u);  // uniform over the workgroup
-    }
-    SCORE_FLUSH(true, ntile - 1, (ntile - 1) % NS);
-    if constexpr (LOCAL) {
+        for (int v = 0; v < NV; ++v) {
+          reinterpret_cast<uint4*>(st + v * 1024)[lane] = (i & 1) ? Ak[1][v] : Ak[0][v];
+          reinterpret_cast<uint4*>(st + (NV + v) * 1024)[lane] = (i & 1) ? Av[1][v] : Av[0][v];
+        }
+      }
+    };
+    commit(0, 0);
+    commit(1, 1);
+    __syncthreads();
+    // a half-block takes part from its block's diagonal on
+    const int first = hb_ok ? 4 * lblk : GT;
+    float f0[4];
+    // step i = 2 t + u (16-row tile u of column tile jc0 + t, stage st); tile
+    // i + 2 is staged meanwhile
+    auto step = [&](int tt, int u, int st) {
+      const int i = 2 * tt + u;
+      if (i + 2 < 2 * ntile) commit(i + 2, (st + 2) % 3);
+      if (i >= first) {
+        const float h2 = s_h2[i * 16 + m16];
+        const float he = h2 + scale_shift(mB, h2);
+        float f[4];
+        score_f<T, NV>(Ak, Av, smem + st * CH * 1024, lane, vm2f, c2, he, f);
+        if (u == 0) {
+#pragma unroll
+          for (int k = 0; k < 4; ++k) f0[k] = f[k];
+        } else {
+          const float4 e = score_e(f0, f, odd);
+          if constexpr (LOCAL) {
+            if (in_panel(jc0 + tt)) {
+              float* col = s_e + (panel_tiles(blk, NT, 4) + 2 * (jc0 + tt) + (q >> 3) - 4 * blk) * kETileLds +
+                           (q & 7) * kETileStride;
+              *reinterpret_cast<float4*>(col + 16 * half + 4 * g) = e;
+            }
+          } else if (in_panel(jc0 + tt)) {
+            *reinterpret_cast<float4*>(ew + (int64_t)(jc0 + tt) * 256) = e;
+          }
+        }
+      }
       __syncthreads();
-      local_decisions();
+    };
+    for (int t3 = 0; t3 < ntile; t3 += 3) {  // six steps: stages 0 1 2 0 1 2
+      step(t3, 0, 0);
+      step(t3, 1, 1);
+      if (t3 + 1 < ntile) {  // uniform over the workgroup
+        step(t3 + 1, 0, 2);
+        step(t3 + 1, 1, 0);
+      }
+      if (t3 + 2 < ntile) {
+        step(t3 + 2, 0, 1);
+        step(t3 + 2, 1, 2);
+      }
     }
+    if constexpr (LOCAL) local_decisions();
   } else if constexpr (!LOCAL && !OWN_ONLY) {
-    rnx = s_rows[min(jt0 * 16 + m16, N - 1) - jt0 * 16];  // staged before the barrier above
+    // Copies of column tile tt into stage st: chunk c = (16-row half, K words
+    // then V words), c = wave, wave + W, ...; lane l of word v brings the
+    // row's 16-byte word 4 v + l / 16.
+    constexpr int L = SS::LPT, NS = SS::STAGES;
+    const uint32_t ring = lds_offset(smem);
+    auto issue = [&](int tt, int st) {
 #pragma unroll
-    for (int k = 0; k < DEPTH; ++k) SCORE_ISSUE(jt0 + k, k);
-    SCORE_COMMIT(0, 0);
-    SCORE_COMMIT(1, 1);
-    SCORE_ISSUE(jt0 + DEPTH, 0);
-    SCORE_ISSUE(jt0 + DEPTH + 1, 1);
-    __syncthreads();
-    // The first ring turn is peeled: the loop is then entered with the same
-    // loads and stores in flight as at its back edge, so the compiler's wait
-    // for a staged tile is for that tile's loads only, not for the stores
-    // issued after them (stores count in vmcnt on this architecture).  The
-    // chunk runs whole ring turns (tiles past ntile are padding).
-    const int nturn = (ntile + DEPTH - 1) / DEPTH;
+      for (int k = 0; k < L; ++k) {
+        const int c = wave + k * W;
+        if (2 * CH % W == 0 || c < 2 * CH) {
+          const int w = c % CH;
+          const int64_t row = s_row[tt * 32 + (c / CH) * 16 + m16];
+          const T* src = (w < NV ? K : V) + row * D;
+          copy16_to_lds(reinterpret_cast<const uint4*>(src) + 4 * (w % NV) + g,
+                        ring + (uint32_t)(st * SS::STAGE + c * 1024));
+        }
+      }
+    };
+    issue(0, 0);
+    if (ntile > 1) issue(1, 1);
+    // scale exponent of every column row for every block of the group
+    float mB[NBW];
 #pragma unroll
-    for (int u = 0; u < DEPTH; ++u) SCORE_TILE(false, u, u);
-    for (int ib = DEPTH; ib < nturn * DEPTH; ib += DEPTH) {
+    for (int b = 0; b < NBW; ++b) mB[b] = fmaxf(s_mh[2 * b], s_mh[2 * b + 1]);
 #pragma unroll
-      for (int u = 0; u < DEPTH; ++u) SCORE_TILE(false, ib + u, u);
+    for (int k = 0; k < RPT; ++k) {
+      const int o = (int)threadIdx.x + k * 64 * W;
+      // 0 for rows past the bucket (whole pairs: N is even)
+      const int j = (jc0 + (o >> 5)) * 32 + frag_row((o >> 4) & 1, o & 15);
+      const float h2 = j < N ? pair_h2f(rh[k]) : 0.0f;
+      if (o < 32 * ntile) {
+#pragma unroll
+        for (int b = 0; b < NBW; ++b) s_he[b * kScoreRowsStaged + o] = h2 + scale_shift(mB[b], h2);
+      }
     }
-    SCORE_FLUSH(false, nturn * DEPTH - 1, (nturn * DEPTH - 1) % NS);
+    // fragments and the first two tiles (and what the compiler has in flight)
+    __builtin_amdgcn_s_waitcnt(0x0F70);
+    const float* he = s_he + lblk * kScoreRowsStaged + m16;
+    int st = 0;
+    for (int tt = 0; tt < ntile; ++tt) {
+      // This wave's copies of tile tt are done once at most its newer
+      // operations are outstanding: the stores of tiles tt - 2 and tt - 1 and
+      // the copies of tile tt + 1 (none for the last tile).
+      if (tt + 1 < ntile) wait_vmcnt<L + 2>(); else wait_vmcnt<2>();
+      __syncthreads();
+      if (NS == 3 && tt + 2 < ntile) issue(tt + 2, st == 0 ? 2 : st - 1);
+      const unsigned char* sp = smem + st * SS::STAGE;
+      float f0[4], f1[4];
+      score_f<T, NV>(Ak, Av, sp, lane, vm2f, c2, he[tt * 32], f0);
+      score_f<T, NV>(Ak, Av, sp + CH * 1024, lane, vm2f, c2, he[tt * 32 + 16], f1);
+      if (NS == 2) {
+        __syncthreads();  // every wave has read the stage
+        if (tt + 2 < ntile) issue(tt + 2, st);
+      }
+      const float4 e = score_e(f0, f1, odd);
+      if (in_panel(jc0 + tt)) *reinterpret_cast<float4*>(ew + (int64_t)(jc0 + tt) * 256) = e;
+      st = st == NS - 1 ? 0 : st + 1;
+    }
   }
-#undef SCORE_TILE
-#undef SCORE_MMA_LDS
-#undef SCORE_FLUSH
-#undef SCORE_EPI_H
-#undef SCORE_MMA_H
-#undef SCORE_BFRAG
-#undef SCORE_ACTIVE
-#undef SCORE_ISSUE
-#undef SCORE_COMMIT
-#undef SCORE_OWN_WRITE
-#undef SCORE_OWN_COMMIT
 }
 
 // Buckets of at most 64 rows (one decision block of P <= 32 pairs): one
@@ -1297,7 +1290,7 @@ struct PassLds {
   static constexpr int CW = QW + 1;
   static constexpr bool COAL = BW >= 6;
   static constexpr size_t kSlot = BP * 8 + 2 * BP * 4 + 2 * BP * CW * 16;
-  static constexpr size_t kColBuf = COAL ? 64 * CW * 16 : 0;
+  static constexpr size_t kColBuf = COAL ? 64 * QW * 16 : 0;
   static_assert(2 + BW <= 16, "counter block");
   __host__ __device__ static size_t mask_off(int P) { return ((size_t)P * 8 + 15) & ~(size_t)15; }
   __host__ __device__ static size_t flag_off(int P) {
@@ -1386,10 +1379,28 @@ __global__ __launch_bounds__(64 * (BW + 2)) void halve_pass_kernel(HalveArgs a) 
         SUM += (((SMASK) >> (4 * q_ + c_)) & 1u) ? -e_[c_] : e_[c_];                   \
     }                                                                                  \
   } while (0)
-  // Column of pair P_ in block B's score panel (P_ at or after block B).
-#define PASS_COL(B, P_)                                                                 \
-  reinterpret_cast<const u32x4*>(Eb + (panel_tiles(B, NT, RT) + ((P_) >> 3) - (B) * RT) * TILE + \
-                                 ((P_) & 7) * BP)
+  // 16-byte word Q_ (0..7: pairs i = 4 Q_ .. 4 Q_ + 3 of the block) of the
+  // column of pair P_ in block B's score panel (P_ at or after block B).
+#define PASS_WORD(B, P_, Q_)                                                            \
+  reinterpret_cast<const u32x4*>(Eb + panel_tiles(B, NT, RT) * TILE +                  \
+                                 ((Q_) >> 2) * half_plane(B, NT, RT) +                 \
+                                 ((P_) - (B) * BP) * 16)[(Q_) & 3]
+  // A chunk's 64 columns of one block with COAL: word lane % 4 of half k >> 2
+  // of column 16 (k & 3) + lane / 4 per load (1 KiB in a row), turned through
+  // the wave's column buffer.  Column c's word w of a half sits at slot
+  // w ^ (c / 2 % 4) of the column's four: both the writes (two columns per
+  // eight lanes) and the reads (one word of eight columns) hit every bank once.
+#define PASS_LOAD(B, C0, K) \
+  PASS_WORD(B, min((C0) + 16 * ((K) & 3) + lane / 4, P - 1), 4 * ((K) >> 2) + lane % 4)
+#define PASS_TURN(BUF, SRC, COL)                                                        \
+  do {                                                                                 \
+    _Pragma("unroll") for (int k_ = 0; k_ < 8; ++k_) {                                 \
+      const int c_ = 16 * (k_ & 3) + lane / 4;                                         \
+      BUF[256 * (k_ >> 2) + 4 * c_ + (lane % 4 ^ ((c_ >> 1) & 3))] = SRC[k_];          \
+    }                                                                                  \
+    _Pragma("unroll") for (int q_ = 0; q_ < QW; ++q_)                                  \
+      COL[q_] = BUF[256 * (q_ >> 2) + 4 * lane + ((q_ & 3) ^ ((lane >> 1) & 3))];      \
+  } while (0)
 
   if (role > 0) {
     // ---- helper (waves 2..): the early rows of chunks ----
@@ -1423,13 +1434,11 @@ __global__ __launch_bounds__(64 * (BW + 2)) void halve_pass_kernel(HalveArgs a) 
       ic = live ? fc : nch;
       if constexpr (L::COAL) {
 #pragma unroll
-        for (int k = 0; k < 8; ++k)
-          dst[k] = (live ? PASS_COL(fb, min(64 * fc + 8 * k + lane / QW, P - 1))
-                         : PASS_COL(0, lane / QW))[lane % QW];
+        for (int k = 0; k < 8; ++k) dst[k] = PASS_LOAD(live ? fb : 0, live ? 64 * fc : 0, k);
       } else {
-        const u32x4* c_ = live ? PASS_COL(fb, min(64 * fc + lane, P - 1)) : PASS_COL(0, 0);
 #pragma unroll
-        for (int k = 0; k < 8; ++k) dst[k] = c_[k];
+        for (int k = 0; k < 8; ++k)
+          dst[k] = PASS_WORD(live ? fb : 0, live ? min(64 * fc + lane, P - 1) : 0, k);
       }
       // lane 0's read, broadcast only when the item is used: the wave does
       // not wait for it here
@@ -1457,10 +1466,7 @@ __global__ __launch_bounds__(64 * (BW + 2)) void halve_pass_kernel(HalveArgs a) 
         const uint32_t smask = live ? decided_mask(gm + b, w0, helper_tag(a.pass_tag, b), a.status) : 0u;
         u32x4 col[QW];
         if constexpr (L::COAL) {
-#pragma unroll
-          for (int k = 0; k < 8; ++k) colbuf[(8 * k + lane / QW) * L::CW + lane % QW] = cb[r][k];
-#pragma unroll
-          for (int q = 0; q < QW; ++q) col[q] = colbuf[lane * L::CW + q];
+          PASS_TURN(colbuf, cb[r], col);
         } else {
 #pragma unroll
           for (int q = 0; q < QW; ++q) col[q] = cb[r][q];
@@ -1559,13 +1565,12 @@ __global__ __launch_bounds__(64 * (BW + 2)) void halve_pass_kernel(HalveArgs a) 
   do {                                                                                 \
     const int b_ = min(B, nblk - 1);                                                   \
     const int npb_ = min(BP, P - b_ * BP);                                             \
-    const float* e_ = Eb + panel_tiles(b_, NT, RT) * TILE;                             \
     _Pragma("unroll") for (int r_ = 0; r_ < 4; ++r_) {                                 \
       const int pc_ = min(lane / QW + 8 * r_, npb_ - 1);                               \
-      fo[K][r_] = reinterpret_cast<const u32x4*>(e_ + (pc_ >> 3) * TILE + (pc_ & 7) * BP)[lane % QW]; \
+      fo[K][r_] = PASS_WORD(b_, b_ * BP + pc_, lane % QW);                             \
       /* next block's pairs (the last block reads its own last column) */           \
       const int pn_ = min((b_ + 1) * BP + lane / QW + 8 * r_, P - 1);                  \
-      fn[K][r_] = PASS_COL(b_, pn_)[lane % QW];                                        \
+      fn[K][r_] = PASS_WORD(b_, pn_, lane % QW);                                       \
     }                                                                                  \
     const int gp_ = b_ * BP + min(lane & (BP - 1), npb_ - 1);                          \
     flbt[K] = a.lbt[pb + gp_];                                                         \
@@ -1658,13 +1663,11 @@ __global__ __launch_bounds__(64 * (BW + 2)) void halve_pass_kernel(HalveArgs a) 
       // used)
       if constexpr (L::COAL) {
 #pragma unroll
-        for (int k = 0; k < 8; ++k)
-          dst[k] = (live ? PASS_COL(fb, min(64 * fc + 8 * k + lane / QW, P - 1))
-                         : PASS_COL(0, lane / QW))[lane % QW];
+        for (int k = 0; k < 8; ++k) dst[k] = PASS_LOAD(live ? fb : 0, live ? 64 * fc : 0, k);
       } else {
-        const u32x4* c_ = live ? PASS_COL(fb, min(64 * fc + lane, P - 1)) : PASS_COL(0, 0);
 #pragma unroll
-        for (int k = 0; k < 8; ++k) dst[k] = c_[k];
+        for (int k = 0; k < 8; ++k)
+          dst[k] = PASS_WORD(live ? fb : 0, live ? min(64 * fc + lane, P - 1) : 0, k);
       }
       if (live && ++fb > last_row(fc)) {
         fc += BW;
@@ -1700,10 +1703,7 @@ __global__ __launch_bounds__(64 * (BW + 2)) void halve_pass_kernel(HalveArgs a) 
         const uint32_t smask = s_mask[live ? b : 0];
         u32x4 col[QW];
         if constexpr (L::COAL) {
-#pragma unroll
-          for (int k = 0; k < 8; ++k) colbuf[(8 * k + lane / QW) * L::CW + lane % QW] = cb[r][k];
-#pragma unroll
-          for (int q = 0; q < QW; ++q) col[q] = colbuf[lane * L::CW + q];
+          PASS_TURN(colbuf, cb[r], col);
         } else {
 #pragma unroll
           for (int q = 0; q < QW; ++q) col[q] = cb[r][q];
@@ -1720,7 +1720,9 @@ __global__ __launch_bounds__(64 * (BW + 2)) void halve_pass_kernel(HalveArgs a) 
     }
   }
 #undef PASS_SUM
-#undef PASS_COL
+#undef PASS_WORD
+#undef PASS_LOAD
+#undef PASS_TURN
 }
 
 // Gram of rows [0,16) against rows [16,32) through the fragment path used by
@@ -1750,7 +1752,7 @@ hipError_t launch_scores_td(const HalveArgs& a0, int64_t nbk, hipStream_t st) {
   using SS = ScoreShape<T, D, WO>;  // own and streamed chunks share the groups
   auto kern_mixed = pair_scores_kernel<T, D, false, false, WO>;
   auto kern_own = pair_scores_kernel<T, D, false, true, WO>;
-  const size_t lds = SS::LDS, lds_own = SS::LDS;
+  const size_t lds = SS::LDS, lds_own = SS::LDS_OWN;
   if (lds > 64 * 1024) {
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern_mixed),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
@@ -1761,9 +1763,10 @@ hipError_t launch_scores_td(const HalveArgs& a0, int64_t nbk, hipStream_t st) {
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_own);
     if (e != hipSuccess) return e;
   }
-  const int64_t NT = (a0.N + 15) / 16;
-  const int64_t groups = (NT + SS::GT - 1) / SS::GT;
-  const int64_t rest = NT > SS::GT ? NT - SS::GT : 0;  // tiles after the first group
+  const int64_t NC = (a0.N + 31) / 32;  // 32-row column tiles
+  constexpr int64_t GC = SS::GT / 2;    // per group
+  const int64_t groups = (NC + GC - 1) / GC;
+  const int64_t rest = NC > GC ? NC - GC : 0;  // tiles after the first group
   // Column tiles per streamed chunk (one workgroup's tiles, taken one after
   // the other): kScoreChunkLong while the launch keeps at least four
   // workgroups per CU (each workgroup loads its group's fragments once, for
@@ -1774,13 +1777,13 @@ hipError_t launch_scores_td(const HalveArgs& a0, int64_t nbk, hipStream_t st) {
   auto workgroups = [&](int64_t c) {
     int64_t w = 0;
     for (int64_t g = 0; g < groups; ++g) {
-      const int64_t rest_g = NT - (g + 1) * SS::GT;
+      const int64_t rest_g = NC - (g + 1) * GC;
       w += 1 + (rest_g > 0 ? (rest_g + c - 1) / c : 0);
     }
     return w * nbk;
   };
   if (workgroups(kScoreChunkLong) >= kScoreLongWorkgroups) a.ch = kScoreChunkLong;
-  for (const int c : {15, 9, 6})
+  for (const int c : {8, 5, 3})
     if (workgroups(a.ch) <= kScoreMinWorkgroups && c < a.ch) a.ch = c;
   const int64_t nch = 1 + (rest + a.ch - 1) / a.ch;
   // one workgroup per (bucket, group, chunk) with work, buckets padded to a
@@ -1792,7 +1795,7 @@ hipError_t launch_scores_td(const HalveArgs& a0, int64_t nbk, hipStream_t st) {
     x.nbk = nbk;
     int64_t ipb = 0;
     for (int64_t g = 0; g < groups; ++g) {
-      const int64_t rest_g = NT - (g + 1) * SS::GT;
+      const int64_t rest_g = NC - (g + 1) * GC;
       const int64_t nsc = rest_g > 0 ? (rest_g + a.ch - 1) / a.ch : 0;
       ipb += std::max<int64_t>(0, std::min<int64_t>(chunk0 + nz, 1 + nsc) - chunk0);
     }
@@ -1850,12 +1853,11 @@ hipError_t launch_local_td(const HalveArgs& a0, int64_t nbk, hipStream_t st) {
   using SS = ScoreShape<T, D, WO>;
   auto kern = pair_scores_kernel<T, D, true, true, WO>;
   const int64_t NT = (a0.N + 15) / 16, nb = (a0.N + 63) / 64, P = a0.N / 2;
-  // stages, score tiles, pair scale exponents of the rows, staged row
-  // scales, half-block row scale maxima, pair terms [2][P], then (8-byte
-  // aligned) the decisions' thresholds and alphas [2][BLOCKS][64] and masks
-  const size_t lds = (size_t)kScoreStages * SS::CHUNKS * 1024 +
-                     (size_t)panel_tiles(nb, NT, 4) * kETileLds * 4 + SS::GT * 16 * 4 +
-                     kScoreStages * 16 * 4 + 2 * SS::BLOCKS * 4 + 2 * P * 4 + 8 +
+  // ring, score tiles, pair scale exponents of the rows, half-block row scale
+  // maxima, pair terms [2][P], then (8-byte aligned) the decisions' thresholds
+  // and alphas [2][BLOCKS][64] and masks
+  const size_t lds = (size_t)SS::OWN_RING + (size_t)panel_tiles(nb, NT, 4) * kETileLds * 4 +
+                     SS::GT * 16 * 4 + 2 * SS::BLOCKS * 4 + 2 * P * 4 + 8 +
                      2 * 64 * SS::BLOCKS * 8 + SS::BLOCKS * 4;
   if (lds > 64 * 1024) {
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
