@@ -334,7 +334,6 @@ int compress_impl(const void* K, const void* V, int32_t dtype, int64_t B, int64_
       a.gflag = ws.gflag;
       a.galpha = ws.galpha;
       a.pass_tag = r + 1;
-      a.chunk0 = 0;
       a.b0 = 0;
       ok(kh_round(dtype, d, a, S * lv.G[r], ws.e_bytes, r, st));
       u_off += lv.n_r[r] / 2;
@@ -571,7 +570,6 @@ hipError_t ex_halve(thin_express* x, const ExRun* run, const int32_t* in, int64_
   a.rowh2_write = 1;
   a.mB = ex_ptr<float>(x, x->L.mB);
   a.status = ex_ptr<int32_t>(x, x->L.status);
-  a.chunk0 = 0;
   a.b0 = 0;
   return kh_round(x->dtype, x->d, a, x->S, x->L.e_bytes, -1, st);
 }

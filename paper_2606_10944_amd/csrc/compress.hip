@@ -406,21 +406,20 @@ __device__ __forceinline__ void frag_pair_terms(const uint4* fk, const uint4* fv
 //
 // Score layout of one bucket (BR = 16 RT rows = BP pairs per block, NT =
 // ceil(N/16) row tiles): panel B (the block's BP pairs as i) holds every pair
-// p of the column tiles jt = B RT .. NT-1 (8 pairs each), as two half-planes:
-// pairs i = 0..15 of the block, then i = 16..31, each [p][16 i], so a pair's
-// scores are two runs of 64 bytes and a wave of the score kernel, which forms
-// the scores of one half-block against 16 pairs at a time, writes 1 KiB in a
-// row with one 16-byte store per lane.  Panel B starts panel_tiles(B) KiB
-// into the bucket's array.
+// p of the column tiles jt = B RT .. NT-1 (8 pairs each) in runs of 16 pairs
+// (8 in the last one when NT is odd), each run the block's pairs i = 0..15 as
+// [p][16 i], then i = 16..31, so a pair's scores are two pieces of 64 bytes
+// and a wave of the score kernel, which forms the scores of one half-block
+// against 16 pairs at a time, writes 1 KiB in a row with one 16-byte store per
+// lane.  Panel B starts panel_tiles(B) KiB into the bucket's array.
 // ---------------------------------------------------------------------------
 __host__ __device__ inline int64_t panel_tiles(int64_t B, int64_t NT, int64_t RT) {
   return B * NT - RT * B * (B - 1) / 2;
 }
 
-// Floats of one half-plane of panel B.
-__host__ __device__ inline int64_t half_plane(int64_t B, int64_t NT, int64_t RT) {
-  return (NT - B * RT) * 8 * 16;
-}
+// Floats from i = 0..15 to i = 16..31 in the run of pairs 16 u .. (whole
+// bucket; RT is even).
+__host__ __device__ inline int half_run(int u, int NT) { return 2 * u + 1 < NT ? 256 : 128; }
 
 // Work decomposition of pair_scores_kernel.  A group is BLOCKS = W / 2
 // consecutive decision blocks (64 rows each) of one bucket; each of the
@@ -430,11 +429,12 @@ __host__ __device__ inline int64_t half_plane(int64_t B, int64_t NT, int64_t RT)
 // waves per SIMD, two workgroups per CU, whose latencies hide each other's),
 // else W = 4 (fp32, d = 128).  Every launch of a bucket size uses the same W,
 // so own and streamed chunks share their groups.  A workgroup handles one
-// (bucket, group, chunk): chunk 0 covers the group's own column tiles, which
-// the owning waves write to LDS from their registers (so the bucket's rows
-// are read from HBM once); chunk c >= 1 covers kScoreChunk column tiles of 32
-// rows after the group (kScoreChunkLong in launches of many workgroups, fewer
-// in launches of few), copied from global memory straight into LDS.
+// (bucket, group, chunk): the own chunk covers the group's own column tiles,
+// which the owning waves write to LDS from their registers (so the bucket's
+// rows are read from HBM once); a streamed chunk the column tiles after the
+// group in one of the bucket's stretches of ch tiles of 32 rows (kScoreChunk,
+// more in launches of many workgroups, fewer in launches of few), copied from
+// global memory straight into LDS.
 //   What bounds it: in the tile loop the vector ALU (about 75 instructions and
 // 16 exponentials per wave and 32-row tile) and the matrix cores (32 MFMAs)
 // are both about 80 % busy (2700 cycles per tile for the four waves of a SIMD,
@@ -445,13 +445,13 @@ __host__ __device__ inline int64_t half_plane(int64_t B, int64_t NT, int64_t RT)
 // launches of 65536 rows x 32 slices (d = 128, bf16) 3.40 -> 3.04 ms, of 16384
 // rows x 64 slices 455 -> 383 us.
 constexpr int kScoreChunk = 16;
-constexpr int kScoreChunkLong = 24;
+constexpr int kScoreChunkMax = 32;
 #ifndef SCORE_MIN_WGS
 #define SCORE_MIN_WGS 128
 #endif
 constexpr int64_t kScoreMinWorkgroups = SCORE_MIN_WGS;  // half the CUs
 constexpr int64_t kScoreLongWorkgroups = 1024;         // four per CU
-constexpr int kScoreRowsStaged = kScoreChunkLong * 32;  // rows of a streamed chunk, at most
+constexpr int kScoreRowsStaged = kScoreChunkMax * 32;  // rows of a streamed chunk, at most
 // A score tile (8 column pairs x 32 row pairs) in the local kernel's LDS:
 // column stride 36 floats, so that the decisions' reads of whole columns by
 // consecutive lanes fall in different banks.
@@ -474,10 +474,11 @@ struct ScoreShape {
   static constexpr int LPT = (2 * CHUNKS + W - 1) / W;  // copies per wave and tile
   // ring, scales of the column rows per block, column row indices, the
   // half-blocks' largest row scales
-  static constexpr int LDS_STREAM = STAGES * STAGE + kScoreRowsStaged * 4 * (BLOCKS + 1) + 2 * BLOCKS * 4;
+  static constexpr int lds_stream(int ch) {
+    return STAGES * STAGE + ch * 32 * 4 * (BLOCKS + 1) + 2 * BLOCKS * 4;
+  }
   // ring, pair scale exponents of the group's rows, the half-blocks' maxima
   static constexpr int LDS_OWN = OWN_RING + GT * 16 * 4 + 2 * BLOCKS * 4;
-  static constexpr int LDS = LDS_STREAM > LDS_OWN ? LDS_STREAM : LDS_OWN;
 };
 
 // Waves of every score launch and of the local kernel (see above).
@@ -673,18 +674,21 @@ void pair_scores_kernel(HalveArgs a) {
   const int NT = (N + 15) >> 4;
   const int NC = (N + 31) >> 5;  // 32-row column tiles
   const int nb = (N + 63) >> 6;
-  // Workgroup -> (bucket, group, chunk).  Workgroups are dealt to the eight
-  // XCDs in turn (linear id mod 8); XCD x takes buckets x, x+8, ... in sets
-  // of il buckets whose workgroups are interleaved, set after set, so the
+  // Workgroup -> (bucket, item).  Workgroups are dealt to the eight XCDs in
+  // turn (linear id mod 8); XCD x takes buckets x, x+8, ... in sets of il
+  // buckets whose workgroups are interleaved, set after set, so the
   // workgroups that share a bucket's rows share one L2 and run close
-  // together.  A bucket's workgroups are its (group, chunk) pairs that have
-  // work, group by group (a workgroup with nothing to do would still take a
-  // dispatch slot).
+  // together.  A bucket's items go column chunk by column chunk, the last
+  // first: the streamed chunks of every group before its last tile, which
+  // read the same column rows one after the other, and beside them the own
+  // chunks of the groups that start in it (their float64 pair terms keep the
+  // vector ALU busy, the streamed chunks the matrix cores).
   int64_t bl;
-  int grp = 0, chunk = 0;
+  int grp = 0, kc = -1;  // kc < 0: the group's own chunk
   if constexpr (LOCAL) {
     bl = blockIdx.x;
   } else {
+    constexpr int GC = GT / 2;
     const int64_t id = blockIdx.x;
     const int64_t k = id >> 3;
     const int64_t per = (int64_t)a.ipb * a.il;
@@ -692,16 +696,23 @@ void pair_scores_kernel(HalveArgs a) {
     bl = (id & 7) + 8 * ((k / per) * a.il + r_ % a.il);
     if (bl >= a.nbk) return;
     int item = r_ / a.il;
-    for (int g_ = 0; g_ < a.ngrp; ++g_) {
-      const int rest_ = NC - (g_ + 1) * (GT / 2);
-      const int nsc_ = rest_ > 0 ? (rest_ + a.ch - 1) / a.ch : 0;  // streamed chunks
-      const int cnt_ = max(0, min(a.chunk0 + a.nz, 1 + nsc_) - a.chunk0);
-      if (item < cnt_) {
-        grp = g_;
-        chunk = a.chunk0 + item;
-        break;
+    if (OWN_ONLY) {
+      grp = item;
+    } else {
+      for (int c = (NC - 1) / a.ch; c >= 0; --c) {
+        const int end = min((c + 1) * a.ch, NC);
+        const int cnt = (end - 1) / GC;  // groups 0 .. cnt - 1 end before the chunk's last tile
+        // groups g0 .. cnt start in the chunk
+        const int g0 = a.own ? (c * a.ch + GC - 1) / GC : cnt + 1;
+        const int n = cnt + max(0, cnt + 1 - g0);
+        if (item < n) {
+          const int j = item - g0;
+          grp = j < 0 ? item : g0 + (j >> 1);
+          if (j < 0 || (j & 1)) kc = c;
+          break;
+        }
+        item -= n;
       }
-      item -= cnt_;
     }
   }
   const int64_t bucket = a.b0 + bl;
@@ -709,10 +720,9 @@ void pair_scores_kernel(HalveArgs a) {
   const int64_t t = bucket % a.G;
   const int jg = grp * (GT / 2);  // the group's first column tile
   if (jg >= NC) return;
-  const bool own = OWN_ONLY || chunk == 0;
-  const int jc0 = own ? jg : jg + GT / 2 + (chunk - 1) * a.ch;
-  if (jc0 >= NC) return;
-  const int ntile = min(jc0 + (own ? GT / 2 : a.ch), NC) - jc0;
+  const bool own = OWN_ONLY || kc < 0;
+  const int jc0 = own ? jg : max(kc * a.ch, jg + GT / 2);
+  const int ntile = min(own ? jg + GT / 2 : (kc + 1) * a.ch, NC) - jc0;
 
   const T* K = reinterpret_cast<const T*>(a.K) + s * a.ld * D;
   const T* V = reinterpret_cast<const T*>(a.V) + s * a.ld * D;
@@ -732,7 +742,7 @@ void pair_scores_kernel(HalveArgs a) {
   float* s_h2 = s_e + (LOCAL ? (int)panel_tiles(nb, NT, 4) : 0) * kETileLds;
   float* s_mh = own ? s_h2 + GT * 16
                     : reinterpret_cast<float*>(smem + SS::STAGES * SS::STAGE) +
-                          kScoreRowsStaged * (NBW + 1);  // [2 * NBW]
+                          32 * a.ch * (NBW + 1);  // [2 * NBW]
   float* s_lbt = s_mh + 2 * NBW;  // LOCAL: pair terms [P] and [P]
   float* s_h2p = s_lbt + P;
   // LOCAL decisions: per block and lane the threshold and the bulk alpha of
@@ -741,9 +751,9 @@ void pair_scores_kernel(HalveArgs a) {
   double* s_alpha = s_thr + 64 * NBW;
   uint32_t* s_mask = reinterpret_cast<uint32_t*>(s_alpha + 64 * NBW);
   // streamed chunks: ring | scale exponents of the column rows for each of
-  // the group's blocks [NBW][kScoreRowsStaged] | column row indices
+  // the group's blocks [NBW][32 ch] | column row indices
   float* s_he = reinterpret_cast<float*>(smem + SS::STAGES * SS::STAGE);
-  int32_t* s_row = reinterpret_cast<int32_t*>(s_he + kScoreRowsStaged * NBW);
+  int32_t* s_row = reinterpret_cast<int32_t*>(s_he + 32 * a.ch * NBW);
 
   // ---- this wave's half-block: rows, fragments and, in chunk 0, pair terms ----
   const int lblk = wave >> 1, half = wave & 1;
@@ -839,8 +849,10 @@ void pair_scores_kernel(HalveArgs a) {
   const int q = 4 * (m16 >> 2) + 2 * (odd ? 1 : 0) + ((m16 >> 1) & 1);
   float* ew = nullptr;
   if constexpr (!LOCAL)
-    ew = a.E + (bl * a.e_tiles + panel_tiles(blk, NT, 4)) * 256 + half * half_plane(blk, NT, 4) -
-         (int64_t)blk * 512 + q * 16 + 4 * g;
+    ew = a.E + (bl * a.e_tiles + panel_tiles(blk, NT, 4) - 4 * blk) * 256 + q * 16 + 4 * g;
+  auto e_tile = [&](int jc) {
+    return reinterpret_cast<float4*>(ew + (int64_t)jc * 512 + half * half_run(jc, NT));
+  };
   auto in_panel = [&](int jc) { return 2 * jc + (q >> 3) < NT; };
 
   // LOCAL: the decisions of the bucket's P <= 32 NBW pairs from the scores
@@ -961,7 +973,7 @@ void pair_scores_kernel(HalveArgs a) {
               *reinterpret_cast<float4*>(col + 16 * half + 4 * g) = e;
             }
           } else if (in_panel(jc0 + tt)) {
-            *reinterpret_cast<float4*>(ew + (int64_t)(jc0 + tt) * 256) = e;
+            *e_tile(jc0 + tt) = e;
           }
         }
       }
@@ -1013,12 +1025,12 @@ void pair_scores_kernel(HalveArgs a) {
       const float h2 = j < N ? pair_h2f(rh[k]) : 0.0f;
       if (o < 32 * ntile) {
 #pragma unroll
-        for (int b = 0; b < NBW; ++b) s_he[b * kScoreRowsStaged + o] = h2 + scale_shift(mB[b], h2);
+        for (int b = 0; b < NBW; ++b) s_he[b * 32 * a.ch + o] = h2 + scale_shift(mB[b], h2);
       }
     }
     // fragments and the first two tiles (and what the compiler has in flight)
     __builtin_amdgcn_s_waitcnt(0x0F70);
-    const float* he = s_he + lblk * kScoreRowsStaged + m16;
+    const float* he = s_he + lblk * 32 * a.ch + m16;
     int st = 0;
     for (int tt = 0; tt < ntile; ++tt) {
       // This wave's copies of tile tt are done once at most its newer
@@ -1036,7 +1048,7 @@ void pair_scores_kernel(HalveArgs a) {
         if (tt + 2 < ntile) issue(tt + 2, st);
       }
       const float4 e = score_e(f0, f1, odd);
-      if (in_panel(jc0 + tt)) *reinterpret_cast<float4*>(ew + (int64_t)(jc0 + tt) * 256) = e;
+      if (in_panel(jc0 + tt)) *e_tile(jc0 + tt) = e;
       st = st == NS - 1 ? 0 : st + 1;
     }
   }
@@ -1382,9 +1394,9 @@ __global__ __launch_bounds__(64 * (BW + 2)) void halve_pass_kernel(HalveArgs a) 
   // 16-byte word Q_ (0..7: pairs i = 4 Q_ .. 4 Q_ + 3 of the block) of the
   // column of pair P_ in block B's score panel (P_ at or after block B).
 #define PASS_WORD(B, P_, Q_)                                                            \
-  reinterpret_cast<const u32x4*>(Eb + panel_tiles(B, NT, RT) * TILE +                  \
-                                 ((Q_) >> 2) * half_plane(B, NT, RT) +                 \
-                                 ((P_) - (B) * BP) * 16)[(Q_) & 3]
+  reinterpret_cast<const u32x4*>(Eb + (panel_tiles(B, NT, RT) - (B) * RT) * TILE +     \
+                                 (int64_t)((P_) >> 4) * 512 +                          \
+                                 ((Q_) >> 2) * half_run((P_) >> 4, NT) + ((P_) & 15) * 16)[(Q_) & 3]
   // A chunk's 64 columns of one block with COAL: word lane % 4 of half k >> 2
   // of column 16 (k & 3) + lane / 4 per load (1 KiB in a row), turned through
   // the wave's column buffer.  Column c's word w of a half sits at slot
@@ -1752,72 +1764,64 @@ hipError_t launch_scores_td(const HalveArgs& a0, int64_t nbk, hipStream_t st) {
   using SS = ScoreShape<T, D, WO>;  // own and streamed chunks share the groups
   auto kern_mixed = pair_scores_kernel<T, D, false, false, WO>;
   auto kern_own = pair_scores_kernel<T, D, false, true, WO>;
-  const size_t lds = SS::LDS, lds_own = SS::LDS_OWN;
+  const int64_t NC = (a0.N + 31) / 32;  // 32-row column tiles
+  constexpr int64_t GC = SS::GT / 2;    // per group
+  const int64_t groups = (NC + GC - 1) / GC;
+  // streamed items of a bucket: for every column chunk, the groups before its
+  // last tile
+  auto streamed = [&](int64_t c) {
+    int64_t w = 0;
+    for (int64_t k = 0; k * c < NC; ++k) w += (std::min((k + 1) * c, NC) - 1) / GC;
+    return w;
+  };
+  // Column tiles per streamed chunk (one workgroup's tiles, taken one after
+  // the other): long chunks load a group's fragments once for more tiles, so
+  // kScoreChunkMax in launches that keep four workgroups per CU, else
+  // kScoreChunk, or fewer when the launch would leave the device short of
+  // workgroups (a few large buckets: each chunk's tiles are then the launch's
+  // critical path).  32 against 16 tiles: 2048 buckets of 1024 rows 875 -> 818
+  // us, 128 of 4096 rows 724 -> 673 us; with 2.5 workgroups per CU (64 buckets
+  // of 2048 rows) 98 -> 99 us, with 1.75 (64 of 1024 rows) 34 -> 40 us.
+  HalveArgs a = a0;
+  auto workgroups = [&](int64_t c) { return (groups + streamed(c)) * nbk; };
+  if (workgroups(kScoreChunkMax) >= kScoreLongWorkgroups) a.ch = kScoreChunkMax;
+  for (const int c : {8, 5, 3})
+    if (workgroups(a.ch) <= kScoreMinWorkgroups && c < a.ch) a.ch = c;
+  const int lds = std::max(SS::lds_stream(a.ch), (int)SS::LDS_OWN), lds_own = SS::LDS_OWN;
   if (lds > 64 * 1024) {
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern_mixed),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     if (e != hipSuccess) return e;
   }
   if (lds_own > 64 * 1024) {
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern_own),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_own);
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, lds_own);
     if (e != hipSuccess) return e;
   }
-  const int64_t NC = (a0.N + 31) / 32;  // 32-row column tiles
-  constexpr int64_t GC = SS::GT / 2;    // per group
-  const int64_t groups = (NC + GC - 1) / GC;
-  const int64_t rest = NC > GC ? NC - GC : 0;  // tiles after the first group
-  // Column tiles per streamed chunk (one workgroup's tiles, taken one after
-  // the other): kScoreChunkLong while the launch keeps at least four
-  // workgroups per CU (each workgroup loads its group's fragments once, for
-  // more tiles), else kScoreChunk, or fewer when the launch would leave the
-  // device short of workgroups (a few large buckets: each chunk's tiles are
-  // then the launch's critical path)
-  HalveArgs a = a0;
-  auto workgroups = [&](int64_t c) {
-    int64_t w = 0;
-    for (int64_t g = 0; g < groups; ++g) {
-      const int64_t rest_g = NC - (g + 1) * GC;
-      w += 1 + (rest_g > 0 ? (rest_g + c - 1) / c : 0);
-    }
-    return w * nbk;
-  };
-  if (workgroups(kScoreChunkLong) >= kScoreLongWorkgroups) a.ch = kScoreChunkLong;
-  for (const int c : {8, 5, 3})
-    if (workgroups(a.ch) <= kScoreMinWorkgroups && c < a.ch) a.ch = c;
-  const int64_t nch = 1 + (rest + a.ch - 1) / a.ch;
-  // one workgroup per (bucket, group, chunk) with work, buckets padded to a
-  // multiple of the eight XCDs (the padding workgroups return at once)
-  auto launch = [&](HalveArgs x, int chunk0, int nz) {
-    x.chunk0 = chunk0;
-    x.nz = nz;
-    x.ngrp = (int32_t)groups;
+  // one workgroup per (bucket, item), buckets padded to a multiple of the
+  // eight XCDs (the padding workgroups return at once)
+  auto launch = [&](HalveArgs x, bool own, bool stream) {
+    x.own = own;
     x.nbk = nbk;
-    int64_t ipb = 0;
-    for (int64_t g = 0; g < groups; ++g) {
-      const int64_t rest_g = NC - (g + 1) * GC;
-      const int64_t nsc = rest_g > 0 ? (rest_g + a.ch - 1) / a.ch : 0;
-      ipb += std::max<int64_t>(0, std::min<int64_t>(chunk0 + nz, 1 + nsc) - chunk0);
-    }
-    x.ipb = (int32_t)ipb;
+    x.ipb = (int32_t)((own ? groups : 0) + (stream ? streamed(a.ch) : 0));
     x.il = (int32_t)std::min<int64_t>(SCORE_IL, (nbk + 7) / 8);
     const int64_t per_xcd = ((nbk + 7) / 8 + x.il - 1) / x.il * x.il;
-    const int64_t wgs = 8 * per_xcd * ipb;
+    const int64_t wgs = 8 * per_xcd * x.ipb;
     // a launch of own chunks only takes the own-only instantiation
-    if (chunk0 == 0 && nz == 1)
+    if (!stream)
       hipLaunchKernelGGL(kern_own, dim3((unsigned)wgs), dim3(64 * WO), lds_own, st, x);
     else
       hipLaunchKernelGGL(kern_mixed, dim3((unsigned)wgs), dim3(64 * WO), lds, st, x);
   };
-  if (a.rowh2_write && nch > 1) {
+  if (a.rowh2_write && NC > GC) {
     // the streamed chunks read the row scales the own chunks write: two launches
-    launch(a, 0, 1);
+    launch(a, true, false);
     HalveArgs rest_a = a;
     rest_a.rowh2_write = 0;
-    launch(rest_a, 1, (int)(nch - 1));
+    launch(rest_a, false, true);
     return hipGetLastError();
   }
-  launch(a, 0, (int)nch);
+  launch(a, true, NC > GC);
   return hipGetLastError();
 }
 
@@ -1865,7 +1869,6 @@ hipError_t launch_local_td(const HalveArgs& a0, int64_t nbk, hipStream_t st) {
     if (e != hipSuccess) return e;
   }
   HalveArgs a = a0;
-  a.chunk0 = 0;
   a.ch = kScoreChunk;
   a.e_tiles = 0;
   hipLaunchKernelGGL(kern, dim3((unsigned)nbk), dim3(64 * WO), lds, st, a);
