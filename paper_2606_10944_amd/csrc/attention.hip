@@ -592,6 +592,7 @@ hipError_t launch_attn_res_d(int64_t n_out, const void* Q, const void* K, const 
 // (offsets from q0 in [0, 128], start in bits 0-15, end in bits 16-30); a
 // causal key is flagged by bit 31 and takes the point's bias.  Same
 // arithmetic as coreset_attn_kernel, with per-key biases sqrt(d) * logw.
+// This kernel takes float rows.
 // ---------------------------------------------------------------------------
 template <typename T, int D, typename TO>
 __global__ __launch_bounds__(64 * PF_WAVES) __attribute__((amdgpu_waves_per_eu(4))) void prefill_attn_kernel(
@@ -600,7 +601,7 @@ __global__ __launch_bounds__(64 * PF_WAVES) __attribute__((amdgpu_waves_per_eu(4
     const int32_t* __restrict__ c0s, const float* __restrict__ w0s,
     const uint8_t* __restrict__ kept, TO* __restrict__ O) {
   constexpr int NV = Frag<T, D>::NV;
-  constexpr bool BF = Elem<T>::bytes == 2;
+  static_assert(Elem<T>::bytes == 4, "bf16 rows have a kernel of their own, below");
   using L = AttnLds<T, D>;
   __shared__ __align__(16) unsigned char lds[L::bytes];
   // a key's interval of the tile's points that see it (packed as above)
@@ -732,38 +733,10 @@ __global__ __launch_bounds__(64 * PF_WAVES) __attribute__((amdgpu_waves_per_eu(4
       if (key < kc) {
         const int64_t r = s_row[key];
         kw = reinterpret_cast<const uint4*>(Ks + r * D)[wi];
-        if (!BF) vw = reinterpret_cast<const uint4*>(Vs + r * D)[wi];
+        vw = reinterpret_cast<const uint4*>(Vs + r * D)[wi];
       }
       *reinterpret_cast<uint4*>(sK + key * L::k_stride + wi * 16) = kw;
-      if (!BF) *reinterpret_cast<uint4*>(sV + key * L::v_stride + wi * 16) = vw;
-    }
-    if (BF) {
-      // V^T: each thread transposes 8 keys x 8 columns in registers and
-      // writes 8 16-byte rows (one per column)
-      for (int b = threadIdx.x; b < (KC / 8) * WPR; b += 64 * PF_WAVES) {
-        const int kb = b / WPR, db = b % WPR;
-        uint32_t v8[8][4];
-#pragma unroll
-        for (int r8 = 0; r8 < 8; ++r8) {
-          const int key = kb * 8 + r8;
-          uint4 x = make_uint4(0, 0, 0, 0);
-          if (key < kc) x = reinterpret_cast<const uint4*>(Vs + (int64_t)s_row[key] * D)[db];
-          v8[r8][0] = x.x; v8[r8][1] = x.y; v8[r8][2] = x.z; v8[r8][3] = x.w;
-        }
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          const int k = e >> 1;
-          uint4 o;
-          if ((e & 1) == 0) {
-            o.x = pack_lo(v8[0][k], v8[1][k]); o.y = pack_lo(v8[2][k], v8[3][k]);
-            o.z = pack_lo(v8[4][k], v8[5][k]); o.w = pack_lo(v8[6][k], v8[7][k]);
-          } else {
-            o.x = pack_hi(v8[0][k], v8[1][k]); o.y = pack_hi(v8[2][k], v8[3][k]);
-            o.z = pack_hi(v8[4][k], v8[5][k]); o.w = pack_hi(v8[6][k], v8[7][k]);
-          }
-          *reinterpret_cast<uint4*>(sV + (db * 8 + e) * L::v_stride + kb * 16) = o;
-        }
-      }
+      *reinterpret_cast<uint4*>(sV + key * L::v_stride + wi * 16) = vw;
     }
     __syncthreads();
     if (ck + KC < M) gather_meta(ck + KC);
@@ -833,37 +806,17 @@ __global__ __launch_bounds__(64 * PF_WAVES) __attribute__((amdgpu_waves_per_eu(4
 #pragma unroll
         for (int dt = 0; dt < D / 16; ++dt) acc[qt][dt] *= scale;
       }
-      if (BF) {
 #pragma unroll
-        for (int c = 0; c < 2; ++c) {
-          float pv[8];
+      for (int kt = 0; kt < 4; ++kt)
 #pragma unroll
-          for (int j = 0; j < 8; ++j) pv[j] = pr[2 * c + (j >> 2)][j & 3];
-          bf16x8_t bhi, blo;
-          split_bf16x8(pv, bhi, blo);
+        for (int i = 0; i < 4; ++i) {
+          const int key = kt * 16 + 4 * g + i;
 #pragma unroll
           for (int dt = 0; dt < D / 16; ++dt) {
-            const unsigned char* row = sV + (dt * 16 + m16) * L::v_stride;
-            uint2 lo = *reinterpret_cast<const uint2*>(row + (32 * c + 4 * g) * 2);
-            uint2 hi = *reinterpret_cast<const uint2*>(row + (32 * c + 16 + 4 * g) * 2);
-            const bf16x8_t av = __builtin_bit_cast(bf16x8_t, make_uint4(lo.x, lo.y, hi.x, hi.y));
-            acc[qt][dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, bhi, acc[qt][dt], 0, 0, 0);
-            acc[qt][dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, blo, acc[qt][dt], 0, 0, 0);
+            const float av = *reinterpret_cast<const float*>(sV + key * L::v_stride + (dt * 16 + m16) * 4);
+            acc[qt][dt] = __builtin_amdgcn_mfma_f32_16x16x4f32(av, pr[kt][i], acc[qt][dt], 0, 0, 0);
           }
         }
-      } else {
-#pragma unroll
-        for (int kt = 0; kt < 4; ++kt)
-#pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            const int key = kt * 16 + 4 * g + i;
-#pragma unroll
-            for (int dt = 0; dt < D / 16; ++dt) {
-              const float av = *reinterpret_cast<const float*>(sV + key * L::v_stride + (dt * 16 + m16) * 4);
-              acc[qt][dt] = __builtin_amdgcn_mfma_f32_16x16x4f32(av, pr[kt][i], acc[qt][dt], 0, 0, 0);
-            }
-          }
-      }
     }
   }
 
@@ -884,14 +837,348 @@ __global__ __launch_bounds__(64 * PF_WAVES) __attribute__((amdgpu_waves_per_eu(4
   }
 }
 
+// ---------------------------------------------------------------------------
+// The same for bf16 rows.  One workgroup = 8 waves of 16 points; the keys go
+// in chunks of KC, double-buffered in LDS and copied there straight from
+// global memory while the previous chunk is used:
+//  - K in MFMA fragment order (16-key tile, 16-byte word, lane): every
+//    fragment read is 1 KiB in a row;
+//  - V rows as they are, the 32-byte column blocks of row r permuted by
+//    XOR with rot(r), so that the transposing reads of four rows by 16 lanes
+//    hit different banks.  ds_read_b64_tr_b16 gives lane i of 16 column i of
+//    the 4 rows the 16 lanes point at: the A operand of O^T += V^T P^T.
+// A key's row, bias and visibility (from the tile's pieces and candidates) are
+// gathered by one wave two chunks ahead: its list reads overlap a chunk's
+// arithmetic, and one barrier per chunk covers both the copies and them.
+// Chunks whose keys are seen by all the tile's points skip the visibility
+// tests.  Same arithmetic as above in the same order.
+//   What bounds it: per chunk and wave 48 MFMAs (768 cycles), about 170 vector
+// instructions and 17 exponentials (900 cycles and more) and 32 KiB of LDS
+// reads (2048 cycles of the CU's LDS per workgroup and chunk, about what the
+// matrix cores and the vector ALU each need).  Against the kernel above with
+// V turned in registers and nothing in flight during a chunk: 65536 points x
+// 32 slices, d = 128: 3660 -> 2270 us.
+// ---------------------------------------------------------------------------
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ uint2 read_tr16(uint32_t lds) {
+  const s16x4 r = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+      (__attribute__((address_space(3))) s16x4*)(uintptr_t)lds);
+  return __builtin_bit_cast(uint2, r);
+}
+
+template <int D>
+struct PfLds {
+  static constexpr int NV = D / 32;             // 16-byte words per lane of a row fragment
+  static constexpr int KB = KC * D * 2;         // bytes of a chunk's keys (and of its values)
+  static constexpr int COPIES = KB / 1024;      // wave copies of either
+  static constexpr int WPR = D / 8;             // 16-byte words per row
+  static constexpr int STAGE = 2 * KB;
+  static constexpr int bytes = 2 * STAGE;
+  // permutation of row r's 32-byte blocks (D / 16 of them): rows 4 i .. 4 i + 3
+  // get blocks in different banks
+  __device__ static int rot(int r) { return D == 32 ? (r >> 1) & 1 : r & (D / 16 - 1); }
+};
+
+template <int D, typename TO>
+__global__ __launch_bounds__(64 * PF_WAVES) __attribute__((amdgpu_waves_per_eu(4))) void prefill_attn_bf16_kernel(
+    const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, const bf16_t* __restrict__ V,
+    int64_t n, const PrefillTile* __restrict__ tiles, const PrefillSeg* __restrict__ segs,
+    const int32_t* __restrict__ c0s, const float* __restrict__ w0s,
+    const uint8_t* __restrict__ kept, TO* __restrict__ O) {
+  using L = PfLds<D>;
+  constexpr int NV = L::NV;
+  // [2][K chunk, V chunk], aligned so that address bits can be permuted by XOR
+  extern __shared__ __align__(1024) unsigned char stages[];
+  // a piece: its row list of this slice (null: rows from start on), bias,
+  // interval.  (Lists are read through global-memory pointers: a generic load
+  // counts in lgkmcnt too, and every wave's wait for LDS would then cover it
+  // and, with it, the copies in flight.)
+  typedef const __attribute__((address_space(1))) int32_t* list_t;
+  struct Piece {
+    list_t src;
+    int32_t start;
+    uint32_t vis;
+    float bias;
+  };
+  __shared__ Piece s_piece[kPrefillMaxSegs];
+  __shared__ int32_t s_end[kPrefillMaxSegs];
+  __shared__ int32_t s_c0[QPB];
+  __shared__ float s_w0[QPB];
+  // per key of a chunk (three chunks in turn): row, bias, visibility; and how
+  // the chunk is tested: 2, every point sees every key; 1, by interval; 0, by
+  // interval and with causal keys that take the point's own bias
+  __shared__ int32_t s_row[3][KC];
+  __shared__ __align__(16) float s_bias[3][KC];
+  __shared__ __align__(16) uint32_t s_vis[3][KC];
+  __shared__ int32_t s_test[3];
+  __shared__ int32_t s_w0_differs;
+
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int m16 = lane & 15, g = lane >> 4;
+  const int64_t s = blockIdx.y;
+  const PrefillTile tile = tiles[blockIdx.x];
+  const int32_t q0 = tile.q0, q1 = tile.q1;
+  const int nseg = min(tile.nseg, kPrefillMaxSegs);
+  const bf16_t* Ks = K + s * n * D;
+  const bf16_t* Vs = V + s * n * D;
+  const float sqrt_d = (float)sqrt((double)D);
+  const float c2 = (float)(kLog2e / sqrt((double)D));
+  // points [lo, hi) as offsets in the tile, clipped to it: start in bits 0-15,
+  // length in bits 16-30
+  auto vis = [&](int32_t lo, int32_t hi) {
+    const uint32_t a = (uint32_t)min(max(lo - q0, 0), QPB);
+    const uint32_t b = (uint32_t)min(max(hi - q0, 0), QPB);
+    return a | (b > a ? b - a : 0u) << 16;
+  };
+  if (threadIdx.x == 0) s_w0_differs = 0;
+  if ((int)threadIdx.x < nseg) {
+    const PrefillSeg sg = segs[tile.seg0 + threadIdx.x];
+    s_piece[threadIdx.x] = {(list_t)(sg.g.src ? sg.g.src + s * sg.g.stride : nullptr), (int32_t)sg.g.start,
+                            vis(sg.vlo, sg.vhi), sg.g.logw * sqrt_d};
+    s_end[threadIdx.x] = (int32_t)sg.g.len;
+  }
+  if ((int)threadIdx.x < QPB && q0 + (int)threadIdx.x < q1) {
+    s_c0[threadIdx.x] = c0s[q0 + threadIdx.x];
+    s_w0[threadIdx.x] = w0s[q0 + threadIdx.x];
+  }
+  const int64_t p = (int64_t)q0 + wave * 16 + m16;  // this lane's point
+  uint4 Bq[NV];
+  load_frag<bf16_t, D>(Q + s * n * D, p, g, p < q1, Bq);
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    int32_t e = 0;
+    for (int k = 0; k < nseg; ++k) s_end[k] = (e += s_end[k]);
+  }
+  // a tile whose points share their C_0 weight (all but those where the level
+  // changes) has one bias for its causal keys
+  if ((int)threadIdx.x < QPB && q0 + (int)threadIdx.x < q1 && s_w0[threadIdx.x] != s_w0[0]) s_w0_differs = 1;
+  __syncthreads();
+  const int32_t F = nseg ? s_end[nseg - 1] : 0;
+  const int32_t M = F + (q1 - tile.causal_lo);
+  const int nch = (M + KC - 1) / KC;
+  const uint32_t causal = s_w0_differs ? 0x80000000u : 0u;  // flag of a causal key
+  const float w0 = s_w0[0] * sqrt_d;
+
+  // ---- metadata of a chunk's keys (one wave, lane = key of the chunk) ----
+  int piece = 0;  // the piece of this lane's last key (keys only grow)
+  uint32_t m_vis = 0, m_vis_nk = 0;
+  int32_t m_row = 0;
+  float m_bias = -INFINITY;
+  uint8_t m_kept = 1;
+  auto gather = [&](int ck) {
+    const int32_t kk = ck * KC + lane;
+    m_vis = m_vis_nk = 0;
+    m_bias = -INFINITY;
+    m_kept = 1;
+    m_row = q1 - 1;  // past the last key: a row the tile attends to anyway, seen by none
+    if (kk < F) {
+      while (kk >= s_end[piece]) ++piece;
+      const Piece& pc = s_piece[piece];
+      const int32_t j = kk - (piece ? s_end[piece - 1] : 0);
+      m_row = pc.src ? pc.src[j] : pc.start + j;
+      m_bias = pc.bias;
+      m_vis = m_vis_nk = pc.vis;
+    } else if (kk < M) {
+      m_row = tile.causal_lo + (kk - F);
+      m_kept = kept[m_row];
+      // the tile's points whose C_0 starts at or before the candidate: a prefix
+      int lo = 0, hi = q1 - q0;
+      while (lo < hi) {
+        const int mid = (lo + hi) >> 1;
+        if (s_c0[mid] <= m_row) lo = mid + 1; else hi = mid;
+      }
+      m_vis = vis(m_row, max(m_row + 1, q0 + lo)) | causal;
+      m_vis_nk = vis(m_row, m_row + 1) | causal;
+      m_bias = w0;
+    }
+  };
+  auto commit = [&](int slot) {
+    const uint32_t v = m_kept ? m_vis : m_vis_nk;
+    s_row[slot][lane] = m_row < 0 ? 0 : (m_row >= n ? (int32_t)(n - 1) : m_row);
+    s_bias[slot][lane] = m_bias;
+    s_vis[slot][lane] = v;
+    const bool all = (int32_t)v >= 0 && (v & 0xffffu) == 0 && (int32_t)(v >> 16) >= q1 - q0;
+    const bool every = __ballot(all) == ~(uint64_t)0, own = __ballot((int32_t)v < 0) != 0;
+    if (lane == 0) s_test[slot] = every ? 2 : own ? 0 : 1;
+  };
+  // ---- copies of a chunk's rows into stage b ----
+  const uint32_t lds0 = lds_offset(stages);
+  auto copies = [&](int slot, int b) {
+#pragma unroll
+    for (int k = 0; k < (L::COPIES + PF_WAVES - 1) / PF_WAVES; ++k) {
+      const int c = wave + k * PF_WAVES;
+      if (L::COPIES % PF_WAVES == 0 || c < L::COPIES) {
+        // keys: fragment word v of 16-key tile kt
+        const int kt = c / NV, v = c % NV;
+        const int64_t rk = s_row[slot][kt * 16 + m16];
+        copy16_to_lds(reinterpret_cast<const uint4*>(Ks + rk * D) + 4 * v + g,
+                      lds0 + (uint32_t)(b * L::STAGE + c * 1024));
+        // values: 1024 / (2 D) rows, blocks permuted
+        const int r = c * (64 / L::WPR) + lane / L::WPR, w = lane % L::WPR;
+        const int64_t rv = s_row[slot][r];
+        copy16_to_lds(reinterpret_cast<const uint4*>(Vs + rv * D) + (((w >> 1) ^ L::rot(r)) << 1 | (w & 1)),
+                      lds0 + (uint32_t)(b * L::STAGE + L::KB + c * 1024));
+      }
+    }
+  };
+  if (wave == 0) {
+    gather(0);
+    commit(0);
+    gather(1);
+    commit(1);
+  }
+  __syncthreads();
+  copies(0, 0);
+
+  float mrun = -INFINITY, lrun = 0.0f;
+  floatx4_t acc[D / 16];
+#pragma unroll
+  for (int dt = 0; dt < D / 16; ++dt) acc[dt] = (floatx4_t){0.f, 0.f, 0.f, 0.f};
+  const uint32_t pl = (uint32_t)(p - q0);  // this point's offset in the tile
+  const float pw0 = p < q1 ? s_w0[pl] * sqrt_d : 0.f;
+  // this lane's address of the transposing reads, but for the stage and block
+  const int vr = 4 * g + (m16 >> 2);
+  const uint32_t v_lane = (uint32_t)(L::KB + vr * D * 2 + L::rot(vr) * 32 + (m16 & 3) * 8);
+
+  // The queries are waited for here, where the compiler sees it: their first
+  // use is in the loop, whose every turn would else wait for the copies too.
+  __builtin_amdgcn_s_waitcnt(0x0F70);
+#pragma unroll
+  for (int v = 0; v < NV; ++v)
+    asm volatile("" : "+v"(Bq[v].x), "+v"(Bq[v].y), "+v"(Bq[v].z), "+v"(Bq[v].w));
+  int slot = 0;
+  for (int ck = 0; ck < nch; ++ck) {
+    const int b = ck & 1;
+    const int nslot = slot == 2 ? 0 : slot + 1;
+    wait_vmcnt<0>();  // this wave's copies of chunk ck
+    __syncthreads();
+    if (ck + 1 < nch) copies(nslot, b ^ 1);
+    if (wave == 0 && ck + 2 < nch) gather(ck + 2);
+
+    // the lane's 16 keys: bias where the point sees the key, else -inf
+    float sc[4][4];
+    const int test = s_test[slot];
+#pragma unroll
+    for (int kt = 0; kt < 4; ++kt) {
+      const float4 b4 = *reinterpret_cast<const float4*>(&s_bias[slot][kt * 16 + 4 * g]);
+      sc[kt][0] = b4.x; sc[kt][1] = b4.y; sc[kt][2] = b4.z; sc[kt][3] = b4.w;
+    }
+    if (test < 2) {
+      uint32_t wv[4][4];
+#pragma unroll
+      for (int kt = 0; kt < 4; ++kt) {
+        const uint4 w4 = *reinterpret_cast<const uint4*>(&s_vis[slot][kt * 16 + 4 * g]);
+        wv[kt][0] = w4.x; wv[kt][1] = w4.y; wv[kt][2] = w4.z; wv[kt][3] = w4.w;
+      }
+      if (test == 0) {
+#pragma unroll
+        for (int kt = 0; kt < 4; ++kt)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            if ((int32_t)wv[kt][i] < 0) sc[kt][i] = pw0;
+            wv[kt][i] &= 0x7fffffffu;
+          }
+      }
+#pragma unroll
+      for (int kt = 0; kt < 4; ++kt)
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          sc[kt][i] = pl - (wv[kt][i] & 0xffffu) < (wv[kt][i] >> 16) ? sc[kt][i] : -INFINITY;
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    const uint4* sk = reinterpret_cast<const uint4*>(stages + b * L::STAGE);
+    float mx = -INFINITY;
+#pragma unroll
+    for (int kt = 0; kt < 4; ++kt) {
+      uint4 ak[NV];
+#pragma unroll
+      for (int v = 0; v < NV; ++v) ak[v] = sk[(kt * NV + v) * 64 + lane];
+      floatx4_t z = {0.f, 0.f, 0.f, 0.f};
+      z = mma_rows<bf16_t, D>(ak, Bq, z);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        sc[kt][i] += z[i];  // -inf stays -inf
+        mx = fmaxf(mx, sc[kt][i]);
+      }
+    }
+    mx = fmaxf(mx, __shfl_xor(mx, 16));
+    mx = fmaxf(mx, __shfl_xor(mx, 32));
+    const float mnew = fmaxf(mrun, mx);
+    const float scale = (mrun == -INFINITY || mnew == -INFINITY)
+                            ? 0.0f : __builtin_amdgcn_exp2f((mrun - mnew) * c2);
+    mrun = mnew;
+    // exp2(-inf) = 0 for the keys the point does not see; a row that sees
+    // none yet subtracts 0 instead of -inf
+    const float mref = mnew == -INFINITY ? 0.0f : mnew;
+    float psum = 0.0f;
+#pragma unroll
+    for (int kt = 0; kt < 4; ++kt)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        sc[kt][i] = __builtin_amdgcn_exp2f((sc[kt][i] - mref) * c2);
+        psum += sc[kt][i];
+      }
+    lrun = lrun * scale + psum;
+    // (the running maxima of most chunks stay put: no rescale then)
+    if (__any(scale != 1.0f)) {
+#pragma unroll
+      for (int dt = 0; dt < D / 16; ++dt) acc[dt] *= scale;
+    }
+    const uint32_t va = lds0 + (uint32_t)(b * L::STAGE) + v_lane;
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+      float pv[8];
+#pragma unroll
+      for (int j = 0; j < 8; ++j) pv[j] = sc[2 * c + (j >> 2)][j & 3];
+      bf16x8_t bhi, blo;
+      split_bf16x8(pv, bhi, blo);
+#pragma unroll
+      for (int dt = 0; dt < D / 16; ++dt) {
+        const uint32_t at = (va ^ (uint32_t)(dt * 32)) + (uint32_t)(32 * c * D * 2);
+        const uint2 lo = read_tr16(at), hi = read_tr16(at + 16 * D * 2);
+        const bf16x8_t av = __builtin_bit_cast(bf16x8_t, make_uint4(lo.x, lo.y, hi.x, hi.y));
+        acc[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, bhi, acc[dt], 0, 0, 0);
+        acc[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, blo, acc[dt], 0, 0, 0);
+      }
+    }
+    if (wave == 0 && ck + 2 < nch) commit(nslot == 2 ? 0 : nslot + 1);
+    slot = nslot;
+  }
+
+  float l = lrun;
+  l += __shfl_xor(l, 16);
+  l += __shfl_xor(l, 32);
+  const float inv = 1.0f / l;
+  if (p < q1) {
+    TO* orow = O + (s * n + p) * D;
+#pragma unroll
+    for (int dt = 0; dt < D / 16; ++dt)
+      store4<TO>(orow + dt * 16 + 4 * g, acc[dt][0] * inv, acc[dt][1] * inv, acc[dt][2] * inv,
+                 acc[dt][3] * inv);
+  }
+}
+
 template <typename T, int D, typename TO>
 hipError_t launch_prefill_t(const void* Q, const void* K, const void* V, int64_t S, int64_t n,
                             const PrefillTile* tiles, int64_t ntiles, const PrefillSeg* segs,
                             const int32_t* c0, const float* w0, const uint8_t* kept, void* O,
                             hipStream_t st) {
   dim3 grid((unsigned)ntiles, (unsigned)S), block(64 * PF_WAVES);
-  hipLaunchKernelGGL((prefill_attn_kernel<T, D, TO>), grid, block, 0, st, (const T*)Q,
-                     (const T*)K, (const T*)V, n, tiles, segs, c0, w0, kept, (TO*)O);
+  if constexpr (Elem<T>::bytes == 2) {
+    auto kern = prefill_attn_bf16_kernel<D, TO>;
+    const size_t lds = PfLds<D>::bytes;
+    if (lds > 48 * 1024) {  // beside the kernel's 12 KiB of static LDS
+      hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
+                                         hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+      if (e != hipSuccess) return e;
+    }
+    hipLaunchKernelGGL(kern, grid, block, lds, st, (const bf16_t*)Q, (const bf16_t*)K,
+                       (const bf16_t*)V, n, tiles, segs, c0, w0, kept, (TO*)O);
+  } else {
+    hipLaunchKernelGGL((prefill_attn_kernel<T, D, TO>), grid, block, 0, st, (const T*)Q,
+                       (const T*)K, (const T*)V, n, tiles, segs, c0, w0, kept, (TO*)O);
+  }
   return hipGetLastError();
 }
 

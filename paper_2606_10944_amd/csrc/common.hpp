@@ -164,6 +164,29 @@ __device__ __forceinline__ floatx4_t mma_aug<float>(const uint4& a, const uint4&
   return __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a.x), __uint_as_float(b.x), acc, 0, 0, 0);
 }
 
+// 64 lanes x 16 bytes from global memory straight into LDS: lane l's 16 bytes
+// at g go to LDS byte lds + 16 l (lds uniform over the wave).  Counted in
+// vmcnt, which the caller waits on: the compiler does not see the copy.  (m0
+// holds the LDS address; nothing else in the kernels that call this uses it.)
+__device__ __forceinline__ void copy16_to_lds(const void* g, uint32_t lds) {
+  asm volatile(
+      "s_mov_b32 m0, %0\n\t"
+      "s_nop 0\n\t"
+      "global_load_lds_dwordx4 %1, off"
+      :
+      : "s"(lds), "v"(g)
+      : "memory");
+}
+__device__ __forceinline__ uint32_t lds_offset(const void* p) {
+  return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void*)p;
+}
+// s_waitcnt vmcnt(N), the other counters untouched.
+template <int N>
+__device__ __forceinline__ void wait_vmcnt() {
+  static_assert(N >= 0 && N < 64, "vmcnt has six bits");
+  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+}
+
 // Load this lane's quarter of row `row` (d columns of T) or zeros if !valid.
 template <typename T, int D>
 __device__ __forceinline__ void load_frag(const T* base, int64_t row, int g, bool valid, uint4* out) {

@@ -572,29 +572,6 @@ __device__ __forceinline__ double block_threshold(float lbt, float h2, float u, 
   return thr;
 }
 
-// 64 lanes x 16 bytes from global memory straight into LDS: lane l's 16 bytes
-// at g go to LDS byte lds + 16 l (lds uniform over the wave).  Counted in
-// vmcnt, which the caller waits on: the compiler does not see the copy.  (m0
-// holds the LDS address; nothing else in these kernels uses it.)
-__device__ __forceinline__ void copy16_to_lds(const void* g, uint32_t lds) {
-  asm volatile(
-      "s_mov_b32 m0, %0\n\t"
-      "s_nop 0\n\t"
-      "global_load_lds_dwordx4 %1, off"
-      :
-      : "s"(lds), "v"(g)
-      : "memory");
-}
-__device__ __forceinline__ uint32_t lds_offset(const void* p) {
-  return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void*)p;
-}
-// s_waitcnt vmcnt(N), the other counters untouched.
-template <int N>
-__device__ __forceinline__ void wait_vmcnt() {
-  static_assert(N >= 0 && N < 64, "vmcnt has six bits");
-  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
-}
-
 // Row of a half-block's (or column tile's) 32 rows that lane m16 of 16-row
 // tile rt holds.  MFMA outputs put rows 4g..4g+3 of a tile in lane group g;
 // with this order the group holds eight consecutive rows over both tiles,
