@@ -252,7 +252,19 @@ __device__ __forceinline__ uint32_t pack_hi(uint32_t x, uint32_t y) { return (x 
 // Target of the output stores of query rows past a workgroup's range (never read).
 __device__ __align__(16) float g_attn_sink[256];
 
-template <int D, int NKT, int QTR, int WR, typename TO, bool W>
+//   The keys are taken in H passes of NKT / H tiles.  One pass (up to 128
+// keys) needs no running maximum and is bound by HBM.  Above 128 keys the
+// coreset takes over 100 KB of LDS, one workgroup per CU, and a wave's reads of
+// it (512 bytes per key, K and V, for every query tile) keep the CU's LDS as
+// busy as the matrix cores: there a wave takes two query tiles (QTR = 2), each
+// fragment serving both, which only fits the registers with the scores of half
+// of the keys at a time (H = 2, online softmax).  256 keys, d = 128, 32 x 65536
+// queries, bf16 output: 521 us with one tile, one pass and 512 workgroups, 463 us
+// so, 440 us with the biases and masks as the score MFMAs' initial value
+// instead of two vector instructions per score; 192 weighted keys, 64 x 16384
+// queries: 203 -> 180 us.  What bounds it now is the vector ALU (softmax and
+// the split of P, 10 instructions per score) beside the matrix cores.
+template <int D, int NKT, int QTR, int WR, int H, typename TO, bool W>
 __global__ __launch_bounds__(64 * WR) void coreset_attn_res_kernel(
     const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, const bf16_t* __restrict__ V,
     const int32_t* __restrict__ idx, const float* __restrict__ logw, int64_t n, int64_t n_q,
@@ -268,10 +280,11 @@ __global__ __launch_bounds__(64 * WR) void coreset_attn_res_kernel(
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int m16 = lane & 15, g = lane >> 4;
   const int64_t s = blockIdx.y;
-  if (W) {
+  // what a key's raw score starts from: its bias, or -inf past n_out
+  {
     const float sqrt_d = (float)sqrt((double)D);
     for (int k = threadIdx.x; k < NK; k += 64 * WR)
-      sB[k] = k < n_out ? logw[s * (int64_t)n_out + k] * sqrt_d : -INFINITY;
+      sB[k] = k < n_out ? (W ? logw[s * (int64_t)n_out + k] * sqrt_d : 0.0f) : -INFINITY;
   }
   const bf16_t* Ks = K + s * n * D;
   const bf16_t* Vs = V + s * n * D;
@@ -345,95 +358,118 @@ __global__ __launch_bounds__(64 * WR) void coreset_attn_res_kernel(
 #pragma unroll
     for (int v = 0; v < NV; ++v)
       asm volatile("" : "+v"(Bq[qt][v].x), "+v"(Bq[qt][v].y), "+v"(Bq[qt][v].z), "+v"(Bq[qt][v].w));
+  constexpr int KT = NKT / H;  // key tiles per pass
+  // keys that every n_out of the tier has (tiers of 32 keys up to 128, then 64)
+  constexpr int FULL = 16 * NKT <= 128 ? 16 * NKT - 32 : 16 * NKT - 64;
+  static_assert(NKT % H == 0 && KT % 2 == 0, "whole pairs of key tiles per pass");
   for (int64_t q0 = q_begin; q0 < q_end; q0 += QSTEP) {
     const int64_t qw = q0 + wave * 16 * QTR;
+    // the next queries, requested early (one pass) or once this step's are no
+    // longer needed (more passes, where registers are short)
     uint4 Nq[QTR][NV];
-#pragma unroll
-    for (int qt = 0; qt < QTR; ++qt) {
-      const int64_t q = qw + QSTEP + qt * 16 + m16;
-      load_frag<bf16_t, D>(Qs, min(q, n_q - 1), g, true, Nq[qt]);
-    }
-    // scores S^T[key][query]; the next key tile's fragment is read while the
-    // current one multiplies, and no further (the scheduling barrier keeps
-    // the compiler from hoisting every tile's LDS reads at once)
-    floatx4_t sc[QTR][NKT];
-    uint4 a[2][NV];
-#pragma unroll
-    for (int v = 0; v < NV; ++v)
-      a[0][v] = reinterpret_cast<const uint4*>(sK + m16 * L::k_stride)[4 * v + g];
-#pragma unroll
-    for (int kt = 0; kt < NKT; ++kt) {
-      if (kt + 1 < NKT) {
-        const uint4* pk = reinterpret_cast<const uint4*>(sK + ((kt + 1) * 16 + m16) * L::k_stride);
-#pragma unroll
-        for (int v = 0; v < NV; ++v) a[(kt + 1) & 1][v] = pk[4 * v + g];
-      }
+    auto next_queries = [&]() {
 #pragma unroll
       for (int qt = 0; qt < QTR; ++qt) {
-        floatx4_t z = {0.f, 0.f, 0.f, 0.f};
-        sc[qt][kt] = mma_rows<bf16_t, D>(a[kt & 1], Bq[qt], z);
+        const int64_t q = qw + QSTEP + qt * 16 + m16;
+        load_frag<bf16_t, D>(Qs, min(q, n_q - 1), g, true, Nq[qt]);
       }
-      __builtin_amdgcn_sched_barrier(0);
-    }
-    float inv_l[QTR];
+    };
+    if constexpr (H == 1) next_queries();
+    float mrun[QTR], l[QTR], inv_l[QTR];
     floatx4_t acc[QTR][D / 16];
 #pragma unroll
     for (int qt = 0; qt < QTR; ++qt) {
-      float mx = -INFINITY;
-#pragma unroll
-      for (int kt = 0; kt < NKT; ++kt) {
-        if (W) {
-          const float4 b = *reinterpret_cast<const float4*>(sB + kt * 16 + 4 * g);
-          sc[qt][kt][0] += b.x; sc[qt][kt][1] += b.y; sc[qt][kt][2] += b.z; sc[qt][kt][3] += b.w;
-        }
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int key = kt * 16 + 4 * g + i;
-          if (!W && key >= n_out) sc[qt][kt][i] = -INFINITY;
-          mx = fmaxf(mx, sc[qt][kt][i]);
-        }
-      }
-      mx = fmaxf(mx, __shfl_xor(mx, 16));
-      mx = fmaxf(mx, __shfl_xor(mx, 32));
-      float l = 0.f;
-#pragma unroll
-      for (int kt = 0; kt < NKT; ++kt)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const float pv = __builtin_amdgcn_exp2f((sc[qt][kt][i] - mx) * c2);
-          sc[qt][kt][i] = pv;
-          l += pv;
-        }
-      l += __shfl_xor(l, 16);
-      l += __shfl_xor(l, 32);
-      inv_l[qt] = 1.0f / l;
+      mrun[qt] = -INFINITY;
+      l[qt] = 0.f;
 #pragma unroll
       for (int dt = 0; dt < D / 16; ++dt) acc[qt][dt] = (floatx4_t){0.f, 0.f, 0.f, 0.f};
     }
-    // O^T += V^T P^T, 32 keys per MFMA; P = hi + lo in bf16
 #pragma unroll
-    for (int c = 0; c < NKT / 2; ++c) {
-      bf16x8_t bhi[QTR], blo[QTR];
+    for (int h = 0; h < H; ++h) {
+      const int k0 = h * KT;  // the pass's first key tile
+      // scores S^T[key][query]; the next key tile's fragment is read while the
+      // current one multiplies, and no further (the scheduling barrier keeps
+      // the compiler from hoisting every tile's LDS reads at once)
+      floatx4_t sc[QTR][KT];
+      uint4 a[2][NV];
+#pragma unroll
+      for (int v = 0; v < NV; ++v)
+        a[0][v] = reinterpret_cast<const uint4*>(sK + (k0 * 16 + m16) * L::k_stride)[4 * v + g];
+#pragma unroll
+      for (int kt = 0; kt < KT; ++kt) {
+        if (kt + 1 < KT) {
+          const uint4* pk = reinterpret_cast<const uint4*>(sK + ((k0 + kt + 1) * 16 + m16) * L::k_stride);
+#pragma unroll
+          for (int v = 0; v < NV; ++v) a[(kt + 1) & 1][v] = pk[4 * v + g];
+        }
+        // unweighted, the tiles every size of the tier fills start from zero
+        floatx4_t z = {0.f, 0.f, 0.f, 0.f};
+        if (W || 16 * (k0 + kt + 1) > FULL) z = *reinterpret_cast<const floatx4_t*>(sB + (k0 + kt) * 16 + 4 * g);
+#pragma unroll
+        for (int qt = 0; qt < QTR; ++qt) sc[qt][kt] = mma_rows<bf16_t, D>(a[kt & 1], Bq[qt], z);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      if constexpr (H > 1)
+        if (h == H - 1) next_queries();
 #pragma unroll
       for (int qt = 0; qt < QTR; ++qt) {
-        float pv[8];
+        float mx = mrun[qt];
 #pragma unroll
-        for (int e = 0; e < 8; ++e) pv[e] = sc[qt][2 * c + (e >> 2)][e & 3];
-        split_bf16x8(pv, bhi[qt], blo[qt]);
-      }
+        for (int kt = 0; kt < KT; ++kt)
 #pragma unroll
-      for (int dt = 0; dt < D / 16; ++dt) {
-        const unsigned char* row = sV + (dt * 16 + m16) * L::v_stride;
-        const uint2 lo = *reinterpret_cast<const uint2*>(row + (32 * c + 4 * g) * 2);
-        const uint2 hi = *reinterpret_cast<const uint2*>(row + (32 * c + 16 + 4 * g) * 2);
-        const bf16x8_t av = __builtin_bit_cast(bf16x8_t, make_uint4(lo.x, lo.y, hi.x, hi.y));
+          for (int i = 0; i < 4; ++i) mx = fmaxf(mx, sc[qt][kt][i]);
+        mx = fmaxf(mx, __shfl_xor(mx, 16));
+        mx = fmaxf(mx, __shfl_xor(mx, 32));
+        if (h > 0) {
+          // (no key of finite weight so far: nothing to rescale)
+          const float scale = W && mrun[qt] == -INFINITY
+                                  ? 0.f : __builtin_amdgcn_exp2f((mrun[qt] - mx) * c2);
+          l[qt] *= scale;
 #pragma unroll
-        for (int qt = 0; qt < QTR; ++qt) {
-          acc[qt][dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, bhi[qt], acc[qt][dt], 0, 0, 0);
-          acc[qt][dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, blo[qt], acc[qt][dt], 0, 0, 0);
+          for (int dt = 0; dt < D / 16; ++dt) acc[qt][dt] *= scale;
+        }
+        mrun[qt] = mx;
+        // a pass whose keys are all dropped leaves zeros, not NaN
+        const float mref = W && H > 1 && mx == -INFINITY ? 0.f : mx;
+#pragma unroll
+        for (int kt = 0; kt < KT; ++kt)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const float pv = __builtin_amdgcn_exp2f((sc[qt][kt][i] - mref) * c2);
+            sc[qt][kt][i] = pv;
+            l[qt] += pv;
+          }
+        if (h == H - 1) {
+          l[qt] += __shfl_xor(l[qt], 16);
+          l[qt] += __shfl_xor(l[qt], 32);
+          inv_l[qt] = 1.0f / l[qt];
         }
       }
-      __builtin_amdgcn_sched_barrier(0);
+      // O^T += V^T P^T, 32 keys per MFMA; P = hi + lo in bf16
+#pragma unroll
+      for (int c = 0; c < KT / 2; ++c) {
+        bf16x8_t bhi[QTR], blo[QTR];
+#pragma unroll
+        for (int qt = 0; qt < QTR; ++qt) {
+          float pv[8];
+#pragma unroll
+          for (int e = 0; e < 8; ++e) pv[e] = sc[qt][2 * c + (e >> 2)][e & 3];
+          split_bf16x8(pv, bhi[qt], blo[qt]);
+        }
+#pragma unroll
+        for (int dt = 0; dt < D / 16; ++dt) {
+          const unsigned char* row = sV + (dt * 16 + m16) * L::v_stride + k0 * 32;
+          const uint2 lo = *reinterpret_cast<const uint2*>(row + (32 * c + 4 * g) * 2);
+          const uint2 hi = *reinterpret_cast<const uint2*>(row + (32 * c + 16 + 4 * g) * 2);
+          const bf16x8_t av = __builtin_bit_cast(bf16x8_t, make_uint4(lo.x, lo.y, hi.x, hi.y));
+#pragma unroll
+          for (int qt = 0; qt < QTR; ++qt) {
+            acc[qt][dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, bhi[qt], acc[qt][dt], 0, 0, 0);
+            acc[qt][dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, blo[qt], acc[qt][dt], 0, 0, 0);
+          }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
     }
 #pragma unroll
     for (int qt = 0; qt < QTR; ++qt) {
@@ -513,12 +549,30 @@ __global__ __launch_bounds__(64 * WR) void coreset_attn_res_kernel(
   }
 }
 
-template <int D, int NKT, int QTR, int WR, typename TO, bool W>
+// Waves per workgroup of the resident kernel; above 128 keys also 16-query
+// tiles per wave per step, passes over the keys and workgroups in all
+#ifndef ATTN_RES_WAVES
+#define ATTN_RES_WAVES 4
+#endif
+#ifndef ATTN_RES_WAVES_BIG
+#define ATTN_RES_WAVES_BIG 8
+#endif
+#ifndef ATTN_RES_QTR_BIG
+#define ATTN_RES_QTR_BIG 2
+#endif
+#ifndef ATTN_RES_H_BIG
+#define ATTN_RES_H_BIG 2
+#endif
+#ifndef ATTN_RES_WGS_BIG
+#define ATTN_RES_WGS_BIG 256
+#endif
+
+template <int D, int NKT, int QTR, int WR, int H, typename TO, bool W>
 hipError_t launch_attn_res_w(const void* Q, const void* K, const void* V, const int32_t* idx,
                              const float* logw, int64_t S, int64_t n, int64_t n_q,
                              int64_t n_out, void* O, hipStream_t st) {
   using L = ResLds<D, NKT>;
-  auto kern = coreset_attn_res_kernel<D, NKT, QTR, WR, TO, W>;
+  auto kern = coreset_attn_res_kernel<D, NKT, QTR, WR, H, TO, W>;
   const size_t lds = L::bytes;
   if (lds > 64 * 1024) {
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
@@ -526,8 +580,10 @@ hipError_t launch_attn_res_w(const void* Q, const void* K, const void* V, const 
     if (e != hipSuccess) return e;
   }
   constexpr int64_t QSTEP = 16 * QTR * WR;
-  // about two workgroups per CU in total, whole steps of queries per workgroup
-  int64_t per_slice = (512 + S - 1) / S;
+  // about as many workgroups as the CUs hold (two each, or one where the
+  // coreset takes most of the LDS), whole steps of queries per workgroup
+  const int64_t want = lds > 80 * 1024 ? ATTN_RES_WGS_BIG : 512;
+  int64_t per_slice = (want + S - 1) / S;
   const int64_t steps = (n_q + QSTEP - 1) / QSTEP;
   if (per_slice > steps) per_slice = steps;
   if (per_slice < 1) per_slice = 1;
@@ -539,41 +595,28 @@ hipError_t launch_attn_res_w(const void* Q, const void* K, const void* V, const 
   return hipGetLastError();
 }
 
-template <int D, int NKT, int QTR, int WR, typename TO>
+template <int D, int NKT, int QTR, int WR, int H, typename TO>
 hipError_t launch_attn_res(const void* Q, const void* K, const void* V, const int32_t* idx,
                            const float* logw, int64_t S, int64_t n, int64_t n_q, int64_t n_out,
                            void* O, hipStream_t st) {
   if (logw)
-    return launch_attn_res_w<D, NKT, QTR, WR, TO, true>(Q, K, V, idx, logw, S, n, n_q, n_out, O, st);
-  return launch_attn_res_w<D, NKT, QTR, WR, TO, false>(Q, K, V, idx, logw, S, n, n_q, n_out, O, st);
+    return launch_attn_res_w<D, NKT, QTR, WR, H, TO, true>(Q, K, V, idx, logw, S, n, n_q, n_out, O, st);
+  return launch_attn_res_w<D, NKT, QTR, WR, H, TO, false>(Q, K, V, idx, logw, S, n, n_q, n_out, O, st);
 }
-
-// 16-query tiles per wave per step and waves per workgroup of the resident kernel
-#ifndef ATTN_RES_QTR
-#define ATTN_RES_QTR 1
-#endif
-#ifndef ATTN_RES_WAVES
-#define ATTN_RES_WAVES 4
-#endif
-// Coresets of 192 or 256 keys take over 100 KB of LDS, one workgroup per CU:
-// eight waves then hide more latency than four (256 keys, d = 128: 353 -> 280 us
-// on the long workload's queries).
-#ifndef ATTN_RES_WAVES_BIG
-#define ATTN_RES_WAVES_BIG 8
-#endif
 
 template <int D, typename TO>
 hipError_t launch_attn_res_d(int64_t n_out, const void* Q, const void* K, const void* V,
                              const int32_t* idx, const float* logw, int64_t S, int64_t n,
                              int64_t n_q, void* O, hipStream_t st, bool* used) {
   *used = true;
-  if (n_out <= 32) return launch_attn_res<D, 2, ATTN_RES_QTR, ATTN_RES_WAVES, TO>(Q, K, V, idx, logw, S, n, n_q, n_out, O, st);
-  if (n_out <= 64) return launch_attn_res<D, 4, ATTN_RES_QTR, ATTN_RES_WAVES, TO>(Q, K, V, idx, logw, S, n, n_q, n_out, O, st);
-  if (n_out <= 96) return launch_attn_res<D, 6, ATTN_RES_QTR, ATTN_RES_WAVES, TO>(Q, K, V, idx, logw, S, n, n_q, n_out, O, st);
-  if (n_out <= 128) return launch_attn_res<D, 8, ATTN_RES_QTR, ATTN_RES_WAVES, TO>(Q, K, V, idx, logw, S, n, n_q, n_out, O, st);
+  if (n_out <= 32) return launch_attn_res<D, 2, 1, ATTN_RES_WAVES, 1, TO>(Q, K, V, idx, logw, S, n, n_q, n_out, O, st);
+  if (n_out <= 64) return launch_attn_res<D, 4, 1, ATTN_RES_WAVES, 1, TO>(Q, K, V, idx, logw, S, n, n_q, n_out, O, st);
+  if (n_out <= 96) return launch_attn_res<D, 6, 1, ATTN_RES_WAVES, 1, TO>(Q, K, V, idx, logw, S, n, n_q, n_out, O, st);
+  if (n_out <= 128) return launch_attn_res<D, 8, 1, ATTN_RES_WAVES, 1, TO>(Q, K, V, idx, logw, S, n, n_q, n_out, O, st);
   // (192 = n_out 128 plus 32 sinks and a 32-row window)
-  if (n_out <= 192 && D <= 128) return launch_attn_res<D, 12, ATTN_RES_QTR, ATTN_RES_WAVES_BIG, TO>(Q, K, V, idx, logw, S, n, n_q, n_out, O, st);
-  if (n_out <= 256 && D <= 128) return launch_attn_res<D, 16, ATTN_RES_QTR, ATTN_RES_WAVES_BIG, TO>(Q, K, V, idx, logw, S, n, n_q, n_out, O, st);
+  constexpr int Q2 = D == 128 ? ATTN_RES_QTR_BIG : 1, H2 = D == 128 ? ATTN_RES_H_BIG : 1;
+  if (n_out <= 192) return launch_attn_res<D, 12, Q2, ATTN_RES_WAVES_BIG, H2, TO>(Q, K, V, idx, logw, S, n, n_q, n_out, O, st);
+  if (n_out <= 256) return launch_attn_res<D, 16, Q2, ATTN_RES_WAVES_BIG, H2, TO>(Q, K, V, idx, logw, S, n, n_q, n_out, O, st);
   *used = false;
   return hipSuccess;
 }
@@ -1057,12 +1100,11 @@ __global__ __launch_bounds__(64 * PF_WAVES) __attribute__((amdgpu_waves_per_eu(4
     if (wave == 0 && ck + 2 < nch) gather(ck + 2);
 
     // the lane's 16 keys: bias where the point sees the key, else -inf
-    float sc[4][4];
+    floatx4_t sc[4];
     const int test = s_test[slot];
 #pragma unroll
     for (int kt = 0; kt < 4; ++kt) {
-      const float4 b4 = *reinterpret_cast<const float4*>(&s_bias[slot][kt * 16 + 4 * g]);
-      sc[kt][0] = b4.x; sc[kt][1] = b4.y; sc[kt][2] = b4.z; sc[kt][3] = b4.w;
+      sc[kt] = *reinterpret_cast<const floatx4_t*>(&s_bias[slot][kt * 16 + 4 * g]);
     }
     if (test < 2) {
       uint32_t wv[4][4];
