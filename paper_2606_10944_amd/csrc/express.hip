@@ -181,26 +181,7 @@ __global__ void express_keys_kernel(ExpressSegs segs, int64_t m, int64_t out_str
 #endif
 constexpr int kDecWaves = DEC_WAVES;
 constexpr int kDecUnroll = 8;
-
-// Row and log-weight of key j of slice s (segments as in express_keys_kernel).
-// (k, off) is a cursor: segment k starts at key off; a lane's keys increase,
-// so the cursor only moves forward.
-__device__ __forceinline__ int64_t seg_key(const ExpressSegs& segs, int64_t s, int64_t j, int& k,
-                                           int64_t& off, float* lw) {
-  while (k + 1 < segs.n && j >= off + segs.seg[k].len) off += segs.seg[k++].len;
-  const ExpressSeg& g = segs.seg[k];
-  *lw = g.logw;
-  return g.src ? (int64_t)g.src[s * g.stride + (j - off)] : g.start + (j - off);
-}
-
-// seg_key over a segment table staged in LDS.
-__device__ __forceinline__ int64_t seg_key_lds(const ExpressSeg* seg, int n, int64_t s, int64_t j,
-                                               int& k, int64_t& off, float* lw) {
-  while (k + 1 < n && j >= off + seg[k].len) off += seg[k++].len;
-  const ExpressSeg& g = seg[k];
-  *lw = g.logw;
-  return g.src ? (int64_t)g.src[s * g.stride + (j - off)] : g.start + (j - off);
-}
+constexpr int64_t kDecMaxWorkgroups = 256;  // one per CU
 
 // The EPW elements of a 16-byte word as floats.
 template <typename T>
@@ -228,6 +209,48 @@ __device__ __forceinline__ void store_out<bf16_t>(bf16_t* p, float v) {
   *reinterpret_cast<__bf16*>(p) = (__bf16)v;
 }
 
+// Sum over the LPK lanes of a key row (LPK consecutive lanes, aligned); every
+// lane gets it.  Within 16 lanes by DPP adds (no LDS): rotations within the
+// row of 16, or, for rows of 4 or 8 lanes, quad permutes and the half mirror.
+template <int CTRL>
+__device__ __forceinline__ float dpp_add(float x) {
+  return x + __uint_as_float((uint32_t)__builtin_amdgcn_mov_dpp((int)__float_as_uint(x), CTRL, 0xF, 0xF, false));
+}
+template <int LPK>
+__device__ __forceinline__ float row_sum(float x) {
+  static_assert(LPK == 4 || LPK == 8 || LPK == 16 || LPK == 32, "key rows of 64..512 bytes");
+  if constexpr (LPK == 32) x += __shfl_xor(x, 16);
+  if constexpr (LPK >= 16) {
+    x = dpp_add<0x128>(x);
+    x = dpp_add<0x124>(x);
+    x = dpp_add<0x122>(x);
+    x = dpp_add<0x121>(x);
+  } else {
+    x = dpp_add<0xB1>(x);
+    x = dpp_add<0x4E>(x);
+    if constexpr (LPK == 8) x = dpp_add<0x141>(x);
+  }
+  return x;
+}
+
+// The values of the lower and the upper of a pair of lane groups OFF apart
+// (OFF = 16, 32: one swap instruction; else LDS), the same pair in both.
+template <int OFF>
+__device__ __forceinline__ void both(float x, float& lower, float& upper) {
+  if constexpr (OFF == 32 || OFF == 16) {
+    const uint32_t u = __float_as_uint(x);
+    const auto r = OFF == 32 ? __builtin_amdgcn_permlane32_swap(u, u, false, false)
+                             : __builtin_amdgcn_permlane16_swap(u, u, false, false);
+    lower = __uint_as_float(r[0]);
+    upper = __uint_as_float(r[1]);
+  } else {
+    const float y = __shfl_xor(x, OFF);
+    const bool up = (threadIdx.x & OFF) != 0;
+    lower = up ? y : x;
+    upper = up ? x : y;
+  }
+}
+
 // Merge of two online-softmax states (m, l, acc) in the log2 domain; an empty
 // state has m = -inf.
 template <int EPW>
@@ -241,71 +264,154 @@ __device__ __forceinline__ void softmax_merge(float& m, float& l, float* acc, fl
   for (int e = 0; e < EPW; ++e) acc[e] = acc[e] * a + acc2[e] * b;
   m = M;
 }
+template <int OFF, int EPW>
+__device__ __forceinline__ void merge_groups(float& m, float& l, float* acc) {
+  float m0, m1, l0, l1, a0[EPW], a1[EPW];
+  both<OFF>(m, m0, m1);
+  both<OFF>(l, l0, l1);
+#pragma unroll
+  for (int e = 0; e < EPW; ++e) both<OFF>(acc[e], a0[e], a1[e]);
+  softmax_merge<EPW>(m0, l0, a0, m1, l1, a1);
+  m = m0;
+  l = l0;
+#pragma unroll
+  for (int e = 0; e < EPW; ++e) acc[e] = a0[e];
+}
 
-template <typename T, int D, typename TO>
+// The segments as the kernel reads them: keys [end of the previous segment,
+// end) are the rows src[s * stride + at + j] (src null: at + j), j the key's
+// position in the whole list.  Caches of at most kDecFewSegs segments (every
+// mbar up to 9) launch with an argument of that size: a third of the bytes to
+// write and to read per step.
+struct DecSeg {
+  const int32_t* src;
+  int64_t stride;
+  int32_t at;
+  int32_t end;
+  float logw;
+};
+constexpr int kDecFewSegs = 12;
+template <int NS>
+struct DecSegs {
+  DecSeg seg[NS];
+  int n;
+};
+
+// Dot product of a 16-byte word of q (as loaded, and as floats) with one of a
+// key: bf16 pairs by the dot instruction (exact products, float32 sums).
+template <typename T>
+__device__ __forceinline__ float word_dot(const u32x4& qw, const float* q, const u32x4& k);
+template <>
+__device__ __forceinline__ float word_dot<float>(const u32x4&, const float* q, const u32x4& k) {
+  float d = 0.f;
+#pragma unroll
+  for (int c = 0; c < 4; ++c) d = __builtin_fmaf(q[c], __uint_as_float(k[c]), d);
+  return d;
+}
+template <>
+__device__ __forceinline__ float word_dot<bf16_t>(const u32x4& qw, const float*, const u32x4& k) {
+  float d = 0.f;
+#pragma unroll
+  for (int c = 0; c < 4; ++c) {
+    const uint32_t a = qw[c], b = k[c];  // (a bit cast of a vector's element itself reads element 0)
+    d = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, a),
+                                        __builtin_bit_cast(bf16x2_t, b), d, false);
+  }
+  return d;
+}
+
+// C workgroups share a slice's run of keys (blockIdx.z = c): each forms every
+// key's weight and adds its D / C columns of V, so nothing is merged between
+// them.  What bounds a step is one CU's vector ALU and the chain of latencies
+// (kernel argument, query, list, rows, the merge in LDS): with 32 slices, 410
+// keys of 128 bf16 and one workgroup per slice, the arithmetic after the rows
+// arrived took 2.3 us of 7.6 (most of it unpacking and adding V) and the
+// look-ups 2 us.
+template <typename T, int D, typename TO, int C, int NS>
 __global__ __launch_bounds__(64 * kDecWaves) void decode_attn_kernel(
-    const T* __restrict__ Q, const T* __restrict__ K, const T* __restrict__ V, ExpressSegs segs,
-    int64_t ld, int64_t m, int split, float* __restrict__ part, TO* __restrict__ O, int32_t* app,
-    int64_t app_stride, int32_t app_val) {
+    const T* __restrict__ Q, const T* __restrict__ K, const T* __restrict__ V, int64_t ld,
+    int32_t m, int split, float* __restrict__ part, TO* __restrict__ O, int32_t* app,
+    int64_t app_stride, int32_t app_val, DecSegs<NS> segs) {
   constexpr int LPK = D * Elem<T>::bytes / 16;  // lanes per key row (16 bytes each)
   constexpr int KPI = 64 / LPK;                 // keys per load instruction
   constexpr int EPW = 16 / Elem<T>::bytes;      // elements per 16-byte word
+  constexpr int EPV = EPW / C;                  // V elements per lane (of this workgroup's columns)
+  constexpr int VB = 16 / C;                    // their bytes
+  constexpr int DV = D / C;
   static_assert(LPK >= 1 && LPK <= 64 && 64 % LPK == 0, "row of 16..1024 bytes");
+  static_assert(VB >= 4, "a V word of 4, 8 or 16 bytes");
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int sub = lane / LPK, pos = lane % LPK;
   const int64_t s = blockIdx.y;
-  const int64_t k0 = m * blockIdx.x / split, k1 = m * (blockIdx.x + 1) / split;
+  const int cz = blockIdx.z;
+  // the segment table: lane k holds segment k (one parallel read of the kernel
+  // argument); no LDS, no barrier
+  const int nseg = segs.n;
+  DecSeg seg{};
+  if (lane < NS) seg = segs.seg[lane];
+  const u32x4 qw = reinterpret_cast<const u32x4*>(Q + s * D)[pos];
+  const int32_t k0 = (int32_t)((int64_t)m * blockIdx.x / split);
+  const int32_t k1 = (int32_t)((int64_t)m * (blockIdx.x + 1) / split);
   // this wave's contiguous run of keys
-  const int64_t per = (k1 - k0 + kDecWaves - 1) / kDecWaves;
-  const int64_t w0 = min(k1, k0 + per * wave), w1 = min(k1, w0 + per);
+  const int32_t per = (k1 - k0 + kDecWaves - 1) / kDecWaves;
+  const int32_t w0 = min(k1, k0 + per * wave), w1 = min(k1, w0 + per);
   const float c2 = (float)(1.4426950408889634 / sqrt((double)D));
   const float l2e = 1.4426950408889634f;
-  float q[EPW];
-  word_to_floats<T>(reinterpret_cast<const u32x4*>(Q + s * D)[pos], q);
   const u32x4* Ks = reinterpret_cast<const u32x4*>(K + s * ld * D);
-  const u32x4* Vs = reinterpret_cast<const u32x4*>(V + s * ld * D);
-  // the segment table in LDS (the kernel argument is read through memory:
-  // scanning it there would put a memory latency on every segment step)
-  __shared__ ExpressSeg s_seg[kExpressMaxSegs];
-  __shared__ int s_nseg;
-  if (threadIdx.x < segs.n) s_seg[threadIdx.x] = segs.seg[threadIdx.x];
-  if (threadIdx.x == 0) s_nseg = segs.n;
-  __syncthreads();
-  float mrun = -INFINITY, lrun = 0.f, acc[EPW];
+  const unsigned char* Vs = reinterpret_cast<const unsigned char*>(V + s * ld * D) + cz * DV * Elem<T>::bytes + pos * VB;
+  const uint64_t g_src = (uint64_t)(uintptr_t)(seg.src ? seg.src + s * seg.stride : nullptr);
+  float q[EPW];
+  word_to_floats<T>(qw, q);
+  float mrun = -INFINITY, lrun = 0.f, acc[EPV];
 #pragma unroll
-  for (int e = 0; e < EPW; ++e) acc[e] = 0.f;
-  int kseg = 0;
-  int64_t koff = 0;
-  for (int64_t j0 = w0; j0 < w1; j0 += KPI * kDecUnroll) {
-    u32x4 kw[kDecUnroll], vw[kDecUnroll];
-    float sc[kDecUnroll];
-    int64_t r[kDecUnroll];
-    // every row index of the batch first (the list reads are independent),
-    // then every row: two dependent memory latencies per batch, not two per key
+  for (int e = 0; e < EPV; ++e) acc[e] = 0.f;
+  constexpr int BK = KPI * kDecUnroll;  // keys per batch
+  constexpr int NL = (BK + 63) / 64;    // a lane looks up this many of them
+  for (int32_t j0 = w0; j0 < w1; j0 += BK) {
+    // Key j0 + 64 h + lane of the batch: its segment (the number of segments
+    // that end at or before it), row index and log-weight.  Every key is
+    // looked up by one lane and handed to the lanes that read its row, so the
+    // batch waits for one list read and then for its rows.
+    int32_t row[NL];
+    float lw[NL];
 #pragma unroll
-    for (int u = 0; u < kDecUnroll; ++u) {
-      const int64_t j = j0 + u * KPI + sub;
-      const bool ok = j < w1;
-      float lw = 0.f;
-      r[u] = ok ? seg_key_lds(s_seg, s_nseg, s, j, kseg, koff, &lw) : -1;
-      sc[u] = ok ? lw * l2e : -INFINITY;
+    for (int h = 0; h < NL; ++h) {
+      const int32_t j = min(j0 + 64 * h + lane, w1 - 1);
+      int k = 0;
+      for (int i = 0; i + 1 < nseg; ++i) k += j >= __builtin_amdgcn_readlane(seg.end, i) ? 1 : 0;
+      const uint64_t src = (uint64_t)(uint32_t)__shfl((int)(uint32_t)g_src, k) |
+                           (uint64_t)(uint32_t)__shfl((int)(uint32_t)(g_src >> 32), k) << 32;
+      row[h] = __shfl(seg.at, k) + j;
+      lw[h] = __shfl(seg.logw, k) * l2e;
+      if (src) row[h] = reinterpret_cast<const __attribute__((address_space(1))) int32_t*>(src)[row[h]];
     }
+    u32x4 kw[kDecUnroll];
+    uint32_t vw[kDecUnroll][VB / 4];
+    float sc[kDecUnroll];
 #pragma unroll
     for (int u = 0; u < kDecUnroll; ++u) {
-      const bool ok = r[u] >= 0;
-      kw[u] = ok ? Ks[r[u] * LPK + pos] : (u32x4){0u, 0u, 0u, 0u};
-      vw[u] = ok ? Vs[r[u] * LPK + pos] : (u32x4){0u, 0u, 0u, 0u};
+      const int k = u * KPI;  // key k + sub of the batch (past the run: its last key again, dropped)
+      const int64_t r = __shfl(row[k / 64], k % 64 + sub);
+      const float w = __shfl(lw[k / 64], k % 64 + sub);
+      sc[u] = j0 + k + sub < w1 ? w : -INFINITY;
+      kw[u] = Ks[r * LPK + pos];
+      const unsigned char* v = Vs + r * (D * Elem<T>::bytes);
+      if constexpr (VB == 16) {
+        const u32x4 x = *reinterpret_cast<const u32x4*>(v);
+#pragma unroll
+        for (int c = 0; c < 4; ++c) vw[u][c] = x[c];
+      } else if constexpr (VB == 8) {
+        const uint2 x = *reinterpret_cast<const uint2*>(v);
+        vw[u][0] = x.x;
+        vw[u][1] = x.y;
+      } else {
+        vw[u][0] = *reinterpret_cast<const uint32_t*>(v);
+      }
     }
     float mx = mrun;
 #pragma unroll
     for (int u = 0; u < kDecUnroll; ++u) {
-      float kf[EPW];
-      word_to_floats<T>(kw[u], kf);
-      float d = 0.f;
-#pragma unroll
-      for (int e = 0; e < EPW; ++e) d = __builtin_fmaf(q[e], kf[e], d);
-#pragma unroll
-      for (int off = LPK / 2; off >= 1; off >>= 1) d += __shfl_xor(d, off);
+      const float d = row_sum<LPK>(word_dot<T>(qw, q, kw[u]));
       sc[u] = sc[u] == -INFINITY ? -INFINITY : __builtin_fmaf(d, c2, sc[u]);
       mx = fmaxf(mx, sc[u]);
     }
@@ -313,42 +419,44 @@ __global__ __launch_bounds__(64 * kDecWaves) void decode_attn_kernel(
     const float scale = mrun == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mrun - mx);
     lrun *= scale;
 #pragma unroll
-    for (int e = 0; e < EPW; ++e) acc[e] *= scale;
+    for (int e = 0; e < EPV; ++e) acc[e] *= scale;
 #pragma unroll
     for (int u = 0; u < kDecUnroll; ++u) {
-      const float p = sc[u] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(sc[u] - mx);
-      float vf[EPW];
-      word_to_floats<T>(vw[u], vf);
+      const float p = __builtin_amdgcn_exp2f(sc[u] - mx);  // 0 for a dropped key
       lrun += p;
 #pragma unroll
-      for (int e = 0; e < EPW; ++e) acc[e] = __builtin_fmaf(p, vf[e], acc[e]);
+      for (int e = 0; e < VB / 4; ++e) {
+        const uint32_t x = sc[u] == -INFINITY ? 0u : vw[u][e];  // (an infinite entry of a dropped key)
+        if constexpr (Elem<T>::bytes == 4) {
+          acc[e] = __builtin_fmaf(p, __uint_as_float(x), acc[e]);
+        } else {
+          acc[2 * e] = __builtin_fmaf(p, __uint_as_float(x << 16), acc[2 * e]);
+          acc[2 * e + 1] = __builtin_fmaf(p, __uint_as_float(x & 0xffff0000u), acc[2 * e + 1]);
+        }
+      }
     }
     mrun = mx;
   }
   // the wave's KPI key groups merge into lanes 0..LPK-1
-#pragma unroll
-  for (int off = LPK; off < 64; off <<= 1) {
-    const float m2 = __shfl_xor(mrun, off), l2 = __shfl_xor(lrun, off);
-    float a2[EPW];
-#pragma unroll
-    for (int e = 0; e < EPW; ++e) a2[e] = __shfl_xor(acc[e], off);
-    softmax_merge<EPW>(mrun, lrun, acc, m2, l2, a2);
-  }
-  __shared__ float s_m[kDecWaves], s_l[kDecWaves], s_acc[kDecWaves][D];
+  if constexpr (LPK <= 4) merge_groups<4, EPV>(mrun, lrun, acc);
+  if constexpr (LPK <= 8) merge_groups<8, EPV>(mrun, lrun, acc);
+  if constexpr (LPK <= 16) merge_groups<16, EPV>(mrun, lrun, acc);
+  merge_groups<32, EPV>(mrun, lrun, acc);
+  __shared__ float s_m[kDecWaves], s_l[kDecWaves], s_acc[kDecWaves][DV];
   if (lane == 0) {
     s_m[wave] = mrun;
     s_l[wave] = lrun;
   }
   if (lane < LPK) {
 #pragma unroll
-    for (int e = 0; e < EPW; ++e) s_acc[wave][pos * EPW + e] = acc[e];
+    for (int e = 0; e < EPV; ++e) s_acc[wave][pos * EPV + e] = acc[e];
   }
   __syncthreads();
-  float M = -INFINITY;
-#pragma unroll
-  for (int w = 0; w < kDecWaves; ++w) M = fmaxf(M, s_m[w]);
   const int c = threadIdx.x;
-  if (c < D) {
+  if (c < DV) {
+    float M = -INFINITY;
+#pragma unroll
+    for (int w = 0; w < kDecWaves; ++w) M = fmaxf(M, s_m[w]);
     float a = 0.f, L = 0.f;
 #pragma unroll
     for (int w = 0; w < kDecWaves; ++w) {
@@ -357,17 +465,17 @@ __global__ __launch_bounds__(64 * kDecWaves) void decode_attn_kernel(
       L = __builtin_fmaf(s_l[w], f, L);
     }
     if (split == 1) {
-      store_out<TO>(O + s * D + c, a / L);
+      store_out<TO>(O + s * D + cz * DV + c, a / L);
     } else {
       float* out = part + (s * split + blockIdx.x) * (int64_t)(D + 2);
-      out[2 + c] = a;
-      if (c == 0) {
+      out[2 + cz * DV + c] = a;
+      if (c == 0 && cz == 0) {
         out[0] = M;
         out[1] = L;
       }
     }
   }
-  if (split == 1 && app && threadIdx.x == 0) app[s * app_stride] = app_val;
+  if (split == 1 && app && cz == 0 && threadIdx.x == 0) app[s * app_stride] = app_val;
 }
 
 // One workgroup per slice: the partials' maxima and sums are staged in LDS
@@ -418,13 +526,49 @@ struct Append {
   int32_t val;
 };
 
+template <typename T, int D, typename TO, int C, int NS>
+void launch_decode_c(const void* Q, const void* K, const void* V, const ExpressSegs& g, int64_t S,
+                     int64_t ld, int64_t m, int split, float* part, void* O, const Append& ap,
+                     hipStream_t st) {
+  DecSegs<NS> segs;
+  segs.n = g.n;
+  int64_t off = 0;
+  for (int k = 0; k < NS; ++k) {
+    const ExpressSeg& x = g.seg[k < g.n ? k : 0];
+    segs.seg[k] = {x.src, x.stride, (int32_t)((x.src ? 0 : x.start) - off), (int32_t)(off + x.len),
+                   x.logw};
+    if (k < g.n) off += x.len;
+  }
+  hipLaunchKernelGGL((decode_attn_kernel<T, D, TO, C, NS>), dim3((unsigned)split, (unsigned)S, C),
+                     dim3(64 * kDecWaves), 0, st, (const T*)Q, (const T*)K, (const T*)V, ld,
+                     (int32_t)m, split, part, (TO*)O, ap.dst, ap.stride, ap.val, segs);
+}
+
+template <typename T, int D, typename TO, int NS>
+void launch_decode_n(const void* Q, const void* K, const void* V, const ExpressSegs& g, int64_t S,
+                     int64_t ld, int64_t m, int split, float* part, void* O, const Append& ap,
+                     hipStream_t st) {
+  // Four workgroups per slice (else two, one) while the launch has at most one
+  // per CU: each then has a CU to itself, with a quarter of V's work.  32
+  // slices, ~410 keys, bf16, d = 128: 6.3 us with four, 6.8 with two, 7.6 with
+  // one (9.4 with one look-up after the other and one workgroup per slice).
+  const int64_t wgs = S * split;
+  if (wgs * 4 <= kDecMaxWorkgroups)
+    launch_decode_c<T, D, TO, 4, NS>(Q, K, V, g, S, ld, m, split, part, O, ap, st);
+  else if (wgs * 2 <= kDecMaxWorkgroups)
+    launch_decode_c<T, D, TO, 2, NS>(Q, K, V, g, S, ld, m, split, part, O, ap, st);
+  else
+    launch_decode_c<T, D, TO, 1, NS>(Q, K, V, g, S, ld, m, split, part, O, ap, st);
+}
+
 template <typename T, int D, typename TO>
-hipError_t launch_decode_t(const void* Q, const void* K, const void* V, const ExpressSegs& segs,
+hipError_t launch_decode_t(const void* Q, const void* K, const void* V, const ExpressSegs& g,
                            int64_t S, int64_t ld, int64_t m, int split, float* part, void* O,
                            const Append& ap, hipStream_t st) {
-  hipLaunchKernelGGL((decode_attn_kernel<T, D, TO>), dim3((unsigned)split, (unsigned)S),
-                     dim3(64 * kDecWaves), 0, st, (const T*)Q, (const T*)K, (const T*)V, segs, ld,
-                     m, split, part, (TO*)O, ap.dst, ap.stride, ap.val);
+  if (g.n <= kDecFewSegs)
+    launch_decode_n<T, D, TO, kDecFewSegs>(Q, K, V, g, S, ld, m, split, part, O, ap, st);
+  else
+    launch_decode_n<T, D, TO, kExpressMaxSegs>(Q, K, V, g, S, ld, m, split, part, O, ap, st);
   if (split > 1)
     hipLaunchKernelGGL((decode_attn_merge_kernel<D, TO>), dim3((unsigned)S), dim3(128), 0, st,
                        (const float*)part, split, (TO*)O, ap.dst, ap.stride, ap.val);
