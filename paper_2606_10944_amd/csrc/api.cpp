@@ -71,14 +71,22 @@ constexpr size_t kScoreCap = (size_t)2 << 30;
 
 size_t score_bytes(int64_t N) { return thin::halve_score_bytes(N); }
 
-size_t score_region(int64_t S, int64_t d, const Levels& lv, size_t cap_bytes = kScoreCap) {
+// `spread` adds the rounds of few small buckets that may run as scores and
+// decisions instead of one local launch (at most kSpreadMaxBuckets buckets of
+// 40 KiB): plans ask for that room, calls use it where the workspace has it.
+size_t score_region(int64_t S, int64_t d, const Levels& lv, size_t cap_bytes = kScoreCap,
+                    bool spread = false) {
   size_t region = 0;
   // rounds whose buckets run as one local launch (for either dtype) need none
   const int64_t local = std::min(thin::halve_local_rows(0, d), thin::halve_local_rows(1, d));
   for (int32_t r = 0; r < lv.L; ++r) {
-    if (lv.N[r] <= local) continue;
     const size_t per = score_bytes(lv.N[r]);
     const size_t all = (size_t)(S * lv.G[r]) * per;
+    if (lv.N[r] <= local) {
+      if (spread && S * lv.G[r] <= thin::kSpreadMaxBuckets && all <= cap_bytes)
+        region = std::max(region, all);
+      continue;
+    }
     const size_t cap = per > cap_bytes ? per : cap_bytes;
     const size_t need = all < cap ? all : cap;
     if (need > region) region = need;
@@ -129,7 +137,8 @@ struct Workspace {
   size_t bytes;
 };
 
-Workspace carve(void* base, int64_t S, int64_t d, const Levels& lv, size_t cap = kScoreCap) {
+Workspace carve(void* base, int64_t S, int64_t d, const Levels& lv, size_t cap = kScoreCap,
+                bool spread = false) {
   Workspace w;
   unsigned char* p = static_cast<unsigned char*>(base);
   const size_t pairs = (size_t)S * (size_t)(lv.n_kept / 2);
@@ -160,14 +169,15 @@ Workspace carve(void* base, int64_t S, int64_t d, const Levels& lv, size_t cap =
   w.mB = reinterpret_cast<float*>(p + off);
   off += align256(block_scales(S, lv) * 4);
   w.E = reinterpret_cast<float*>(p + off);
-  w.e_bytes = score_region(S, d, lv, cap);
+  w.e_bytes = score_region(S, d, lv, cap, spread);
   off += align256(w.e_bytes);
   w.bytes = off;
   return w;
 }
 
-size_t workspace_size(int64_t S, int64_t d, const Levels& lv, size_t cap = kScoreCap) {
-  return carve(nullptr, S, d, lv, cap).bytes;
+size_t workspace_size(int64_t S, int64_t d, const Levels& lv, size_t cap = kScoreCap,
+                      bool spread = false) {
+  return carve(nullptr, S, d, lv, cap, spread).bytes;
 }
 
 // The launch observer is a diagnostic of the calling thread (thread-local):
@@ -191,7 +201,9 @@ hipError_t observed(int32_t kernel, int32_t round, hipStream_t st, F&& launch) {
 // as many launches as the score region (e_bytes) needs.
 hipError_t kh_round(int32_t dtype, int64_t d, thin::HalveArgs a, int64_t buckets, size_t e_bytes,
                     int32_t r, hipStream_t st) {
-  if (a.N <= thin::halve_local_rows(dtype, d)) {
+  if (a.N <= thin::halve_local_rows(dtype, d) &&
+      !(thin::halve_spread(dtype, a.N, buckets) &&
+        e_bytes >= (size_t)buckets * thin::halve_score_bytes(a.N))) {
     a.b0 = 0;
     return observed(THIN_KERNEL_LOCAL, r, st,
                     [&] { return thin::launch_local(dtype, d, a, buckets, st); });
@@ -247,7 +259,9 @@ int compress_impl(const void* K, const void* V, int32_t dtype, int64_t B, int64_
       if (!(delta[r] > 0.0 && delta[r] <= 1.0)) return THIN_EINVAL;
   if (!workspace || workspace_bytes < workspace_size(S, d, lv, cap)) return THIN_EWORKSPACE;
   if ((reinterpret_cast<uintptr_t>(workspace) & 255u) != 0) return THIN_EWORKSPACE;
-  Workspace ws = carve(workspace, S, d, lv, cap);
+  // (the score region is the last: only its end moves)
+  Workspace ws = carve(workspace, S, d, lv, cap,
+                       workspace_bytes >= workspace_size(S, d, lv, cap, true));
   hipStream_t st = static_cast<hipStream_t>(stream);
   const size_t esz = dtype == THIN_FP32 ? 4 : 2;
   const void* Km = static_cast<const unsigned char*>(K) + (size_t)n_sinks * (size_t)d * esz;
@@ -695,7 +709,7 @@ int thin_plan(int64_t B, int64_t H, int64_t n, int64_t d, int64_t n_out, int32_t
   plan->uniforms_per_slice = lv.U;
   plan->uniforms_total = S * lv.U;
   plan->max_bucket = lv.max_bucket;
-  plan->workspace_bytes = workspace_size(S, d, lv);
+  plan->workspace_bytes = workspace_size(S, d, lv, kScoreCap, true);
   return THIN_OK;
 }
 
@@ -1135,9 +1149,6 @@ hipError_t pf_halve(int32_t dtype, int64_t d, int32_t halve, const PfLayout& L,
   a.rowh2_write = 1;
   a.mB = reinterpret_cast<float*>(ws + L.mB);
   a.status = reinterpret_cast<int32_t*>(ws + L.status);
-  if (N <= thin::halve_local_rows(dtype, d))  // every call in one local launch
-    return observed(THIN_KERNEL_LOCAL, -1, st,
-                    [&] { return thin::launch_local(dtype, d, a, S * G, st); });
   return kh_round(dtype, d, a, S * G, L.e_bytes, -1, st);
 }
 

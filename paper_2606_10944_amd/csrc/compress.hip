@@ -581,6 +581,19 @@ __device__ __forceinline__ int frag_row(int rt, int m16) {
   return 8 * (m16 >> 2) + 4 * rt + (m16 & 3);
 }
 
+// F of two 16 x 16 Gram tiles (rows of the wave's 16 pairs) at scale 2^-he.
+__device__ __forceinline__ void score_kappa(const floatx4_t* gk, const floatx4_t* gv, float c2,
+                                            float he, float* f) {
+#pragma unroll
+  for (int rt = 0; rt < 2; ++rt) {
+    float kap[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      kap[e] = __builtin_amdgcn_exp2f(gk[rt][e] * c2 - he) * gv[rt][e];
+    f[2 * rt] = kap[1] - kap[0];
+    f[2 * rt + 1] = kap[3] - kap[2];
+  }
+}
 // F = kappa(y'_i, x) - kappa(y_i, x) of the wave's 16 pairs i against the
 // column rows x of one 16-row tile, whose fragments (CHUNKS KiB) start at st:
 // lane (g, m16) gets f[k] for the pairs i = 4g + k against row m16, at the
@@ -606,15 +619,7 @@ __device__ __forceinline__ void score_f(const uint4 (&Ak)[2][NV], const uint4 (&
       gv[rt] = mma_word<T>(Av[rt][v], bv, gv[rt]);
     }
   }
-#pragma unroll
-  for (int rt = 0; rt < 2; ++rt) {
-    float kap[4];
-#pragma unroll
-    for (int e = 0; e < 4; ++e)
-      kap[e] = __builtin_amdgcn_exp2f(gk[rt][e] * c2 - he) * gv[rt][e];
-    f[2 * rt] = kap[1] - kap[0];
-    f[2 * rt + 1] = kap[3] - kap[2];
-  }
+  score_kappa(gk, gv, c2, he, f);
 }
 // E(i, p) = F(i, y_p) - F(i, y'_p) of the four pairs i = 4g + k: the even lane
 // of a pair of lanes takes the pair p of the first 16-row column tile (f0),
@@ -1029,6 +1034,144 @@ void pair_scores_kernel(HalveArgs a) {
       st = st == NS - 1 ? 0 : st + 1;
     }
   }
+}
+
+// Scores of a round of few buckets, one wave per unit of 32 rows x 32 columns:
+// half-block hb of the bucket against column tile jc >= 2 (hb / 2).  A
+// workgroup of the kernel above holds 256 rows and takes its tiles one after
+// the other, so a launch of few buckets runs on few CUs and a workgroup's chain
+// is its time; here every unit is a wave of its own with its rows read straight
+// into registers (no LDS, no barrier), which reads a row N / 32 times but puts
+// the launch on every CU.  Same products in the same order, same scales, same
+// score layout.  The diagonal units write the pair terms (and row scales), the
+// first unit of a block its largest row scale.  In the first round (no table of
+// row scales yet) a unit forms the scales it needs itself.
+constexpr int kUnitWaves = 4;
+__host__ __device__ inline int64_t score_units(int64_t N) {
+  const int64_t NC = (N + 31) / 32, nb = (N + 63) / 64;
+  return 2 * (nb * NC - nb * (nb - 1));  // two half-blocks of every block, tiles 2 blk .. NC - 1
+}
+
+template <typename T, int D>
+__global__ __launch_bounds__(64 * kUnitWaves) void score_units_kernel(HalveArgs a) {
+  constexpr int NV = Frag<T, D>::NV;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int m16 = lane & 15, g = lane >> 4;
+  const bool odd = (m16 & 1) != 0;
+  const int N = a.N, P = N >> 1;
+  const int NT = (N + 15) >> 4, NC = (N + 31) >> 5, nb = (N + 63) >> 6;
+  const int64_t id = (int64_t)blockIdx.x * kUnitWaves + wave;
+  const int64_t bl = id / a.ipb;
+  if (bl >= a.nbk) return;  // whole waves; no barrier below
+  // unit -> block (its units: two half-blocks x tiles 2 blk .. NC - 1), half, tile
+  int u = (int)(id - bl * a.ipb), blk = 0;
+  while (u >= 2 * (NC - 2 * blk)) u -= 2 * (NC - 2 * blk++);
+  const int half = u & 1, jc = 2 * blk + (u >> 1);
+  const int64_t bucket = a.b0 + bl;
+  const int64_t s = bucket / a.G, t = bucket % a.G;
+  const T* K = reinterpret_cast<const T*>(a.K) + s * a.ld * D;
+  const T* V = reinterpret_cast<const T*>(a.V) + s * a.ld * D;
+  const int32_t* rows_in = a.idx_in ? a.idx_in + s * in_stride(a) + t * (int64_t)N : nullptr;
+  const int64_t row_base = t * (int64_t)N;
+  const bool table = !a.rowh2_write;
+  const double inv_sqrt_d = 1.0 / sqrt((double)D);
+  const float c2 = (float)(kLog2e * inv_sqrt_d);
+  const bool diag = jc == 2 * blk + half;
+  auto row_of = [&](int j) { return j < N ? (rows_in ? (int64_t)rows_in[j] : row_base + j) : -1; };
+
+  // rows of the half-block, of the column tile and (for the block's largest
+  // scale, without a table) of the block's other half
+  int64_t ar[2], br[2], cr[2];
+#pragma unroll
+  for (int rt = 0; rt < 2; ++rt) {
+    ar[rt] = row_of(blk * 64 + half * 32 + frag_row(rt, m16));
+    br[rt] = row_of(jc * 32 + frag_row(rt, m16));
+    cr[rt] = table ? -1 : row_of(blk * 64 + (half ^ 1) * 32 + frag_row(rt, m16));
+  }
+  const int64_t tr = table ? row_of(blk * 64 + lane) : -1;
+  const float vmax = __uint_as_float(a.vmax_bits[a.vmax_per_bucket ? bucket : s]);
+  const float th = tr >= 0 ? a.rowh2[s * a.n + tr] : 0.0f;
+  float bh[2];
+#pragma unroll
+  for (int rt = 0; rt < 2; ++rt) bh[rt] = table && br[rt] >= 0 ? a.rowh2[s * a.n + br[rt]] : 0.0f;
+  uint4 Ak[2][NV], Av[2][NV], Bk[2][NV], Ck[2][NV];
+#pragma unroll
+  for (int rt = 0; rt < 2; ++rt) {
+    load_frag<T, D>(K, ar[rt] >= 0 ? ar[rt] : 0, g, ar[rt] >= 0, Ak[rt]);
+    load_frag<T, D>(K, br[rt] >= 0 ? br[rt] : 0, g, br[rt] >= 0, Bk[rt]);
+    load_frag<T, D>(V, ar[rt] >= 0 ? ar[rt] : 0, g, ar[rt] >= 0, Av[rt]);
+    if (!table) load_frag<T, D>(K, cr[rt] >= 0 ? cr[rt] : 0, g, cr[rt] >= 0, Ck[rt]);
+  }
+  const float vm2f = vmax * vmax;
+  const double vm2d = (double)vmax * (double)vmax;
+  auto scale_of = [&](const uint4* f) {  // a row's scale exponent (0 for a row of zeros)
+    return row_h2f(sum_quarters(quarter_self_dot<T, D>(f)), inv_sqrt_d);
+  };
+  // the block's largest row scale and the columns' pair scales
+  float mB;
+  if (table) {
+    mB = wave_max_f(th);
+  } else {
+    float m = 0.0f;
+#pragma unroll
+    for (int rt = 0; rt < 2; ++rt) m = fmaxf(m, fmaxf(scale_of(Ak[rt]), scale_of(Ck[rt])));
+    mB = wave_max_f(m);
+#pragma unroll
+    for (int rt = 0; rt < 2; ++rt) bh[rt] = scale_of(Bk[rt]);
+  }
+  if (diag) {
+    const int64_t pb = s * (a.n_r >> 1) + t * (int64_t)P;
+#pragma unroll
+    for (int rt = 0; rt < 2; ++rt) {
+      float rh2, h2f, lbt;
+      frag_pair_terms<T, D>(Ak[rt], Av[rt], vm2d, inv_sqrt_d, rh2, h2f, lbt);
+      const int j = jc * 32 + frag_row(rt, m16);
+      if (g == 0 && j < N) {
+        if ((j & 1) == 0) {
+          a.h2[pb + (j >> 1)] = h2f;
+          a.lbt[pb + (j >> 1)] = lbt;
+        }
+        if (a.rowh2_write) a.rowh2[s * a.n + ar[rt]] = rh2;
+      }
+    }
+  }
+  if (half == 0 && jc == 2 * blk && lane == 0) a.mB[bucket * nb + blk] = mB;
+
+  floatx4_t gk[2][2], gv[2][2];  // [column half][row half]
+#pragma unroll
+  for (int ct = 0; ct < 2; ++ct)
+#pragma unroll
+    for (int rt = 0; rt < 2; ++rt) {
+      gk[ct][rt] = (floatx4_t){0.f, 0.f, 0.f, 0.f};
+      gv[ct][rt] = (floatx4_t){vm2f, vm2f, vm2f, vm2f};  // <v,v'> + v_max^2
+    }
+#pragma unroll
+  for (int ct = 0; ct < 2; ++ct)
+#pragma unroll
+    for (int v = 0; v < NV; ++v)
+#pragma unroll
+      for (int rt = 0; rt < 2; ++rt) gk[ct][rt] = mma_word<T>(Ak[rt][v], Bk[ct][v], gk[ct][rt]);
+#pragma unroll
+  for (int ct = 0; ct < 2; ++ct)
+    load_frag<T, D>(V, br[ct] >= 0 ? br[ct] : 0, g, br[ct] >= 0, Bk[ct]);
+#pragma unroll
+  for (int ct = 0; ct < 2; ++ct)
+#pragma unroll
+    for (int v = 0; v < NV; ++v)
+#pragma unroll
+      for (int rt = 0; rt < 2; ++rt) gv[ct][rt] = mma_word<T>(Av[rt][v], Bk[ct][v], gv[ct][rt]);
+  float f[2][4];
+#pragma unroll
+  for (int ct = 0; ct < 2; ++ct) {
+    const float h2 = pair_h2f(bh[ct]);
+    score_kappa(gk[ct], gv[ct], c2, h2 + scale_shift(mB, h2), f[ct]);
+  }
+  const float4 e = score_e(f[0], f[1], odd);
+  const int q = 4 * (m16 >> 2) + 2 * (odd ? 1 : 0) + ((m16 >> 1) & 1);
+  if (2 * jc + (q >> 3) < NT)
+    *reinterpret_cast<float4*>(a.E + (bl * a.e_tiles + panel_tiles(blk, NT, 4) - 4 * blk) * 256 +
+                               (int64_t)jc * 512 + half * half_run(jc, NT) + q * 16 + 4 * g) = e;
 }
 
 // Buckets of at most 64 rows (one decision block of P <= 32 pairs): one
@@ -1735,8 +1878,26 @@ __global__ __launch_bounds__(64) void gram16_kernel(const T* rows, float* out) {
 #ifndef SCORE_IL
 #define SCORE_IL 16
 #endif
+// Float score launches of at most this many units of 32 x 32 take a wave per
+// unit: 16 buckets of 1024 rows (8448 units, first round) 77 -> 61 us, of 512
+// rows 38 -> 24 us (d = 64).  Beyond, the device is full either way and the
+// workgroups of eight waves read each row once for 256 others.  bf16 rows stay
+// with those at every size: their products are eight times as fast and the
+// launch is all latency (32 buckets of 512 rows: 15 us against 19).
+constexpr int64_t kUnitLaunchMax = 16384;
+
 template <typename T, int D>
 hipError_t launch_scores_td(const HalveArgs& a0, int64_t nbk, hipStream_t st) {
+  if constexpr (Elem<T>::bytes == 4) {
+    if (score_units(a0.N) * nbk <= kUnitLaunchMax) {
+      HalveArgs u = a0;
+      u.nbk = nbk;
+      u.ipb = (int32_t)score_units(a0.N);
+      const unsigned wgs = (unsigned)((u.ipb * nbk + kUnitWaves - 1) / kUnitWaves);
+      hipLaunchKernelGGL((score_units_kernel<T, D>), dim3(wgs), dim3(64 * kUnitWaves), 0, st, u);
+      return hipGetLastError();
+    }
+  }
   constexpr int WO = score_waves<T, D>();
   using SS = ScoreShape<T, D, WO>;  // own and streamed chunks share the groups
   auto kern_mixed = pair_scores_kernel<T, D, false, false, WO>;
@@ -1955,6 +2116,14 @@ hipError_t launch_scores(int dtype, int64_t d, const HalveArgs& a0, int64_t nbk,
 
 int64_t halve_local_rows(int dtype, int64_t d) {
   return dtype == 0 ? local_rows_t<float>(d) : local_rows_t<bf16_t>(d);
+}
+
+// Float buckets of 129 to 256 rows: one CU's float matrix rate sets the local
+// launch's time (1 to 32 buckets of 256 rows, d = 64: 40 us), against 11.5 us
+// for the units and 10 us for the decisions of 1 to 16 buckets.  From about 32
+// buckets on the units' own work shows, and at 128 rows both take 20 us.
+bool halve_spread(int dtype, int64_t N, int64_t nbk) {
+  return dtype == 0 && N > 128 && nbk <= kSpreadMaxBuckets;
 }
 
 hipError_t launch_local(int dtype, int64_t d, const HalveArgs& a, int64_t nbk, hipStream_t st) {

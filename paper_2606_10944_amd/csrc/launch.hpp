@@ -114,6 +114,11 @@ constexpr int kMaxHelpers = 7;
 // Buckets of at most halve_local_rows(dtype, d) rows: the whole round (scores
 // in LDS, then the decisions) in one launch, no score buffer.
 int64_t halve_local_rows(int dtype, int64_t d);
+// A round of nbk buckets small enough for the local launch that is faster as
+// scores and decisions, the scores spread over the device (needs nbk buckets'
+// score bytes).
+constexpr int64_t kSpreadMaxBuckets = 32;
+bool halve_spread(int dtype, int64_t N, int64_t nbk);
 hipError_t launch_local(int dtype, int64_t d, const HalveArgs& a, int64_t nbk, hipStream_t st);
 
 // Express cache (express.hip).  A segment of a slice's key list: src null =

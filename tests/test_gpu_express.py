@@ -84,6 +84,28 @@ def test_express_decode_parity(c):
     print(f"near ties {near}")
 
 
+# A step's columns of V over four, two and one workgroups per slice (up to 64,
+# up to 128 and more slices), each with key rows of 4, 8, 16 and 32 lanes, and a
+# cache of over 1024 keys (two workgroups of keys per slice, then the merge).
+SPLIT = [dict(B=1, H=S, d=d, dtype=t, n_out=8, mbar=2, n=70, halve="uniform")
+         for S in (64, 65, 129) for d, t in ((32, "bf16"), (64, "bf16"), (128, "bf16"), (128, "fp32"))]
+SPLIT += [dict(B=1, H=S, d=64, dtype="bf16", n_out=1100, mbar=2, n=1110, halve="uniform")
+          for S in (2, 33, 65)]
+
+
+@pytest.mark.parametrize("c", SPLIT, ids=lambda c: f"S{c['H']}-o{c['n_out']}-d{c['d']}-{c['dtype']}")
+def test_express_decode_column_split(c):
+    w, Q, K, V, U, O, idx, lw, m, tr, plan, draws = _run(c)
+    us = plan["uniforms_per_slice"]
+    Us = U.numpy().reshape(w.S, -1) if us else np.zeros((w.S, 1), np.float32)
+    for s in (0, w.S // 2, w.S - 1):
+        r = oracle.express_decode(Q[0, s], K[0, s], V[0, s], c["n_out"], c["mbar"], Us[s],
+                                  halve="uniform", sub_u=draws)
+        assert np.array_equal(r["idx"], idx[0, s]), s
+        err = np.abs(r["O"] - O[0, s]).max()
+        assert err <= (2e-3 if c["dtype"] == "bf16" else 1e-5), (s, err)
+
+
 @pytest.mark.parametrize("c", CASES, ids=lambda c: f"o{c['n_out']}-mbar{c['mbar']}-n{c['n']}-d{c['d']}-{c['dtype']}-{c['halve']}")
 def test_express_prefill_parity(c):
     """Masked prefill: every point's output equals Thinformer decoding's (the

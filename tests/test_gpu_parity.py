@@ -191,6 +191,34 @@ CUSTOM = [
 ]
 
 
+# Edges of the score launches' units of 32 x 32 and of their column chunks:
+# bucket sizes with 2, 8, 18 or 30 rows past a multiple of 32 (a last column
+# tile of half its pairs), in the wave-per-unit launches (float rows, the first
+# round and later ones, and buckets of 129-256 rows) and in the streamed chunks
+# (bf16; float rows past the unit launches' size).
+UNIT_EDGES = [
+    dict(B=1, H=1, n=132, n_out=66, g=0, d=64, dtype="fp32", kind="gauss_d4"),
+    dict(B=2, H=1, n=1000, n_out=125, g=3, d=32, dtype="fp32", kind="gauss_d4"),
+    dict(B=1, H=2, n=1192, n_out=149, g=3, d=64, dtype="fp32", kind="heavy_tail_mean"),
+    dict(B=1, H=1, n=804, n_out=201, g=2, d=128, dtype="fp32", kind="gauss_d4"),
+    dict(B=1, H=2, n=2276, n_out=569, g=2, d=128, dtype="bf16", kind="heavy_tail"),
+    dict(B=1, H=1, n=5000, n_out=625, g=3, d=64, dtype="bf16", kind="gauss"),
+    dict(B=1, H=1, n=4104, n_out=513, g=3, d=32, dtype="bf16", kind="layernorm"),
+    # 40 slices of one 1200-row bucket: 59280 units, so streamed chunks
+    dict(B=4, H=10, n=1200, n_out=600, g=0, d=32, dtype="fp32", kind="gauss_d4"),
+    # 48 buckets of 200 rows: the local launch again
+    dict(B=4, H=12, n=200, n_out=100, g=0, d=64, dtype="fp32", kind="gauss_d4"),
+]
+
+
+@pytest.mark.parametrize("cfg", UNIT_EDGES, ids=lambda c: f"S{c['B'] * c['H']}-n{c['n']}-o{c['n_out']}-g{c['g']}-d{c['d']}-{c['dtype']}")
+def test_score_unit_and_chunk_edges(cfg):
+    w = W.custom("units", seed=19, **cfg)
+    Q, K, V = W.make_qkv(w)
+    plan, U, idx, tr = _compress_gpu(w, Q, K, V)
+    _check_compress(w, K, V, U, idx, tr, range(min(w.S, 4)))
+
+
 @pytest.mark.parametrize("cfg", CUSTOM, ids=lambda c: f"n{c['n']}-o{c['n_out']}-g{c['g']}-d{c['d']}-{c['dtype']}")
 def test_custom_shapes_parity(cfg):
     w = W.custom("custom", seed=11, **cfg)
@@ -518,3 +546,30 @@ def test_resident_attention_tiers(d, n_out):
         ref = oracle.weighted_attention(Q[0, h], K[0, h], V[0, h], idx[0, h],
                                         logw[0, h].astype(np.float64))
         assert np.abs(ref - Ow[0, h]).max() <= 2e-3, (d, n_out, h, "weighted")
+
+
+@pytest.mark.parametrize("n_out", [129, 161, 192, 193, 225, 256])
+@pytest.mark.parametrize("dropped", ["first", "last"])
+def test_two_pass_attention_with_a_dropped_pass(n_out, dropped):
+    """Above 128 keys (d = 128) the keys are taken in two passes: one whose keys
+    all weigh nothing adds nothing (n_out at the edges of the key tiles, an odd
+    query count over several workgroup steps)."""
+    w = W.custom("tp", B=1, H=2, n=600, n_q=1031, d=128, dtype="bf16", kind="gauss")
+    Q, K, V = W.make_qkv(w)
+    rng = np.random.default_rng(n_out)
+    idx = rng.integers(0, 600, size=(1, 2, n_out)).astype(np.int32)
+    logw = (rng.standard_normal((1, 2, n_out)) * 2).astype(np.float32)
+    half = (96 if n_out <= 192 else 128)
+    if dropped == "first":
+        logw[:, :, :half] = -np.inf
+    else:
+        logw[:, :, half:] = -np.inf
+    args = [t.to(DEV) for t in (Q, K, V, torch.from_numpy(idx))]
+    O = thin_attention(*args, logw=torch.from_numpy(logw).to(DEV)).cpu().numpy()
+    Ob = thin_attention(*args, out_dtype=torch.bfloat16).float().cpu().numpy()
+    for h in range(2):
+        ref = oracle.weighted_attention(Q[0, h], K[0, h], V[0, h], idx[0, h],
+                                        logw[0, h].astype(np.float64))
+        assert np.abs(ref - O[0, h]).max() <= 2e-3, h
+        ref = oracle.attention(Q[0, h], K[0, h], V[0, h], idx[0, h])
+        assert np.all(np.abs(ref - Ob[0, h]) <= 2e-3 + 2.0 ** -8 * np.abs(ref)), h
