@@ -5,7 +5,7 @@
 // <q, k_j> gets the bias sqrt(d) * logw[s, j], staged in LDS beside the keys
 // (a key past n_out or of weight 0 has bias -inf, which also masks it).
 //
-// One workgroup = 4 waves = 128 queries of one slice.  The coreset is walked
+// One workgroup = 4 waves = 64 or 128 queries of one slice.  The coreset is walked
 // in chunks of 64 keys staged in LDS (gathered through idx); scores S^T =
 // K_I Q^T come from 16x16 MFMA tiles (keys x queries), the softmax is online
 // in float32, and O^T += V_I^T P^T reuses the score tile's register layout as
@@ -13,6 +13,8 @@
 // MFMA as two terms, P = hi + lo with hi = bf16(P), lo = bf16(P - hi), so the
 // product keeps about 16 significant bits of P instead of 8.
 #include <math.h>
+
+#include <algorithm>
 
 #include "common.hpp"
 #include "launch.hpp"
@@ -22,10 +24,9 @@ namespace thin {
 namespace {
 
 constexpr int KC = 64;   // keys per chunk
-constexpr int QT = 2;    // 16-query tiles per wave
 constexpr int WAVES = 4;
-constexpr int QPB = 16 * QT * WAVES;  // queries per workgroup
-// The prefill kernel takes the same 128 queries per workgroup as 8 waves of
+constexpr int QPB = 128;  // points per prefill tile
+// The prefill kernel takes 128 queries per workgroup as 8 waves of
 // one 16-query tile: half the registers per wave (128, four waves per SIMD,
 // two workgroups per CU), so a chunk's gathers, barriers and arithmetic of
 // one workgroup overlap the other's (65536 points x 32 slices: 8.19 -> 5.76
@@ -59,7 +60,7 @@ __device__ __forceinline__ void store4<bf16_t>(bf16_t* p, float a, float b, floa
   *reinterpret_cast<uint2*>(p) = make_uint2(__builtin_bit_cast(uint32_t, lo), __builtin_bit_cast(uint32_t, hi));
 }
 
-template <typename T, int D, typename TO, bool W>
+template <typename T, int D, typename TO, bool W, int QT>
 __global__ __launch_bounds__(64 * WAVES) void coreset_attn_kernel(
     const T* __restrict__ Q, const T* __restrict__ K, const T* __restrict__ V,
     const int32_t* __restrict__ idx, const float* __restrict__ logw, int64_t n, int64_t n_q,
@@ -75,7 +76,6 @@ __global__ __launch_bounds__(64 * WAVES) void coreset_attn_kernel(
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int m16 = lane & 15, g = lane >> 4;
   const int64_t s = blockIdx.y;
-  const int64_t q0 = (int64_t)blockIdx.x * QPB + wave * 16 * QT;
   const float* Ws = W ? logw + s * (int64_t)n_out : nullptr;
   const float sqrt_d = (float)sqrt((double)D);
   const T* Ks = K + s * n * D;
@@ -83,143 +83,152 @@ __global__ __launch_bounds__(64 * WAVES) void coreset_attn_kernel(
   const int32_t* Is = idx + s * (int64_t)n_out;
   const float c2 = (float)(kLog2e / sqrt((double)D));
 
-  uint4 Bq[QT][NV];
-#pragma unroll
-  for (int qt = 0; qt < QT; ++qt) {
-    const int64_t q = q0 + qt * 16 + m16;
-    load_frag<T, D>(Q + s * n_q * D, q, g, q < n_q, Bq[qt]);
-  }
-
-  float mrun[QT], lrun[QT];
-  floatx4_t acc[QT][D / 16];
-#pragma unroll
-  for (int qt = 0; qt < QT; ++qt) {
-    mrun[qt] = -INFINITY;
-    lrun[qt] = 0.0f;
-#pragma unroll
-    for (int dt = 0; dt < D / 16; ++dt) acc[qt][dt] = (floatx4_t){0.f, 0.f, 0.f, 0.f};
-  }
-
   constexpr int WPR = D * Elem<T>::bytes / 16;  // 16-byte words per row
-  for (int c0 = 0; c0 < n_out; c0 += KC) {
-    const int kc = min(KC, n_out - c0);
-    __syncthreads();
-    if (W && threadIdx.x < KC)
-      sB[threadIdx.x] = (int)threadIdx.x < kc ? Ws[c0 + threadIdx.x] * sqrt_d : -INFINITY;
-    for (int w = threadIdx.x; w < KC * WPR; w += 64 * WAVES) {
-      const int key = w / WPR, wi = w % WPR;
-      uint4 kw = make_uint4(0, 0, 0, 0), vw = make_uint4(0, 0, 0, 0);
-      if (key < kc) {
-        int64_t r = Is[c0 + key];
-        r = r < 0 ? 0 : (r >= n ? n - 1 : r);
-        kw = reinterpret_cast<const uint4*>(Ks + r * D)[wi];
-        vw = reinterpret_cast<const uint4*>(Vs + r * D)[wi];
-      }
-      *reinterpret_cast<uint4*>(sK + key * L::k_stride + wi * 16) = kw;
-      if (BF) {
-        const uint16_t* e = reinterpret_cast<const uint16_t*>(&vw);
-#pragma unroll
-        for (int j = 0; j < 8; ++j)
-          *reinterpret_cast<uint16_t*>(sV + (wi * 8 + j) * L::v_stride + key * 2) = e[j];
-      } else {
-        *reinterpret_cast<uint4*>(sV + key * L::v_stride + wi * 16) = vw;
-      }
-    }
-    __syncthreads();
-
-    uint4 Ak[4][NV];
-#pragma unroll
-    for (int kt = 0; kt < 4; ++kt) {
-      const uint4* p = reinterpret_cast<const uint4*>(sK + (kt * 16 + m16) * L::k_stride);
-#pragma unroll
-      for (int v = 0; v < NV; ++v) Ak[kt][v] = p[4 * v + g];
-    }
-
+  // The workgroup's blocks of queries, gridDim.x apart; a coreset of one chunk
+  // is staged for the first of them and stays.
+  const int64_t nqb = (n_q + 16 * QT * WAVES - 1) / (16 * QT * WAVES);
+  for (int64_t qb = blockIdx.x; qb < nqb; qb += gridDim.x) {
+    const int64_t q0 = qb * (16 * QT * WAVES) + wave * 16 * QT;
+    uint4 Bq[QT][NV];
 #pragma unroll
     for (int qt = 0; qt < QT; ++qt) {
-      float sc[4][4];
-      float mx = -INFINITY;
-#pragma unroll
-      for (int kt = 0; kt < 4; ++kt) {
-        floatx4_t z = {0.f, 0.f, 0.f, 0.f};
-        z = mma_rows<T, D>(Ak[kt], Bq[qt], z);
-        if (W) {
-          const float4 b = *reinterpret_cast<const float4*>(sB + kt * 16 + 4 * g);
-          z[0] += b.x; z[1] += b.y; z[2] += b.z; z[3] += b.w;
-        }
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int key = kt * 16 + 4 * g + i;
-          sc[kt][i] = W || key < kc ? z[i] : -INFINITY;
-          mx = fmaxf(mx, sc[kt][i]);
-        }
-      }
-      mx = fmaxf(mx, __shfl_xor(mx, 16));
-      mx = fmaxf(mx, __shfl_xor(mx, 32));
-      const float mnew = fmaxf(mrun[qt], mx);
-      const float scale = mrun[qt] == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f((mrun[qt] - mnew) * c2);
-      mrun[qt] = mnew;
-      float psum = 0.0f;
-      float pr[4][4];
-#pragma unroll
-      for (int kt = 0; kt < 4; ++kt)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const float pv = sc[kt][i] == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f((sc[kt][i] - mnew) * c2);
-          pr[kt][i] = pv;
-          psum += pv;
-        }
-      lrun[qt] = lrun[qt] * scale + psum;
-#pragma unroll
-      for (int dt = 0; dt < D / 16; ++dt) acc[qt][dt] *= scale;
+      const int64_t q = q0 + qt * 16 + m16;
+      load_frag<T, D>(Q + s * n_q * D, q, g, q < n_q, Bq[qt]);
+    }
 
-      if (BF) {
+    float mrun[QT], lrun[QT];
+    floatx4_t acc[QT][D / 16];
 #pragma unroll
-        for (int c = 0; c < 2; ++c) {
-          float pv[8];
+    for (int qt = 0; qt < QT; ++qt) {
+      mrun[qt] = -INFINITY;
+      lrun[qt] = 0.0f;
 #pragma unroll
-          for (int j = 0; j < 8; ++j) pv[j] = pr[2 * c + (j >> 2)][j & 3];
-          bf16x8_t bhi, blo;
-          split_bf16x8(pv, bhi, blo);
+      for (int dt = 0; dt < D / 16; ++dt) acc[qt][dt] = (floatx4_t){0.f, 0.f, 0.f, 0.f};
+    }
+
+    for (int c0 = 0; c0 < n_out; c0 += KC) {
+      const int kc = min(KC, n_out - c0);
+      if (n_out > KC || qb == (int64_t)blockIdx.x) {
+        __syncthreads();
+        if (W && threadIdx.x < KC)
+          sB[threadIdx.x] = (int)threadIdx.x < kc ? Ws[c0 + threadIdx.x] * sqrt_d : -INFINITY;
+        for (int w = threadIdx.x; w < KC * WPR; w += 64 * WAVES) {
+          const int key = w / WPR, wi = w % WPR;
+          uint4 kw = make_uint4(0, 0, 0, 0), vw = make_uint4(0, 0, 0, 0);
+          if (key < kc) {
+            int64_t r = Is[c0 + key];
+            r = r < 0 ? 0 : (r >= n ? n - 1 : r);
+            kw = reinterpret_cast<const uint4*>(Ks + r * D)[wi];
+            vw = reinterpret_cast<const uint4*>(Vs + r * D)[wi];
+          }
+          *reinterpret_cast<uint4*>(sK + key * L::k_stride + wi * 16) = kw;
+          if (BF) {
+            const uint16_t* e = reinterpret_cast<const uint16_t*>(&vw);
 #pragma unroll
-          for (int dt = 0; dt < D / 16; ++dt) {
-            const unsigned char* row = sV + (dt * 16 + m16) * L::v_stride;
-            uint2 lo = *reinterpret_cast<const uint2*>(row + (32 * c + 4 * g) * 2);
-            uint2 hi = *reinterpret_cast<const uint2*>(row + (32 * c + 16 + 4 * g) * 2);
-            const bf16x8_t av = __builtin_bit_cast(bf16x8_t, make_uint4(lo.x, lo.y, hi.x, hi.y));
-            acc[qt][dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, bhi, acc[qt][dt], 0, 0, 0);
-            acc[qt][dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, blo, acc[qt][dt], 0, 0, 0);
+            for (int j = 0; j < 8; ++j)
+              *reinterpret_cast<uint16_t*>(sV + (wi * 8 + j) * L::v_stride + key * 2) = e[j];
+          } else {
+            *reinterpret_cast<uint4*>(sV + key * L::v_stride + wi * 16) = vw;
           }
         }
-      } else {
+        __syncthreads();
+      }
+      if (q0 >= n_q) continue;  // (whole waves; no barrier below)
+
+      uint4 Ak[4][NV];
+#pragma unroll
+      for (int kt = 0; kt < 4; ++kt) {
+        const uint4* p = reinterpret_cast<const uint4*>(sK + (kt * 16 + m16) * L::k_stride);
+#pragma unroll
+        for (int v = 0; v < NV; ++v) Ak[kt][v] = p[4 * v + g];
+      }
+
+#pragma unroll
+      for (int qt = 0; qt < QT; ++qt) {
+        float sc[4][4];
+        float mx = -INFINITY;
+#pragma unroll
+        for (int kt = 0; kt < 4; ++kt) {
+          floatx4_t z = {0.f, 0.f, 0.f, 0.f};
+          z = mma_rows<T, D>(Ak[kt], Bq[qt], z);
+          if (W) {
+            const float4 b = *reinterpret_cast<const float4*>(sB + kt * 16 + 4 * g);
+            z[0] += b.x; z[1] += b.y; z[2] += b.z; z[3] += b.w;
+          }
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const int key = kt * 16 + 4 * g + i;
+            sc[kt][i] = W || key < kc ? z[i] : -INFINITY;
+            mx = fmaxf(mx, sc[kt][i]);
+          }
+        }
+        mx = fmaxf(mx, __shfl_xor(mx, 16));
+        mx = fmaxf(mx, __shfl_xor(mx, 32));
+        const float mnew = fmaxf(mrun[qt], mx);
+        const float scale = mrun[qt] == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f((mrun[qt] - mnew) * c2);
+        mrun[qt] = mnew;
+        float psum = 0.0f;
+        float pr[4][4];
 #pragma unroll
         for (int kt = 0; kt < 4; ++kt)
 #pragma unroll
           for (int i = 0; i < 4; ++i) {
-            const int key = kt * 16 + 4 * g + i;
+            const float pv = sc[kt][i] == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f((sc[kt][i] - mnew) * c2);
+            pr[kt][i] = pv;
+            psum += pv;
+          }
+        lrun[qt] = lrun[qt] * scale + psum;
+#pragma unroll
+        for (int dt = 0; dt < D / 16; ++dt) acc[qt][dt] *= scale;
+
+        if (BF) {
+#pragma unroll
+          for (int c = 0; c < 2; ++c) {
+            float pv[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) pv[j] = pr[2 * c + (j >> 2)][j & 3];
+            bf16x8_t bhi, blo;
+            split_bf16x8(pv, bhi, blo);
 #pragma unroll
             for (int dt = 0; dt < D / 16; ++dt) {
-              const float av = *reinterpret_cast<const float*>(sV + key * L::v_stride + (dt * 16 + m16) * 4);
-              acc[qt][dt] = __builtin_amdgcn_mfma_f32_16x16x4f32(av, pr[kt][i], acc[qt][dt], 0, 0, 0);
+              const unsigned char* row = sV + (dt * 16 + m16) * L::v_stride;
+              uint2 lo = *reinterpret_cast<const uint2*>(row + (32 * c + 4 * g) * 2);
+              uint2 hi = *reinterpret_cast<const uint2*>(row + (32 * c + 16 + 4 * g) * 2);
+              const bf16x8_t av = __builtin_bit_cast(bf16x8_t, make_uint4(lo.x, lo.y, hi.x, hi.y));
+              acc[qt][dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, bhi, acc[qt][dt], 0, 0, 0);
+              acc[qt][dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, blo, acc[qt][dt], 0, 0, 0);
             }
           }
+        } else {
+#pragma unroll
+          for (int kt = 0; kt < 4; ++kt)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+              const int key = kt * 16 + 4 * g + i;
+#pragma unroll
+              for (int dt = 0; dt < D / 16; ++dt) {
+                const float av = *reinterpret_cast<const float*>(sV + key * L::v_stride + (dt * 16 + m16) * 4);
+                acc[qt][dt] = __builtin_amdgcn_mfma_f32_16x16x4f32(av, pr[kt][i], acc[qt][dt], 0, 0, 0);
+              }
+            }
+        }
       }
     }
-  }
 
 #pragma unroll
-  for (int qt = 0; qt < QT; ++qt) {
-    float l = lrun[qt];
-    l += __shfl_xor(l, 16);
-    l += __shfl_xor(l, 32);
-    const float inv = 1.0f / l;
-    const int64_t q = q0 + qt * 16 + m16;
-    if (q < n_q) {
-      TO* orow = O + (s * n_q + q) * D;
+    for (int qt = 0; qt < QT; ++qt) {
+      float l = lrun[qt];
+      l += __shfl_xor(l, 16);
+      l += __shfl_xor(l, 32);
+      const float inv = 1.0f / l;
+      const int64_t q = q0 + qt * 16 + m16;
+      if (q < n_q) {
+        TO* orow = O + (s * n_q + q) * D;
 #pragma unroll
-      for (int dt = 0; dt < D / 16; ++dt)
-        store4<TO>(orow + dt * 16 + 4 * g, acc[qt][dt][0] * inv, acc[qt][dt][1] * inv,
-                   acc[qt][dt][2] * inv, acc[qt][dt][3] * inv);
+        for (int dt = 0; dt < D / 16; ++dt)
+          store4<TO>(orow + dt * 16 + 4 * g, acc[qt][dt][0] * inv, acc[qt][dt][1] * inv,
+                     acc[qt][dt][2] * inv, acc[qt][dt][3] * inv);
+      }
     }
   }
 }
@@ -549,6 +558,7 @@ __global__ __launch_bounds__(64 * WR) void coreset_attn_res_kernel(
   }
 }
 
+constexpr int64_t kAttnWorkgroups = 1024;  // of the chunked kernel: four per CU
 // Waves per workgroup of the resident kernel; above 128 keys also 16-query
 // tiles per wave per step, passes over the keys and workgroups in all
 #ifndef ATTN_RES_WAVES
@@ -1241,12 +1251,24 @@ template <typename T, int D, typename TO>
 hipError_t launch_attn_t(const void* Q, const void* K, const void* V, const int32_t* idx,
                          const float* logw, int64_t S, int64_t n, int64_t n_q, int64_t n_out,
                          void* O, hipStream_t st) {
-  dim3 grid((unsigned)((n_q + QPB - 1) / QPB), (unsigned)S), block(64 * WAVES);
+  // Float rows: one 16-query tile per wave, whose registers let four workgroups
+  // share a CU (16 slices x 4096 queries x 64 keys, d = 64: 17.3 us with two
+  // tiles, 16.5 with one; 8 x 2048, d = 128: 17.7, 11.8).  bf16 rows: two, so
+  // that a chunk's staging, which turns V, serves twice the queries (8 x 3000
+  // x 400 keys, d = 128: 38 us, 45 with one).
+  constexpr int QT = Elem<T>::bytes == 4 ? 1 : 2;
+  constexpr int64_t per = 16 * QT * WAVES;
+  int64_t wgs = (n_q + per - 1) / per;
+  // one chunk of keys is staged once per workgroup: no more workgroups than
+  // fit the device together, each taking its share of the queries (a last,
+  // nearly empty round of workgroups cost the 16 x 4097 case 5 us)
+  if (n_out <= KC) wgs = std::min(wgs, std::max<int64_t>(1, kAttnWorkgroups / S));
+  dim3 grid((unsigned)wgs, (unsigned)S), block(64 * WAVES);
   if (logw)
-    hipLaunchKernelGGL((coreset_attn_kernel<T, D, TO, true>), grid, block, 0, st, (const T*)Q,
+    hipLaunchKernelGGL((coreset_attn_kernel<T, D, TO, true, QT>), grid, block, 0, st, (const T*)Q,
                        (const T*)K, (const T*)V, idx, logw, n, n_q, (int)n_out, (TO*)O);
   else
-    hipLaunchKernelGGL((coreset_attn_kernel<T, D, TO, false>), grid, block, 0, st, (const T*)Q,
+    hipLaunchKernelGGL((coreset_attn_kernel<T, D, TO, false, QT>), grid, block, 0, st, (const T*)Q,
                        (const T*)K, (const T*)V, idx, logw, n, n_q, (int)n_out, (TO*)O);
   return hipGetLastError();
 }

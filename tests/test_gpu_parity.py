@@ -573,3 +573,26 @@ def test_two_pass_attention_with_a_dropped_pass(n_out, dropped):
         assert np.abs(ref - O[0, h]).max() <= 2e-3, h
         ref = oracle.attention(Q[0, h], K[0, h], V[0, h], idx[0, h])
         assert np.all(np.abs(ref - Ob[0, h]) <= 2e-3 + 2.0 ** -8 * np.abs(ref)), h
+
+
+@pytest.mark.parametrize("dtype,d,n_out", [("fp32", 64, 64), ("fp32", 128, 33), ("bf16", 32, 64),
+                                           ("fp32", 32, 65)])
+def test_chunked_attention_in_several_rounds_of_queries(dtype, d, n_out):
+    """More query blocks than the launch's workgroups: with one chunk of keys a
+    workgroup stages it once and takes several blocks (the last one a query or
+    two wide); with two it stages them for every block."""
+    w = W.custom("rounds", B=1, H=64, n=300, n_q=2178, d=d, dtype=dtype, kind="gauss")
+    Q, K, V = W.make_qkv(w)
+    rng = np.random.default_rng(d + n_out)
+    idx = rng.integers(0, 300, size=(1, 64, n_out)).astype(np.int32)
+    logw = rng.standard_normal((1, 64, n_out)).astype(np.float32)
+    args = [t.to(DEV) for t in (Q, K, V, torch.from_numpy(idx))]
+    O = thin_attention(*args).cpu().numpy()
+    Ow = thin_attention(*args, logw=torch.from_numpy(logw).to(DEV)).cpu().numpy()
+    rows = np.r_[0:40, 1000:1060, 2040:2060, 2170:2178]
+    for h in (0, 31, 63):
+        ref = oracle.attention(Q[0, h][rows], K[0, h], V[0, h], idx[0, h])
+        assert np.abs(ref - O[0, h][rows]).max() <= _tol(w), h
+        ref = oracle.weighted_attention(Q[0, h][rows], K[0, h], V[0, h], idx[0, h],
+                                        logw[0, h].astype(np.float64))
+        assert np.abs(ref - Ow[0, h][rows]).max() <= _tol(w), h
