@@ -208,6 +208,15 @@ hipError_t kh_round(int32_t dtype, int64_t d, thin::HalveArgs a, int64_t buckets
     return observed(THIN_KERNEL_LOCAL, r, st,
                     [&] { return thin::launch_local(dtype, d, a, buckets, st); });
   }
+  if (a.vmax_own) {  // not a local launch: the calls' v_max first
+    const hipError_t e = observed(THIN_KERNEL_EXPRESS, -1, st, [&] {
+      return thin::launch_vmax_rows(dtype, a.V, a.ld, d, a.idx_in, a.in_stride ? a.in_stride : a.n_r,
+                                    a.N, a.G, a.S, const_cast<uint32_t*>(a.vmax_bits), st);
+    });
+    if (e != hipSuccess) return e;
+    a.vmax_own = 0;
+    a.vmax_per_bucket = 1;
+  }
   const size_t per = thin::halve_score_bytes(a.N);
   int64_t chunk = (int64_t)(e_bytes / per);
   if (chunk < 1) chunk = 1;
@@ -555,17 +564,13 @@ hipError_t ex_halve(thin_express* x, const ExRun* run, const int32_t* in, int64_
     return observed(THIN_KERNEL_UNIFORM, -1, st, [&] {
       return thin::launch_uniform_halve(x->S, N, in, run->U, x->u_slice, o, out, run->trace, st);
     });
-  uint32_t* vmax = ex_ptr<uint32_t>(x, x->L.vmax);
-  hipError_t e = observed(THIN_KERNEL_EXPRESS, -1, st, [&] {
-    return thin::launch_vmax_rows(x->dtype, run->V, x->n_max, x->d, in, N, N, 1, x->S, vmax, st);
-  });
-  if (e != hipSuccess) return e;
   thin::HalveArgs a{};
   a.K = run->K;
   a.V = run->V;
   a.n = x->n_max;
   a.ld = x->n_max;
-  a.vmax_bits = vmax;
+  a.vmax_bits = ex_ptr<uint32_t>(x, x->L.vmax);
+  a.vmax_own = 1;
   a.idx_in = in;
   a.n_r = N;
   a.N = (int32_t)N;
@@ -823,7 +828,7 @@ struct PfLayout {
   std::vector<std::vector<size_t>> region;     // [m/2][depth] node store of the calls
   std::vector<std::vector<int64_t>> rstride;   // [m/2][depth] its row stride per slice
   std::vector<size_t> enode;                   // [m/2] E after the Halve phase of level m - 2
-  size_t status, kept, keptrow, keptflag, hp, ein, vmax, absmax, lbt, h2, rowh2, mB, score, utab,
+  size_t status, kept, keptrow, keptflag, hp, ein, vmax, lbt, h2, rowh2, mB, score, utab,
       tiles, segs, c0, w0;
   size_t e_bytes, bytes;
   int64_t max_tiles, max_segs, max_utab;
@@ -879,7 +884,6 @@ PfLayout pf_layout(int64_t S, int64_t n_out, int32_t mbar, int64_t n, const Expr
     L.enode[lv + 1] = take(s4 * n_out);
   }
   L.vmax = take(s4 * gmax);
-  L.absmax = take(s4 * n);  // every row's largest |V| entry (the calls' v_max)
   L.lbt = take(s4 * pmax);
   L.h2 = take(s4 * pmax);
   L.rowh2 = take(s4 * n);
@@ -1115,19 +1119,13 @@ hipError_t pf_halve(int32_t dtype, int64_t d, int32_t halve, const PfLayout& L,
       return thin::launch_uniform_halve(S, G * N, in, U, u_slice, u_off, out, trace, st, N,
                                         u_bucket, in_stride, out_stride);
     });
-  uint32_t* vmax = reinterpret_cast<uint32_t*>(ws + L.vmax);
-  hipError_t e = observed(THIN_KERNEL_EXPRESS, -1, st, [&] {
-    return thin::launch_vmax_table(reinterpret_cast<const uint32_t*>(ws + L.absmax), L.n, in,
-                                   in_stride, N, G, S, vmax, st);
-  });
-  if (e != hipSuccess) return e;
   thin::HalveArgs a{};
   a.K = K;
   a.V = V;
   a.n = L.n;
   a.ld = L.n;
-  a.vmax_bits = vmax;
-  a.vmax_per_bucket = 1;
+  a.vmax_bits = reinterpret_cast<uint32_t*>(ws + L.vmax);
+  a.vmax_own = 1;
   a.idx_in = in;
   a.in_stride = in_stride;
   a.n_r = G * N;
@@ -1354,11 +1352,6 @@ int thin_express_prefill(int32_t dtype, int64_t B, int64_t H, int64_t n, int64_t
   auto dev = [&](size_t off) { return reinterpret_cast<int32_t*>(ws + off); };
   ok(observed(THIN_KERNEL_STATUS, -1, st,
               [&] { return thin::launch_zero_status(dev(L.status), st); }));
-  if (halve == THIN_HALVE_KH)  // the KH calls' v_max come from this table
-    ok(observed(THIN_KERNEL_EXPRESS, -1, st, [&] {
-      return thin::launch_row_absmax(dtype, V, n, d, S,
-                                     reinterpret_cast<uint32_t*>(ws + L.absmax), st);
-    }));
   int32_t* kept = dev(L.kept);
   const int64_t nk = (int64_t)h.keptrow.size();
   if (e == hipSuccess && nk > 0)

@@ -31,6 +31,11 @@ __device__ __forceinline__ float wave_max_f(float v) {
   for (int off = 32; off >= 1; off >>= 1) v = fmaxf(v, __shfl_xor(v, off));
   return v;
 }
+__device__ __forceinline__ uint32_t wave_max_u(uint32_t v) {
+#pragma unroll
+  for (int off = 32; off >= 1; off >>= 1) v = max(v, (uint32_t)__shfl_xor((int)v, off));
+  return v;
+}
 __device__ __forceinline__ double wave_max_d(double v) {
 #pragma unroll
   for (int off = 32; off >= 1; off >>= 1) v = fmax(v, __shfl_xor(v, off));
@@ -572,6 +577,31 @@ __device__ __forceinline__ double block_threshold(float lbt, float h2, float u, 
   return thr;
 }
 
+// The largest |x| of this lane's words of RT row fragments, as the float's bits
+// (magnitude bits order like magnitudes; bf16 pairs by packed 16-bit maxima).
+template <typename T, int NV, int RT>
+__device__ __forceinline__ uint32_t frag_absmax(const uint4 (&f)[RT][NV]) {
+  typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
+  uint32_t m = 0u;
+  u16x2 m2 = {0, 0};
+#pragma unroll
+  for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+    for (int v = 0; v < NV; ++v) {
+      const uint32_t w[4] = {f[rt][v].x, f[rt][v].y, f[rt][v].z, f[rt][v].w};
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        if constexpr (Elem<T>::bytes == 4) {
+          m = max(m, w[c] & 0x7fffffffu);
+        } else {
+          const uint32_t x = w[c] & 0x7fff7fffu;
+          m2 = __builtin_elementwise_max(m2, __builtin_bit_cast(u16x2, x));
+        }
+      }
+    }
+  return Elem<T>::bytes == 4 ? m : (uint32_t)max(m2[0], m2[1]) << 16;
+}
+
 // Row of a half-block's (or column tile's) 32 rows that lane m16 of 16-row
 // tile rt holds.  MFMA outputs put rows 4g..4g+3 of a tile in lane group g;
 // with this order the group holds eight consecutive rows over both tiles,
@@ -710,9 +740,9 @@ void pair_scores_kernel(HalveArgs a) {
   const T* V = reinterpret_cast<const T*>(a.V) + s * a.ld * D;
   const int32_t* rows_in = a.idx_in ? a.idx_in + s * in_stride(a) + t * (int64_t)N : nullptr;
   const int64_t row_base = t * (int64_t)N;
-  const float vmax = __uint_as_float(a.vmax_bits[a.vmax_per_bucket ? bucket : s]);
-  const float vm2f = vmax * vmax;
-  const double vm2d = (double)vmax * (double)vmax;
+  // (LOCAL: possibly the largest entry of the bucket's own rows, formed below)
+  const bool vmax_own = LOCAL && a.vmax_own;
+  float vmax = vmax_own ? 0.0f : __uint_as_float(a.vmax_bits[a.vmax_per_bucket ? bucket : s]);
   const double inv_sqrt_d = 1.0 / sqrt((double)D);
   const float c2 = (float)(kLog2e * inv_sqrt_d);
 
@@ -732,6 +762,7 @@ void pair_scores_kernel(HalveArgs a) {
   double* s_thr = reinterpret_cast<double*>((reinterpret_cast<uintptr_t>(s_h2p + P) + 7) & ~(uintptr_t)7);
   double* s_alpha = s_thr + 64 * NBW;
   uint32_t* s_mask = reinterpret_cast<uint32_t*>(s_alpha + 64 * NBW);
+  uint32_t* s_vm = s_mask + NBW;  // [W]: the waves' largest |V| entries
   // streamed chunks: ring | scale exponents of the column rows for each of
   // the group's blocks [NBW][32 ch] | column row indices
   float* s_he = reinterpret_cast<float*>(smem + SS::STAGES * SS::STAGE);
@@ -789,6 +820,21 @@ void pair_scores_kernel(HalveArgs a) {
     // earlier tiles on every iteration (stores count in vmcnt on this
     // architecture).
     __builtin_amdgcn_s_waitcnt(0x0F70);
+    if constexpr (LOCAL) {
+      if (vmax_own) {
+        const uint32_t mv = wave_max_u(frag_absmax<T>(Av));
+        if (lane == 0) s_vm[wave] = mv;
+        __syncthreads();
+        uint32_t m = 0u;
+#pragma unroll
+        for (int w = 0; w < W; ++w) m = max(m, s_vm[w]);
+        vmax = __uint_as_float(m);
+      }
+    }
+  }
+  const float vm2f = vmax * vmax;
+  const double vm2d = (double)vmax * (double)vmax;
+  if (own) {
     const int64_t pb = s * (a.n_r >> 1) + t * (int64_t)P;
     if (hb_ok) {
 #pragma unroll
@@ -1206,9 +1252,6 @@ __global__ __launch_bounds__(64 * kTinyWaves) void tiny_halve_kernel(HalveArgs a
   const T* V = reinterpret_cast<const T*>(a.V) + s * a.ld * D;
   const int32_t* rows_in = a.idx_in ? a.idx_in + s * in_stride(a) + t * (int64_t)N : nullptr;
   const int64_t row_base = t * (int64_t)N;
-  const float vmax = __uint_as_float(a.vmax_bits[a.vmax_per_bucket ? bucket : s]);
-  const float vm2f = vmax * vmax;
-  const double vm2d = (double)vmax * (double)vmax;
   const double inv_sqrt_d = 1.0 / sqrt((double)D);
   const float c2 = (float)(kLog2e * inv_sqrt_d);
 
@@ -1230,6 +1273,15 @@ __global__ __launch_bounds__(64 * kTinyWaves) void tiny_halve_kernel(HalveArgs a
     load_frag<T, D>(K, valid ? ar[rt] : 0, g, valid, Ak[rt]);
     load_frag<T, D>(V, valid ? ar[rt] : 0, g, valid, Av[rt]);
   }
+  // v_max of the slice, or of the bucket's own rows
+  float vmax;
+  if (a.vmax_own) {
+    vmax = __uint_as_float(wave_max_u(frag_absmax<T>(Av)));
+  } else {
+    vmax = __uint_as_float(a.vmax_bits[a.vmax_per_bucket ? bucket : s]);
+  }
+  const float vm2f = vmax * vmax;
+  const double vm2d = (double)vmax * (double)vmax;
   // pair terms; the block's largest row scale (rows past the bucket: 0)
   float h2c[RT];
   float mB = 0.0f;
@@ -1997,10 +2049,10 @@ hipError_t launch_local_td(const HalveArgs& a0, int64_t nbk, hipStream_t st) {
   const int64_t NT = (a0.N + 15) / 16, nb = (a0.N + 63) / 64, P = a0.N / 2;
   // ring, score tiles, pair scale exponents of the rows, half-block row scale
   // maxima, pair terms [2][P], then (8-byte aligned) the decisions' thresholds
-  // and alphas [2][BLOCKS][64] and masks
+  // and alphas [2][BLOCKS][64], masks and the waves' |V| maxima
   const size_t lds = (size_t)SS::OWN_RING + (size_t)panel_tiles(nb, NT, 4) * kETileLds * 4 +
                      SS::GT * 16 * 4 + 2 * SS::BLOCKS * 4 + 2 * P * 4 + 8 +
-                     2 * 64 * SS::BLOCKS * 8 + SS::BLOCKS * 4;
+                     2 * 64 * SS::BLOCKS * 8 + SS::BLOCKS * 4 + WO * 4;
   if (lds > 64 * 1024) {
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
