@@ -289,9 +289,13 @@ int compress_impl(const void* K, const void* V, int32_t dtype, int64_t B, int64_
   };
   if (trace)
     ok(observed(THIN_KERNEL_TRACE_CLEAR, -1, st, [&] { return thin::launch_zero_u8(trace, Utot, st); }));
+  // with a subsample, its launch clears what the v_max launch needs cleared
+  const bool kh = lv.L > 0 && halve == THIN_HALVE_KH;
   if (lv.sub)
     ok(observed(THIN_KERNEL_SUBSAMPLE, -1, st, [&] {
-      return thin::launch_subsample(S, nm, lv.n_kept, uniforms, lv.U, ws.buf_a, st);
+      return thin::launch_subsample(S, nm, lv.n_kept, uniforms, lv.U, ws.buf_a, st,
+                                    kh ? ws.vmax_bits : nullptr,
+                                    kh ? std::max(ws.zero_words, S) : 0, kh ? ws.status : nullptr);
     }));
   const int32_t* cur = lv.sub ? ws.buf_a : nullptr;
   // the status word is cleared by the v_max launch of the KH path; calls
@@ -324,7 +328,8 @@ int compress_impl(const void* K, const void* V, int32_t dtype, int64_t B, int64_
     }
   } else {
     ok(observed(THIN_KERNEL_VMAX, -1, st, [&] {
-      return thin::launch_vmax(dtype, Vm, S, nm, n, d, ws.vmax_bits, st, ws.status, ws.zero_words);
+      return thin::launch_vmax(dtype, Vm, S, nm, n, d, ws.vmax_bits, st, ws.status, ws.zero_words,
+                               lv.sub);
     }));
     int64_t u_off = lv.sub ? lv.n_kept : 0;
     for (int32_t r = 0; r < lv.L && e == hipSuccess; ++r) {

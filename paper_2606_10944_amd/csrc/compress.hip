@@ -112,10 +112,16 @@ __global__ void zero_u8_kernel(uint8_t* p, int64_t count) {
 // stratum t = [floor(t n / n_kept), floor((t+1) n / n_kept)), pick
 // start + floor(u len) computed in integers from k = floor(u 2^24).
 // ---------------------------------------------------------------------------
+// Also clears zero[0..zero_words) and *also (nullable): what the v_max launch
+// after it would else need a launch of its own for.
 __global__ void subsample_kernel(int64_t n, int64_t n_kept, const float* U, int64_t u_slice,
-                                 int32_t* idx0) {
+                                 int32_t* idx0, uint32_t* zero, int64_t zero_words,
+                                 int32_t* also) {
   const int64_t s = blockIdx.y;
   const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const int64_t threads = (int64_t)gridDim.x * blockDim.x;
+  for (int64_t i = s * threads + t; i < zero_words; i += gridDim.y * threads) zero[i] = 0u;
+  if (also && s == 0 && t == 0) *also = 0;
   if (t >= n_kept) return;
   const int64_t start = (t * n) / n_kept;
   const int64_t len = ((t + 1) * n) / n_kept - start;
@@ -2222,12 +2228,15 @@ hipError_t launch_decide(const HalveArgs& a0, int64_t nbk, hipStream_t st) {
 }
 
 hipError_t launch_vmax(int dtype, const void* V, int64_t S, int64_t n, int64_t ld, int64_t d,
-                       uint32_t* vmax_bits, hipStream_t st, int32_t* status, int64_t zero_words) {
-  const int64_t zw = zero_words > S ? zero_words : S;
-  hipLaunchKernelGGL(zero_u32_kernel, dim3((unsigned)((zw + 255) / 256)), dim3(256), 0, st,
-                     vmax_bits, zw, status);
+                       uint32_t* vmax_bits, hipStream_t st, int32_t* status, int64_t zero_words,
+                       bool cleared) {
   const int64_t bytes = dtype == 0 ? 4 : 2;
   const int64_t words = n * d * bytes / 16, slice_words = ld * d * bytes / 16;
+  if (!cleared) {
+    const int64_t zw = zero_words > S ? zero_words : S;
+    hipLaunchKernelGGL(zero_u32_kernel, dim3((unsigned)((zw + 255) / 256)), dim3(256), 0, st,
+                       vmax_bits, zw, status);
+  }
   // 256 KiB of V per workgroup, less for small inputs so that the scan has
   // about 1024 workgroups (one workgroup reads ~40 GB/s; 64 of them made the
   // ViT-like workload's scan take 13 us), in whole turns of the 8-load loop
@@ -2247,9 +2256,11 @@ hipError_t launch_vmax(int dtype, const void* V, int64_t S, int64_t n, int64_t l
 }
 
 hipError_t launch_subsample(int64_t S, int64_t n, int64_t n_kept, const float* U,
-                            int64_t u_slice, int32_t* idx0, hipStream_t st) {
+                            int64_t u_slice, int32_t* idx0, hipStream_t st, uint32_t* zero,
+                            int64_t zero_words, int32_t* also) {
   dim3 grid((unsigned)((n_kept + 255) / 256), (unsigned)S);
-  hipLaunchKernelGGL(subsample_kernel, grid, dim3(256), 0, st, n, n_kept, U, u_slice, idx0);
+  hipLaunchKernelGGL(subsample_kernel, grid, dim3(256), 0, st, n, n_kept, U, u_slice, idx0, zero,
+                     zero_words, also);
   return hipGetLastError();
 }
 

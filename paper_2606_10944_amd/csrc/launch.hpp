@@ -74,13 +74,16 @@ int compress_fixed(const void* K, const void* V, int32_t dtype, int64_t B, int64
 // dtype: 0 = fp32, 1 = bf16.  Returns a hipError_t.
 // v_max of n rows per slice, slices ld rows apart.
 // status (nullable) is cleared by the same launch, and max(S, zero_words)
-// words from vmax_bits on (the decision helpers' flags follow the bits).
+// words from vmax_bits on (the decision helpers' flags follow the bits), unless
+// an earlier launch has cleared them (cleared).
 hipError_t launch_vmax(int dtype, const void* V, int64_t S, int64_t n, int64_t ld, int64_t d,
                        uint32_t* vmax_bits, hipStream_t st, int32_t* status = nullptr,
-                       int64_t zero_words = 0);
+                       int64_t zero_words = 0, bool cleared = false);
 hipError_t launch_zero_status(int32_t* status, hipStream_t st);
 hipError_t launch_subsample(int64_t S, int64_t n, int64_t n_kept, const float* U,
-                            int64_t u_slice, int32_t* idx0, hipStream_t st);
+                            int64_t u_slice, int32_t* idx0, hipStream_t st,
+                            uint32_t* zero = nullptr, int64_t zero_words = 0,
+                            int32_t* also = nullptr);
 hipError_t launch_fill_rows(int64_t S, int64_t n_out, const int32_t* src, int64_t src_stride,
                             int32_t* dst, hipStream_t st);
 hipError_t launch_zero_u8(uint8_t* p, int64_t count, hipStream_t st);
