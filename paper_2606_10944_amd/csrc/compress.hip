@@ -753,10 +753,11 @@ void pair_scores_kernel(HalveArgs a) {
   const float c2 = (float)(kLog2e * inv_sqrt_d);
 
   extern __shared__ __align__(16) unsigned char smem[];
-  // own chunks: ring | (LOCAL) every score tile of the bucket | pair scales of
+  // own chunks: ring (LOCAL with stage_all: every row tile) | (LOCAL) every score tile of the bucket | pair scales of
   // the group's rows [GT * 16] | half-blocks' largest row scales | (LOCAL)
   // pair terms and the decisions' state
-  float* s_e = reinterpret_cast<float*>(smem + SS::OWN_RING);
+  const bool stage_all = LOCAL && a.stage_all;
+  float* s_e = reinterpret_cast<float*>(smem + (stage_all ? 2 * NC * CH * 1024 : SS::OWN_RING));
   float* s_h2 = s_e + (LOCAL ? (int)panel_tiles(nb, NT, 4) : 0) * kETileLds;
   float* s_mh = own ? s_h2 + GT * 16
                     : reinterpret_cast<float*>(smem + SS::STAGES * SS::STAGE) +
@@ -775,9 +776,18 @@ void pair_scores_kernel(HalveArgs a) {
   int32_t* s_row = reinterpret_cast<int32_t*>(s_he + 32 * a.ch * NBW);
 
   // ---- this wave's half-block: rows, fragments and, in chunk 0, pair terms ----
-  const int lblk = wave >> 1, half = wave & 1;
+  // With stage_all and at most half the blocks, parts waves share a
+  // half-block and take every parts-th of its column tiles; the later parts go
+  // through the half-blocks in reverse, so that a SIMD (waves w and w + 4)
+  // gets a long and a short one.
+  const int nhb = 2 * nb;
+  const int parts = stage_all && nhb <= W / 2 ? W / nhb : 1;
+  const int pass = parts > 1 ? wave / nhb : 0;
+  const int hbw = parts > 1 ? (pass & 1 ? nhb - 1 - wave % nhb : wave % nhb) : wave;  // local half-block
+  const int part = pass;
+  const int lblk = hbw >> 1, half = hbw & 1;
   const int blk = grp * NBW + lblk;
-  const bool hb_ok = blk < nb;
+  const bool hb_ok = blk < nb && part < parts;
   const bool odd = (m16 & 1) != 0;
   // Streamed chunk: column row o of the chunk in fragment order (tile o / 32,
   // 16-row half o / 16 & 1, lane o % 16); this thread's are o = threadIdx.x +
@@ -842,14 +852,14 @@ void pair_scores_kernel(HalveArgs a) {
   const double vm2d = (double)vmax * (double)vmax;
   if (own) {
     const int64_t pb = s * (a.n_r >> 1) + t * (int64_t)P;
-    if (hb_ok) {
+    if (hb_ok && part == 0) {
 #pragma unroll
       for (int rt = 0; rt < 2; ++rt) {
         float rh2, h2f, lbt;
         frag_pair_terms<T, D>(Ak[rt], Av[rt], vm2d, inv_sqrt_d, rh2, h2f, lbt);
         arh[rt] = ar[rt] >= 0 ? rh2 : 0.0f;
         const int j = blk * 64 + half * 32 + frag_row(rt, m16);
-        if (g == 0) s_h2[(2 * wave + rt) * 16 + m16] = j < N ? h2f : 0.0f;
+        if (g == 0) s_h2[(2 * hbw + rt) * 16 + m16] = j < N ? h2f : 0.0f;
         if (g == 0 && j < N && (j & 1) == 0) {
           if (LOCAL) {
             s_h2p[j >> 1] = h2f;
@@ -872,7 +882,7 @@ void pair_scores_kernel(HalveArgs a) {
   // the largest row scale of each half-block (rows past the bucket: 0, and
   // every row scale is >= 0), published in LDS before the tile loop's first
   // barrier
-  {
+  if (part == 0) {
     const float mh = wave_max_f(fmaxf(arh[0], arh[1]));
     if (lane == 0) s_mh[2 * lblk + half] = mh;
   }
@@ -968,9 +978,28 @@ void pair_scores_kernel(HalveArgs a) {
     if (!LOCAL && (int)threadIdx.x < NBW && grp * NBW + (int)threadIdx.x < nb)
       a.mB[bucket * nb + grp * NBW + threadIdx.x] =
           fmaxf(s_mh[2 * threadIdx.x], s_mh[2 * threadIdx.x + 1]);
-    // 16-row tile i (of wave i / 2's fragments) into stage i mod 3
+    // E of column tile jc (group-local tt) from its two halves' F
+    auto put = [&](int tt, const float* fa, const float* fb) {
+      const float4 e = score_e(fa, fb, odd);
+      if constexpr (LOCAL) {
+        if (in_panel(jc0 + tt)) {
+          float* col = s_e + (panel_tiles(blk, NT, 4) + 2 * (jc0 + tt) + (q >> 3) - 4 * blk) * kETileLds +
+                       (q & 7) * kETileStride;
+          *reinterpret_cast<float4*>(col + 16 * half + 4 * g) = e;
+        }
+      } else if (in_panel(jc0 + tt)) {
+        *e_tile(jc0 + tt) = e;
+      }
+    };
+    // F against 16-row tile i, staged at st
+    auto form = [&](int i, const unsigned char* st, float* f) {
+      const float h2 = s_h2[i * 16 + m16];
+      score_f<T, NV>(Ak, Av, st, lane, vm2f, c2, h2 + scale_shift(mB, h2), f);
+    };
+    // 16-row tile i (of the fragments of the wave holding half-block i / 2)
+    // into a stage
     auto commit = [&](int i, int stage) {
-      if (wave == (i >> 1)) {
+      if (hbw == (i >> 1) && part == 0) {
         unsigned char* st = smem + stage * CH * 1024;
 #pragma unroll
         for (int v = 0; v < NV; ++v) {
@@ -979,50 +1008,56 @@ void pair_scores_kernel(HalveArgs a) {
         }
       }
     };
-    commit(0, 0);
-    commit(1, 1);
-    __syncthreads();
     // a half-block takes part from its block's diagonal on
-    const int first = hb_ok ? 4 * lblk : GT;
-    float f0[4];
-    // step i = 2 t + u (16-row tile u of column tile jc0 + t, stage st); tile
-    // i + 2 is staged meanwhile
-    auto step = [&](int tt, int u, int st) {
-      const int i = 2 * tt + u;
-      if (i + 2 < 2 * ntile) commit(i + 2, (st + 2) % 3);
-      if (i >= first) {
-        const float h2 = s_h2[i * 16 + m16];
-        const float he = h2 + scale_shift(mB, h2);
-        float f[4];
-        score_f<T, NV>(Ak, Av, smem + st * CH * 1024, lane, vm2f, c2, he, f);
-        if (u == 0) {
+    const int first = hb_ok ? 2 * lblk : GT;
+    if (stage_all) {
+      if constexpr (LOCAL) {
+        if (hbw < ntile) {  // (a half-block past the bucket has no tile)
+          commit(2 * hbw, 2 * hbw);
+          commit(2 * hbw + 1, 2 * hbw + 1);
+        }
+        __syncthreads();
+        for (int tt = first + part; tt < ntile; tt += parts) {
+          float fa[4], fb[4];
+          form(2 * tt, smem + 2 * tt * CH * 1024, fa);
+          form(2 * tt + 1, smem + (2 * tt + 1) * CH * 1024, fb);
+          put(tt, fa, fb);
+        }
+        __syncthreads();
+      }
+    } else {
+      commit(0, 0);
+      commit(1, 1);
+      __syncthreads();
+      float f0[4];
+      // step i = 2 t + u (16-row tile u of column tile jc0 + t, stage st); tile
+      // i + 2 is staged meanwhile
+      auto step = [&](int tt, int u, int st) {
+        const int i = 2 * tt + u;
+        if (i + 2 < 2 * ntile) commit(i + 2, (st + 2) % 3);
+        if (tt >= first) {
+          float f[4];
+          form(i, smem + st * CH * 1024, f);
+          if (u == 0) {
 #pragma unroll
-          for (int k = 0; k < 4; ++k) f0[k] = f[k];
-        } else {
-          const float4 e = score_e(f0, f, odd);
-          if constexpr (LOCAL) {
-            if (in_panel(jc0 + tt)) {
-              float* col = s_e + (panel_tiles(blk, NT, 4) + 2 * (jc0 + tt) + (q >> 3) - 4 * blk) * kETileLds +
-                           (q & 7) * kETileStride;
-              *reinterpret_cast<float4*>(col + 16 * half + 4 * g) = e;
-            }
-          } else if (in_panel(jc0 + tt)) {
-            *e_tile(jc0 + tt) = e;
+            for (int k = 0; k < 4; ++k) f0[k] = f[k];
+          } else {
+            put(tt, f0, f);
           }
         }
-      }
-      __syncthreads();
-    };
-    for (int t3 = 0; t3 < ntile; t3 += 3) {  // six steps: stages 0 1 2 0 1 2
-      step(t3, 0, 0);
-      step(t3, 1, 1);
-      if (t3 + 1 < ntile) {  // uniform over the workgroup
-        step(t3 + 1, 0, 2);
-        step(t3 + 1, 1, 0);
-      }
-      if (t3 + 2 < ntile) {
-        step(t3 + 2, 0, 1);
-        step(t3 + 2, 1, 2);
+        __syncthreads();
+      };
+      for (int t3 = 0; t3 < ntile; t3 += 3) {  // six steps: stages 0 1 2 0 1 2
+        step(t3, 0, 0);
+        step(t3, 1, 1);
+        if (t3 + 1 < ntile) {  // uniform over the workgroup
+          step(t3 + 1, 0, 2);
+          step(t3 + 1, 1, 0);
+        }
+        if (t3 + 2 < ntile) {
+          step(t3 + 2, 0, 1);
+          step(t3 + 2, 1, 2);
+        }
       }
     }
     if constexpr (LOCAL) local_decisions();
@@ -2056,9 +2091,17 @@ hipError_t launch_local_td(const HalveArgs& a0, int64_t nbk, hipStream_t st) {
   // ring, score tiles, pair scale exponents of the rows, half-block row scale
   // maxima, pair terms [2][P], then (8-byte aligned) the decisions' thresholds
   // and alphas [2][BLOCKS][64], masks and the waves' |V| maxima
-  const size_t lds = (size_t)SS::OWN_RING + (size_t)panel_tiles(nb, NT, 4) * kETileLds * 4 +
-                     SS::GT * 16 * 4 + 2 * SS::BLOCKS * 4 + 2 * P * 4 + 8 +
-                     2 * 64 * SS::BLOCKS * 8 + SS::BLOCKS * 4 + WO * 4;
+  const size_t rest = (size_t)panel_tiles(nb, NT, 4) * kETileLds * 4 + SS::GT * 16 * 4 +
+                      2 * SS::BLOCKS * 4 + 2 * P * 4 + 8 + 2 * 64 * SS::BLOCKS * 8 +
+                      SS::BLOCKS * 4 + WO * 4;
+  // Every row tile staged at once (no barrier per tile, and buckets of at most
+  // half the blocks spread a half-block's tiles over several waves) where that
+  // costs no resident workgroup: launches of at most one per CU, or LDS for two
+  // per CU all the same.  1 to 32 buckets of 128 rows (float, d = 64) 20.3 ->
+  // 18.1 us, of 256 rows (bf16, d = 64) 19.1 -> 17.5 us, 64 rows 13.2 -> 12.3.
+  const size_t all = (size_t)((a0.N + 31) / 32) * 2 * SS::CHUNKS * 1024 + rest;
+  const bool stage_all = all <= 80 * 1024 || (nbk <= 256 && all <= 160 * 1024);
+  const size_t lds = stage_all ? all : SS::OWN_RING + rest;
   if (lds > 64 * 1024) {
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
@@ -2066,6 +2109,7 @@ hipError_t launch_local_td(const HalveArgs& a0, int64_t nbk, hipStream_t st) {
   }
   HalveArgs a = a0;
   a.ch = kScoreChunk;
+  a.stage_all = stage_all;
   a.e_tiles = 0;
   hipLaunchKernelGGL(kern, dim3((unsigned)nbk), dim3(64 * WO), lds, st, a);
   return hipGetLastError();
