@@ -419,7 +419,8 @@ int thin_workspace_status(const void* workspace, int32_t* status, void* stream);
  * when a slice keeps at most 32768 rows, else one launch per round).  A round
  * runs either as SCORES + DECIDE launches or, when its buckets are small
  * enough for one workgroup to hold all their scores in LDS, as one LOCAL
- * launch.  The setting belongs to the calling thread (thread-local): only
+ * launch (float rounds of few buckets of 129 to 256 rows take the former
+ * where the workspace has room for their scores).  The setting belongs to the calling thread (thread-local): only
  * launches made by that thread are observed, and calls on other threads are
  * unaffected.  hook = NULL turns it off (the default).  Returns THIN_OK.
  */

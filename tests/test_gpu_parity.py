@@ -596,3 +596,25 @@ def test_chunked_attention_in_several_rounds_of_queries(dtype, d, n_out):
         ref = oracle.weighted_attention(Q[0, h][rows], K[0, h], V[0, h], idx[0, h],
                                         logw[0, h].astype(np.float64))
         assert np.abs(ref - Ow[0, h][rows]).max() <= _tol(w), h
+
+
+def test_compress_without_room_for_spread_rounds():
+    """A float round of few 256-row buckets runs as scores and decisions where
+    the workspace has room for its scores (40 KiB per bucket, the plan's size
+    includes it) and as one local launch where it has not: same rows."""
+    w = W.WORKLOADS["tiny"]
+    Q, K, V = W.make_qkv(w)
+    plan = thin_plan(w.B, w.H, w.n, w.d, w.n_out, w.g)
+    U = W.make_uniforms(w, plan["uniforms_total"]).to(DEV)
+    Kd, Vd = K.to(DEV), V.to(DEV)
+    got = []
+    for size in (plan["workspace_bytes"], plan["workspace_bytes"] - 40 * 1024):
+        ws = torch.empty(size, dtype=torch.uint8, device=DEV)
+        stream = torch.cuda.current_stream()
+        with LaunchTimer(stream) as lt:
+            idx = thin_compress(Kd, Vd, w.n_out, w.g, U, workspace=ws, stream=stream)
+            torch.cuda.synchronize()
+        assert workspace_status(ws) == 0
+        got.append((idx.cpu(), ("scores", 2) in [(k, r) for k, r, _ in lt.records()]))
+    assert torch.equal(got[0][0], got[1][0])
+    assert got[0][1] and not got[1][1]
