@@ -910,7 +910,7 @@ __global__ __launch_bounds__(64 * PF_WAVES) __attribute__((amdgpu_waves_per_eu(4
 // reads (2048 cycles of the CU's LDS per workgroup and chunk, about what the
 // matrix cores and the vector ALU each need).  Against the kernel above with
 // V turned in registers and nothing in flight during a chunk: 65536 points x
-// 32 slices, d = 128: 3660 -> 2270 us.
+// 32 slices, d = 128: 3660 -> 2270 us (2054 with the order of tiles below).
 // ---------------------------------------------------------------------------
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ uint2 read_tr16(uint32_t lds) {
@@ -935,9 +935,9 @@ struct PfLds {
 template <int D, typename TO>
 __global__ __launch_bounds__(64 * PF_WAVES) __attribute__((amdgpu_waves_per_eu(4))) void prefill_attn_bf16_kernel(
     const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, const bf16_t* __restrict__ V,
-    int64_t n, const PrefillTile* __restrict__ tiles, const PrefillSeg* __restrict__ segs,
-    const int32_t* __restrict__ c0s, const float* __restrict__ w0s,
-    const uint8_t* __restrict__ kept, TO* __restrict__ O) {
+    int64_t n, int32_t ntiles, int64_t work, const PrefillTile* __restrict__ tiles,
+    const PrefillSeg* __restrict__ segs, const int32_t* __restrict__ c0s,
+    const float* __restrict__ w0s, const uint8_t* __restrict__ kept, TO* __restrict__ O) {
   using L = PfLds<D>;
   constexpr int NV = L::NV;
   // [2][K chunk, V chunk], aligned so that address bits can be permuted by XOR
@@ -969,8 +969,14 @@ __global__ __launch_bounds__(64 * PF_WAVES) __attribute__((amdgpu_waves_per_eu(4
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int m16 = lane & 15, g = lane >> 4;
-  const int64_t s = blockIdx.y;
-  const PrefillTile tile = tiles[blockIdx.x];
+  // Workgroups are dealt to the eight XCDs in turn; each XCD takes a contiguous
+  // eighth of the tiles, slice after slice, so that the cache pieces a slice's
+  // tiles share stay in one L2 (65536 points x 32 slices 2318 -> 2054 us).
+  const int64_t per = (work + 7) >> 3;
+  const int64_t at = (int64_t)(blockIdx.x & 7) * per + (blockIdx.x >> 3);
+  if (at >= min(work, ((int64_t)(blockIdx.x & 7) + 1) * per)) return;
+  const int64_t s = at / ntiles;
+  const PrefillTile tile = tiles[at - s * ntiles];
   const int32_t q0 = tile.q0, q1 = tile.q1;
   const int nseg = min(tile.nseg, kPrefillMaxSegs);
   const bf16_t* Ks = K + s * n * D;
@@ -1225,8 +1231,11 @@ hipError_t launch_prefill_t(const void* Q, const void* K, const void* V, int64_t
                                          hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
       if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL(kern, grid, block, lds, st, (const bf16_t*)Q, (const bf16_t*)K,
-                       (const bf16_t*)V, n, tiles, segs, c0, w0, kept, (TO*)O);
+    const int64_t work = ntiles * S;
+    if (work > ((int64_t)1 << 30)) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(kern, dim3((unsigned)((work + 7) / 8 * 8)), block, lds, st,
+                       (const bf16_t*)Q, (const bf16_t*)K, (const bf16_t*)V, n, (int32_t)ntiles,
+                       work, tiles, segs, c0, w0, kept, (TO*)O);
   } else {
     hipLaunchKernelGGL((prefill_attn_kernel<T, D, TO>), grid, block, 0, st, (const T*)Q,
                        (const T*)K, (const T*)V, n, tiles, segs, c0, w0, kept, (TO*)O);
