@@ -446,10 +446,10 @@ __host__ __device__ inline int half_run(int u, int NT) { return 2 * u + 1 < NT ?
 // group in one of the bucket's stretches of ch tiles of 32 rows (kScoreChunk,
 // more in launches of many workgroups, fewer in launches of few), copied from
 // global memory straight into LDS.
-//   What bounds it: in the tile loop the vector ALU (about 75 instructions and
-// 16 exponentials per wave and 32-row tile) and the matrix cores (32 MFMAs)
-// are both about 80 % busy (2700 cycles per tile for the four waves of a SIMD,
-// 65536 rows x 32 slices); a workgroup's row loads before the loop take about
+//   What bounds it: a 32-row tile takes the four waves of a SIMD 2700 cycles
+// (s_memtime; 65536 rows x 32 slices), of which their 32 MFMAs each need 2048
+// and their vector instructions (about 75 and 16 exponentials each) about
+// 2200; a workgroup's row loads before the loop take about
 // a quarter of its time.  Tiles of 32 columns with one barrier each, copied
 // straight to LDS, and scores stored from the registers, against tiles of 16
 // columns staged through registers with the scores turned in LDS: score
