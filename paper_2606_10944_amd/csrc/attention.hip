@@ -430,16 +430,17 @@ __global__ __launch_bounds__(64 * WR) void coreset_attn_res_kernel(
         mx = fmaxf(mx, __shfl_xor(mx, 16));
         mx = fmaxf(mx, __shfl_xor(mx, 32));
         if (h > 0) {
-          // (no key of finite weight so far: nothing to rescale)
-          const float scale = W && mrun[qt] == -INFINITY
+          // (no finite score so far: nothing to rescale)
+          const float scale = mrun[qt] == -INFINITY
                                   ? 0.f : __builtin_amdgcn_exp2f((mrun[qt] - mx) * c2);
           l[qt] *= scale;
 #pragma unroll
           for (int dt = 0; dt < D / 16; ++dt) acc[qt][dt] *= scale;
         }
         mrun[qt] = mx;
-        // a pass whose keys are all dropped leaves zeros, not NaN
-        const float mref = W && H > 1 && mx == -INFINITY ? 0.f : mx;
+        // a pass whose scores are all -inf (keys of weight zero, or products
+        // past float32's range) leaves zeros, not NaN
+        const float mref = H > 1 && mx == -INFINITY ? 0.f : mx;
 #pragma unroll
         for (int kt = 0; kt < KT; ++kt)
 #pragma unroll

@@ -575,6 +575,34 @@ def test_two_pass_attention_with_a_dropped_pass(n_out, dropped):
         assert np.all(np.abs(ref - Ob[0, h]) <= 2e-3 + 2.0 ** -8 * np.abs(ref)), h
 
 
+@pytest.mark.parametrize("n_q", [40, 40000])
+@pytest.mark.parametrize("n_out", [160, 256])
+@pytest.mark.parametrize("low", ["first", "last"])
+def test_attention_with_half_of_the_scores_at_minus_infinity(low, n_out, n_q):
+    """Raw scores past float32's range (query and key entries of 1e20 with
+    opposite signs) are -inf and weigh nothing, also where they fill one of the
+    two passes over more than 128 keys."""
+    w = W.custom("low", B=1, H=1, n=600, n_q=n_q, d=128, dtype="bf16", kind="gauss")
+    Q, K, V = W.make_qkv(w)
+    half = 96 if n_out <= 192 else 128
+    rows = np.random.default_rng(n_out).permutation(600)[:n_out].astype(np.int32)
+    lows = rows[:half] if low == "first" else rows[half:]
+    Q[..., 0] = 1e20
+    K[..., 0] = 0.0
+    K[0, 0, torch.from_numpy(lows).long(), 0] = -1e20
+    idx = rows.reshape(1, 1, n_out)
+    logw = np.random.default_rng(3).standard_normal((1, 1, n_out)).astype(np.float32)
+    args = [t.to(DEV) for t in (Q, K, V, torch.from_numpy(idx))]
+    O = thin_attention(*args).cpu().numpy()
+    Ow = thin_attention(*args, logw=torch.from_numpy(logw).to(DEV)).cpu().numpy()
+    r = np.unique(np.r_[0:40, n_q - 40:n_q])
+    ref = oracle.attention(Q[0, 0][r], K[0, 0], V[0, 0], idx[0, 0])
+    assert np.abs(ref - O[0, 0][r]).max() <= _tol(w)
+    ref = oracle.weighted_attention(Q[0, 0][r], K[0, 0], V[0, 0], idx[0, 0],
+                                    logw[0, 0].astype(np.float64))
+    assert np.abs(ref - Ow[0, 0][r]).max() <= _tol(w)
+
+
 @pytest.mark.parametrize("dtype,d,n_out", [("fp32", 64, 64), ("fp32", 128, 33), ("bf16", 32, 64),
                                            ("fp32", 32, 65)])
 def test_chunked_attention_in_several_rounds_of_queries(dtype, d, n_out):
