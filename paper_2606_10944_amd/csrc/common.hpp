@@ -166,8 +166,12 @@ __device__ __forceinline__ floatx4_t mma_aug<float>(const uint4& a, const uint4&
 
 // 64 lanes x 16 bytes from global memory straight into LDS: lane l's 16 bytes
 // at g go to LDS byte lds + 16 l (lds uniform over the wave).  Counted in
-// vmcnt, which the caller waits on: the compiler does not see the copy.  (m0
-// holds the LDS address; nothing else in the kernels that call this uses it.)
+// vmcnt, which the caller waits on: the compiler does not see the copy, only
+// that m0 (the LDS address) changes.  (It warns that m0 is a reserved register,
+// i.e. that it will not save m0 around the statement; it does set m0 anew for
+// its own next use, which is all that is needed.)
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
 __device__ __forceinline__ void copy16_to_lds(const void* g, uint32_t lds) {
   asm volatile(
       "s_mov_b32 m0, %0\n\t"
@@ -175,8 +179,9 @@ __device__ __forceinline__ void copy16_to_lds(const void* g, uint32_t lds) {
       "global_load_lds_dwordx4 %1, off"
       :
       : "s"(lds), "v"(g)
-      : "memory");
+      : "memory", "m0");
 }
+#pragma clang diagnostic pop
 __device__ __forceinline__ uint32_t lds_offset(const void* p) {
   return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void*)p;
 }
