@@ -16,6 +16,7 @@
 
 #include <algorithm>
 
+#include "attn_plan.hpp"
 #include "common.hpp"
 #include "launch.hpp"
 
@@ -84,10 +85,11 @@ __global__ __launch_bounds__(64 * WAVES) void coreset_attn_kernel(
   const float c2 = (float)(kLog2e / sqrt((double)D));
 
   constexpr int WPR = D * Elem<T>::bytes / 16;  // 16-byte words per row
-  // The workgroup's blocks of queries, gridDim.x apart; a coreset of one chunk
-  // is staged for the first of them and stays.
+  // The workgroup's blocks of queries, as many apart as there are workgroups; a
+  // coreset of one chunk is staged for the first of them and stays.
   const int64_t nqb = (n_q + 16 * QT * WAVES - 1) / (16 * QT * WAVES);
-  for (int64_t qb = blockIdx.x; qb < nqb; qb += gridDim.x) {
+  const int64_t first = blockIdx.x + (int64_t)gridDim.x * blockIdx.z;
+  for (int64_t qb = first; qb < nqb; qb += (int64_t)gridDim.x * gridDim.z) {
     const int64_t q0 = qb * (16 * QT * WAVES) + wave * 16 * QT;
     uint4 Bq[QT][NV];
 #pragma unroll
@@ -108,7 +110,7 @@ __global__ __launch_bounds__(64 * WAVES) void coreset_attn_kernel(
 
     for (int c0 = 0; c0 < n_out; c0 += KC) {
       const int kc = min(KC, n_out - c0);
-      if (n_out > KC || qb == (int64_t)blockIdx.x) {
+      if (n_out > KC || qb == first) {
         __syncthreads();
         if (W && threadIdx.x < KC)
           sB[threadIdx.x] = (int)threadIdx.x < kc ? Ws[c0 + threadIdx.x] * sqrt_d : -INFINITY;
@@ -974,7 +976,8 @@ __global__ __launch_bounds__(64 * PF_WAVES) __attribute__((amdgpu_waves_per_eu(4
   // eighth of the tiles, slice after slice, so that the cache pieces a slice's
   // tiles share stay in one L2 (65536 points x 32 slices 2318 -> 2054 us).
   const int64_t per = (work + 7) >> 3;
-  const int64_t at = (int64_t)(blockIdx.x & 7) * per + (blockIdx.x >> 3);
+  const int64_t at = (int64_t)(blockIdx.x & 7) * per + (blockIdx.x >> 3) +
+                     (int64_t)(gridDim.x >> 3) * blockIdx.y;
   if (at >= min(work, ((int64_t)(blockIdx.x & 7) + 1) * per)) return;
   const int64_t s = at / ntiles;
   const PrefillTile tile = tiles[at - s * ntiles];
@@ -1233,8 +1236,8 @@ hipError_t launch_prefill_t(const void* Q, const void* K, const void* V, int64_t
       if (e != hipSuccess) return e;
     }
     const int64_t work = ntiles * S;
-    if (work > ((int64_t)1 << 30)) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(kern, dim3((unsigned)((work + 7) / 8 * 8)), block, lds, st,
+    const GridRows g = grid_rows((work + 7) / 8 * 8, 64 * PF_WAVES, 8);
+    hipLaunchKernelGGL(kern, dim3((unsigned)g.x, (unsigned)g.rows), block, lds, st,
                        (const bf16_t*)Q, (const bf16_t*)K, (const bf16_t*)V, n, (int32_t)ntiles,
                        work, tiles, segs, c0, w0, kept, (TO*)O);
   } else {
@@ -1273,7 +1276,8 @@ hipError_t launch_attn_t(const void* Q, const void* K, const void* V, const int3
   // fit the device together, each taking its share of the queries (a last,
   // nearly empty round of workgroups cost the 16 x 4097 case 5 us)
   if (n_out <= KC) wgs = std::min(wgs, std::max<int64_t>(1, kAttnWorkgroups / S));
-  dim3 grid((unsigned)wgs, (unsigned)S), block(64 * WAVES);
+  const GridRows g = grid_rows(wgs, 64 * WAVES);
+  dim3 grid((unsigned)g.x, (unsigned)S, (unsigned)g.rows), block(64 * WAVES);
   if (logw)
     hipLaunchKernelGGL((coreset_attn_kernel<T, D, TO, true, QT>), grid, block, 0, st, (const T*)Q,
                        (const T*)K, (const T*)V, idx, logw, n, n_q, (int)n_out, (TO*)O);
