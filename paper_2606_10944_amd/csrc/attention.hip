@@ -267,11 +267,12 @@ __device__ __align__(16) float g_attn_sink[256];
 // keys) needs no running maximum and is bound by HBM.  Above 128 keys the
 // coreset takes over 100 KB of LDS, one workgroup per CU, and a wave's reads of
 // it (512 bytes per key, K and V, for every query tile) keep the CU's LDS as
-// busy as the matrix cores: there a wave takes two query tiles (QTR = 2), each
-// fragment serving both, which only fits the registers with the scores of half
-// of the keys at a time (H = 2, online softmax).  256 keys, d = 128, 32 x 65536
-// queries, bf16 output: 521 us with one tile, one pass and 512 workgroups, 463 us
-// so, 440 us with the biases and masks as the score MFMAs' initial value
+// busy as the matrix cores: a wave with two query tiles (QTR = 2), each
+// fragment serving both, only fits the registers with the scores of half of
+// the keys at a time (H = 2, online softmax).  Launches that would leave the
+// device short of such workgroups keep one tile and one pass (attn_tile_plan).
+// 256 keys, d = 128, 32 x 65536 queries, bf16 output: 521 us with one tile, one
+// pass and 512 workgroups, 463 us with two, 440 us with the biases and masks as the score MFMAs' initial value
 // instead of two vector instructions per score; 192 weighted keys, 64 x 16384
 // queries: 203 -> 180 us.  What bounds it now is the vector ALU (softmax and
 // the split of P, 10 instructions per score) beside the matrix cores.
@@ -561,29 +562,20 @@ __global__ __launch_bounds__(64 * WR) void coreset_attn_res_kernel(
   }
 }
 
+constexpr int64_t kDeviceCus = 256;
 constexpr int64_t kAttnWorkgroups = 1024;  // of the chunked kernel: four per CU
-// Waves per workgroup of the resident kernel; above 128 keys also 16-query
-// tiles per wave per step, passes over the keys and workgroups in all
+// Waves per workgroup of the resident kernel, up to 128 keys and above
 #ifndef ATTN_RES_WAVES
 #define ATTN_RES_WAVES 4
 #endif
 #ifndef ATTN_RES_WAVES_BIG
 #define ATTN_RES_WAVES_BIG 8
 #endif
-#ifndef ATTN_RES_QTR_BIG
-#define ATTN_RES_QTR_BIG 2
-#endif
-#ifndef ATTN_RES_H_BIG
-#define ATTN_RES_H_BIG 2
-#endif
-#ifndef ATTN_RES_WGS_BIG
-#define ATTN_RES_WGS_BIG 256
-#endif
 
 template <int D, int NKT, int QTR, int WR, int H, typename TO, bool W>
 hipError_t launch_attn_res_w(const void* Q, const void* K, const void* V, const int32_t* idx,
                              const float* logw, int64_t S, int64_t n, int64_t n_q,
-                             int64_t n_out, void* O, hipStream_t st) {
+                             int64_t n_out, void* O, int64_t run, hipStream_t st) {
   using L = ResLds<D, NKT>;
   auto kern = coreset_attn_res_kernel<D, NKT, QTR, WR, H, TO, W>;
   const size_t lds = L::bytes;
@@ -593,14 +585,14 @@ hipError_t launch_attn_res_w(const void* Q, const void* K, const void* V, const 
     if (e != hipSuccess) return e;
   }
   constexpr int64_t QSTEP = 16 * QTR * WR;
-  // about as many workgroups as the CUs hold (two each, or one where the
-  // coreset takes most of the LDS), whole steps of queries per workgroup
-  const int64_t want = lds > 80 * 1024 ? ATTN_RES_WGS_BIG : 512;
-  int64_t per_slice = (want + S - 1) / S;
+  // whole steps of queries per workgroup: the caller's run of them, or else
+  // (run 0) as many as leave about two workgroups per CU, which hold two
   const int64_t steps = (n_q + QSTEP - 1) / QSTEP;
-  if (per_slice > steps) per_slice = steps;
-  if (per_slice < 1) per_slice = 1;
-  const int64_t q_per_wg = ((steps + per_slice - 1) / per_slice) * QSTEP;
+  if (run < 1) {
+    const int64_t per_slice = std::min((512 + S - 1) / S, steps);
+    run = (steps + per_slice - 1) / per_slice;
+  }
+  const int64_t q_per_wg = run * QSTEP;
   const int64_t wgs = (n_q + q_per_wg - 1) / q_per_wg;
   dim3 grid((unsigned)wgs, (unsigned)S), block(64 * WR);
   hipLaunchKernelGGL(kern, grid, block, lds, st, (const bf16_t*)Q, (const bf16_t*)K,
@@ -611,10 +603,28 @@ hipError_t launch_attn_res_w(const void* Q, const void* K, const void* V, const 
 template <int D, int NKT, int QTR, int WR, int H, typename TO>
 hipError_t launch_attn_res(const void* Q, const void* K, const void* V, const int32_t* idx,
                            const float* logw, int64_t S, int64_t n, int64_t n_q, int64_t n_out,
-                           void* O, hipStream_t st) {
+                           void* O, hipStream_t st, int64_t run = 0) {
   if (logw)
-    return launch_attn_res_w<D, NKT, QTR, WR, H, TO, true>(Q, K, V, idx, logw, S, n, n_q, n_out, O, st);
-  return launch_attn_res_w<D, NKT, QTR, WR, H, TO, false>(Q, K, V, idx, logw, S, n, n_q, n_out, O, st);
+    return launch_attn_res_w<D, NKT, QTR, WR, H, TO, true>(Q, K, V, idx, logw, S, n, n_q, n_out, O, run, st);
+  return launch_attn_res_w<D, NKT, QTR, WR, H, TO, false>(Q, K, V, idx, logw, S, n, n_q, n_out, O, run, st);
+}
+
+// Above 128 keys: the coreset of d = 128 fills a CU's LDS, and the launch takes
+// one or two query tiles per wave (attn_tile_plan); d = 64 leaves room for two
+// workgroups of one tile.
+template <int D, int NKT, typename TO>
+hipError_t launch_attn_res_big(const void* Q, const void* K, const void* V, const int32_t* idx,
+                               const float* logw, int64_t S, int64_t n, int64_t n_q, int64_t n_out,
+                               void* O, hipStream_t st) {
+  if constexpr (D == 128) {
+    static_assert(ResLds<D, NKT>::bytes > 80 * 1024, "one workgroup per CU");
+    const TilePlan plan = attn_tile_plan(S, n_q, kDeviceCus);
+    if (plan.tiles == 2)
+      return launch_attn_res<D, NKT, 2, ATTN_RES_WAVES_BIG, 2, TO>(Q, K, V, idx, logw, S, n, n_q, n_out, O, st, plan.split.run);
+    return launch_attn_res<D, NKT, 1, ATTN_RES_WAVES_BIG, 1, TO>(Q, K, V, idx, logw, S, n, n_q, n_out, O, st, plan.split.run);
+  } else {
+    return launch_attn_res<D, NKT, 1, ATTN_RES_WAVES_BIG, 1, TO>(Q, K, V, idx, logw, S, n, n_q, n_out, O, st);
+  }
 }
 
 template <int D, typename TO>
@@ -627,9 +637,8 @@ hipError_t launch_attn_res_d(int64_t n_out, const void* Q, const void* K, const 
   if (n_out <= 96) return launch_attn_res<D, 6, 1, ATTN_RES_WAVES, 1, TO>(Q, K, V, idx, logw, S, n, n_q, n_out, O, st);
   if (n_out <= 128) return launch_attn_res<D, 8, 1, ATTN_RES_WAVES, 1, TO>(Q, K, V, idx, logw, S, n, n_q, n_out, O, st);
   // (192 = n_out 128 plus 32 sinks and a 32-row window)
-  constexpr int Q2 = D == 128 ? ATTN_RES_QTR_BIG : 1, H2 = D == 128 ? ATTN_RES_H_BIG : 1;
-  if (n_out <= 192) return launch_attn_res<D, 12, Q2, ATTN_RES_WAVES_BIG, H2, TO>(Q, K, V, idx, logw, S, n, n_q, n_out, O, st);
-  if (n_out <= 256) return launch_attn_res<D, 16, Q2, ATTN_RES_WAVES_BIG, H2, TO>(Q, K, V, idx, logw, S, n, n_q, n_out, O, st);
+  if (n_out <= 192) return launch_attn_res_big<D, 12, TO>(Q, K, V, idx, logw, S, n, n_q, n_out, O, st);
+  if (n_out <= 256) return launch_attn_res_big<D, 16, TO>(Q, K, V, idx, logw, S, n, n_q, n_out, O, st);
   *used = false;
   return hipSuccess;
 }

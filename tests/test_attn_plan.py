@@ -18,6 +18,12 @@ void grid_rows(int64_t blocks, int64_t threads, int64_t multiple, int64_t* out) 
   out[0] = g.x;
   out[1] = g.rows;
 }
+void tile_plan(int64_t S, int64_t n_q, int64_t slots, int64_t* out) {
+  const thin::TilePlan p = thin::attn_tile_plan(S, n_q, slots);
+  out[0] = p.tiles;
+  out[1] = p.split.parts;
+  out[2] = p.split.run;
+}
 }
 """
 
@@ -65,3 +71,47 @@ def test_prefill_tiles_are_each_taken_once_over_several_grid_rows(plan, work):
             if at < min(work, ((bx & 7) + 1) * per):
                 seen.append(at)
     assert sorted(seen) == list(range(work))
+
+
+def _ceil(a, b):
+    return -(-a // b)
+
+
+def _tile_cost(S, n_q, tiles, parts):
+    """Rounds of the device's 256 workgroups times a workgroup's time, in steps
+    of one tile (a step of two takes 1.75, staging the coreset 2)."""
+    steps = _ceil(n_q, 128 * tiles)
+    run = _ceil(steps, parts)
+    return _ceil(S * _ceil(steps, run), 256) * (2.0 + run * (1.0, 1.75)[tiles - 1])
+
+
+SLICES = [1, 2, 3, 4, 8, 12, 16, 20, 24, 32, 40, 48, 64, 96, 128, 200, 255, 256, 257, 300, 513, 4000]
+
+
+@pytest.mark.parametrize("S", SLICES)
+def test_attention_tile_plan_is_no_worse_than_a_fixed_workgroup_count(plan, S):
+    """129-256 keys, d = 128: 256 workgroups of two query tiles, or 512 of one,
+    rounded up to whole workgroups per slice, leave a nearly empty last round
+    wherever the slices do not divide them."""
+    out = (C.c_int64 * 3)()
+    for n_q in (1, 33, 128, 129, 256, 257, 1000, 1024, 4096, 8191, 16384, 65536, 1 << 20, 1 << 30):
+        plan.tile_plan(C.c_int64(S), C.c_int64(n_q), C.c_int64(256), out)
+        tiles, parts, run = out
+        step = 128 * tiles
+        assert tiles in (1, 2) and parts >= 1 and run >= 1
+        assert parts * run * step >= n_q > (parts - 1) * run * step, "every part has queries"
+        cost = _tile_cost(S, n_q, tiles, parts)
+        for t, want in ((1, 512), (2, 256)):
+            fixed = min(_ceil(want, S), _ceil(n_q, 128 * t))
+            assert cost <= _tile_cost(S, n_q, t, fixed) + 1e-9, (S, n_q, tiles, parts, t)
+
+
+@pytest.mark.parametrize("S,n_q,want", [
+    (64, 16384, (2, 4, 16)), (32, 65536, (2, 8, 32)),  # the long workloads fill the device
+    (8, 4096, (1, 32, 1)), (1, 1024, (1, 8, 1)),       # too few queries for two tiles
+    (24, 65536, (2, 10, 26)),                          # 240 workgroups, not 264
+])
+def test_attention_tile_plan_of_known_sizes(plan, S, n_q, want):
+    out = (C.c_int64 * 3)()
+    plan.tile_plan(C.c_int64(S), C.c_int64(n_q), C.c_int64(256), out)
+    assert tuple(out) == want

@@ -575,6 +575,33 @@ def test_two_pass_attention_with_a_dropped_pass(n_out, dropped):
         assert np.all(np.abs(ref - Ob[0, h]) <= 2e-3 + 2.0 ** -8 * np.abs(ref)), h
 
 
+# Above 128 keys (d = 128) a launch takes one query tile per wave and all keys
+# at once, or two tiles and the keys in two passes, by its workgroups' rounds on
+# the device: one step of the former, a part-filled last step of the latter over
+# one slice, several steps per workgroup over 40 slices.
+@pytest.mark.parametrize("S,n_q", [(1, 300), (1, 40001), (40, 2305)])
+@pytest.mark.parametrize("n_out", [129, 192, 193, 256])
+def test_attention_above_128_keys_in_both_forms(S, n_q, n_out):
+    w = W.custom("forms", B=1, H=S, n=300, n_q=n_q, d=128, dtype="bf16", kind="gauss")
+    Q, K, V = W.make_qkv(w)
+    rng = np.random.default_rng(n_out)
+    idx = rng.integers(0, 300, size=(1, S, n_out)).astype(np.int32)
+    logw = (rng.standard_normal((1, S, n_out)) * 2).astype(np.float32)
+    half = 96 if n_out <= 192 else 128
+    logw[:, ::2, :half] = -np.inf  # nothing weighs in the first pass, or in the
+    logw[:, 1::2, half:] = -np.inf  # second
+    args = [t.to(DEV) for t in (Q, K, V, torch.from_numpy(idx))]
+    O = thin_attention(*args).cpu().numpy()
+    Ow = thin_attention(*args, logw=torch.from_numpy(logw).to(DEV)).cpu().numpy()
+    r = np.unique(np.r_[0:20, 120:140, 250:260, n_q - 300:n_q])
+    for h in sorted({0, 1 % S, S - 1}):
+        ref = oracle.attention(Q[0, h][r], K[0, h], V[0, h], idx[0, h])
+        assert np.abs(ref - O[0, h][r]).max() <= _tol(w), h
+        ref = oracle.weighted_attention(Q[0, h][r], K[0, h], V[0, h], idx[0, h],
+                                        logw[0, h].astype(np.float64))
+        assert np.abs(ref - Ow[0, h][r]).max() <= _tol(w), h
+
+
 @pytest.mark.parametrize("n_q", [40, 40000])
 @pytest.mark.parametrize("n_out", [160, 256])
 @pytest.mark.parametrize("low", ["first", "last"])
