@@ -61,7 +61,7 @@ __device__ __forceinline__ void store4<bf16_t>(bf16_t* p, float a, float b, floa
   *reinterpret_cast<uint2*>(p) = make_uint2(__builtin_bit_cast(uint32_t, lo), __builtin_bit_cast(uint32_t, hi));
 }
 
-template <typename T, int D, typename TO, bool W, int QT>
+template <typename T, int D, typename TO, bool W, int QT, bool ONE>
 __global__ __launch_bounds__(64 * WAVES) void coreset_attn_kernel(
     const T* __restrict__ Q, const T* __restrict__ K, const T* __restrict__ V,
     const int32_t* __restrict__ idx, const float* __restrict__ logw, int64_t n, int64_t n_q,
@@ -85,8 +85,8 @@ __global__ __launch_bounds__(64 * WAVES) void coreset_attn_kernel(
   const float c2 = (float)(kLog2e / sqrt((double)D));
 
   constexpr int WPR = D * Elem<T>::bytes / 16;  // 16-byte words per row
-  // The workgroup's blocks of queries, as many apart as there are workgroups; a
-  // coreset of one chunk is staged for the first of them and stays.
+  // ONE: a coreset of one chunk, staged for the first of the workgroup's blocks
+  // of queries (as many apart as there are workgroups) and kept; else one block.
   const int64_t nqb = (n_q + 16 * QT * WAVES - 1) / (16 * QT * WAVES);
   const int64_t first = blockIdx.x + (int64_t)gridDim.x * blockIdx.z;
   for (int64_t qb = first; qb < nqb; qb += (int64_t)gridDim.x * gridDim.z) {
@@ -110,7 +110,7 @@ __global__ __launch_bounds__(64 * WAVES) void coreset_attn_kernel(
 
     for (int c0 = 0; c0 < n_out; c0 += KC) {
       const int kc = min(KC, n_out - c0);
-      if (n_out > KC || qb == first) {
+      if (!ONE || qb == first) {
         __syncthreads();
         if (W && threadIdx.x < KC)
           sB[threadIdx.x] = (int)threadIdx.x < kc ? Ws[c0 + threadIdx.x] * sqrt_d : -INFINITY;
@@ -232,6 +232,7 @@ __global__ __launch_bounds__(64 * WAVES) void coreset_attn_kernel(
                      acc[qt][dt][2] * inv, acc[qt][dt][3] * inv);
       }
     }
+    if constexpr (!ONE) break;
   }
 }
 
@@ -272,9 +273,9 @@ __device__ __align__(16) float g_attn_sink[256];
 // the keys at a time (H = 2, online softmax).  Launches that would leave the
 // device short of such workgroups keep one tile and one pass (attn_tile_plan).
 // 256 keys, d = 128, 32 x 65536 queries, bf16 output: 521 us with one tile, one
-// pass and 512 workgroups, 463 us with two, 440 us with the biases and masks as the score MFMAs' initial value
-// instead of two vector instructions per score; 192 weighted keys, 64 x 16384
-// queries: 203 -> 180 us.  What bounds it now is the vector ALU (softmax and
+// pass and 512 workgroups, 463 us with two, 440 us with the biases and masks as
+// the score MFMAs' initial value instead of two vector instructions per score;
+// 192 weighted keys, 64 x 16384 queries: 203 -> 180 us.  What bounds it now is the vector ALU (softmax and
 // the split of P, 10 instructions per score) beside the matrix cores.
 template <int D, int NKT, int QTR, int WR, int H, typename TO, bool W>
 __global__ __launch_bounds__(64 * WR) void coreset_attn_res_kernel(
@@ -563,7 +564,6 @@ __global__ __launch_bounds__(64 * WR) void coreset_attn_res_kernel(
 }
 
 constexpr int64_t kDeviceCus = 256;
-constexpr int64_t kAttnWorkgroups = 1024;  // of the chunked kernel: four per CU
 // Waves per workgroup of the resident kernel, up to 128 keys and above
 #ifndef ATTN_RES_WAVES
 #define ATTN_RES_WAVES 4
@@ -1280,19 +1280,33 @@ hipError_t launch_attn_t(const void* Q, const void* K, const void* V, const int3
   // x 400 keys, d = 128: 38 us, 45 with one).
   constexpr int QT = Elem<T>::bytes == 4 ? 1 : 2;
   constexpr int64_t per = 16 * QT * WAVES;
-  int64_t wgs = (n_q + per - 1) / per;
-  // one chunk of keys is staged once per workgroup: no more workgroups than
-  // fit the device together, each taking its share of the queries (a last,
-  // nearly empty round of workgroups cost the 16 x 4097 case 5 us)
-  if (n_out <= KC) wgs = std::min(wgs, std::max<int64_t>(1, kAttnWorkgroups / S));
-  const GridRows g = grid_rows(wgs, 64 * WAVES);
-  dim3 grid((unsigned)g.x, (unsigned)S, (unsigned)g.rows), block(64 * WAVES);
+  const int64_t blocks = (n_q + per - 1) / per;
+  auto launch = [&](auto kern, int64_t wgs) {
+    const GridRows g = grid_rows(wgs, 64 * WAVES);
+    hipLaunchKernelGGL(kern, dim3((unsigned)g.x, (unsigned)S, (unsigned)g.rows), dim3(64 * WAVES),
+                       0, st, (const T*)Q, (const T*)K, (const T*)V, idx, logw, n, n_q, (int)n_out,
+                       (TO*)O);
+  };
+  // One chunk of float keys: several blocks of queries per workgroup.  (bf16
+  // rows come here with d = 32 or more than 256 keys only; over one chunk of
+  // d = 32 a block's arithmetic is so short that the blocks' loads are better
+  // overlapped by workgroups of their own: 200 x 4097 queries over 16 keys 38
+  // us, 45 with 768 workgroups.)
+  if constexpr (Elem<T>::bytes == 4) {
+    if (n_out <= KC) {
+      constexpr int per_cu = D == 32 ? 5 : D == 64 ? 4 : 2;  // as the registers allow
+      const int64_t wgs = split_blocks(S, blocks, per_cu * kDeviceCus);
+      if (logw)
+        launch(coreset_attn_kernel<T, D, TO, true, QT, true>, wgs);
+      else
+        launch(coreset_attn_kernel<T, D, TO, false, QT, true>, wgs);
+      return hipGetLastError();
+    }
+  }
   if (logw)
-    hipLaunchKernelGGL((coreset_attn_kernel<T, D, TO, true, QT>), grid, block, 0, st, (const T*)Q,
-                       (const T*)K, (const T*)V, idx, logw, n, n_q, (int)n_out, (TO*)O);
+    launch(coreset_attn_kernel<T, D, TO, true, QT, false>, blocks);
   else
-    hipLaunchKernelGGL((coreset_attn_kernel<T, D, TO, false, QT>), grid, block, 0, st, (const T*)Q,
-                       (const T*)K, (const T*)V, idx, logw, n, n_q, (int)n_out, (TO*)O);
+    launch(coreset_attn_kernel<T, D, TO, false, QT, false>, blocks);
   return hipGetLastError();
 }
 

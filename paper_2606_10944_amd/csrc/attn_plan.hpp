@@ -43,6 +43,29 @@ inline StepSplit split_steps(int64_t S, int64_t steps, int64_t slots, double sta
   return best;
 }
 
+// Workgroups per slice of float attention over one chunk of at most 64 keys,
+// which a workgroup stages once (worth about half a block) and keeps for its
+// share of the slice's `blocks` blocks of 64 queries, dealt out in turn; several
+// workgroups share a CU, `slots` fit the device.  A share of less than two
+// blocks counts as whole blocks (one of the workgroups has two).  d = 64, 1024
+// slots, us: one workgroup per block | 1024 / S of them | this: 64 x 4097 queries
+// over 16 keys 50 | 48 | 48, 520 x 1000 94 | 124 | 95, 1000 x 256 51 | 46 | 46;
+// over 64 keys 59 | 50 | 50, 123 | 128 | 103, 67 | 49 | 49.
+inline int64_t split_blocks(int64_t S, int64_t blocks, int64_t slots) {
+  int64_t best = 0;
+  double least = 0.0;
+  const int64_t r0 = (S + slots - 1) / slots;
+  for (int64_t r = r0; r < r0 + 8; ++r) {
+    const int64_t parts = std::min(blocks, slots * r / S);
+    const double share = 2 * parts <= blocks ? (double)blocks / (double)parts
+                                             : (double)((blocks + parts - 1) / parts);
+    const double cost = (double)((S * parts + slots - 1) / slots) * (0.55 + share);
+    if (best == 0 || cost < least * (1.0 - 1e-9)) best = parts, least = cost;
+    if (parts == blocks) break;
+  }
+  return best;
+}
+
 // Attention over 129 to 256 keys of d = 128 (one workgroup per CU): a step is
 // 128 queries with one query tile per wave, or 256 with two, which read each
 // fragment of the coreset once for both and so take 1.75 times as long as one

@@ -24,6 +24,9 @@ void tile_plan(int64_t S, int64_t n_q, int64_t slots, int64_t* out) {
   out[1] = p.split.parts;
   out[2] = p.split.run;
 }
+int64_t split_blocks(int64_t S, int64_t blocks, int64_t slots) {
+  return thin::split_blocks(S, blocks, slots);
+}
 }
 """
 
@@ -35,7 +38,9 @@ def plan(tmp_path_factory):
     so = d / "shim.so"
     subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-shared", "-fPIC", "-I", CSRC,
                     str(d / "shim.cpp"), "-o", str(so)], check=True)
-    return C.CDLL(str(so))
+    lib = C.CDLL(str(so))
+    lib.split_blocks.restype = C.c_int64
+    return lib
 
 
 # The most float queries a call takes (2^30) in blocks of 64, and one block more
@@ -115,3 +120,24 @@ def test_attention_tile_plan_of_known_sizes(plan, S, n_q, want):
     out = (C.c_int64 * 3)()
     plan.tile_plan(C.c_int64(S), C.c_int64(n_q), C.c_int64(256), out)
     assert tuple(out) == want
+
+
+@pytest.mark.parametrize("S", [1, 7, 64, 100, 512, 513, 600, 1000, 1023, 1024, 1025, 2000, 65535])
+@pytest.mark.parametrize("slots", [512, 1024, 1280])
+def test_blocks_of_one_chunk_of_keys_fill_the_device(plan, S, slots):
+    for blocks in (1, 2, 4, 5, 16, 65, 257, 1 << 24):
+        parts = plan.split_blocks(C.c_int64(S), C.c_int64(blocks), C.c_int64(slots))
+        assert 1 <= parts <= blocks
+        # no device half empty, where the queries would fill it
+        if blocks >= 16:
+            assert S * parts > slots // 2 or parts == blocks
+            rounds = _ceil(S * parts, slots)
+            assert rounds == 1 or S * parts / (rounds * slots) > 0.6, (blocks, parts)
+
+
+@pytest.mark.parametrize("S,blocks,slots,want", [
+    (16, 65, 1024, 64), (64, 65, 1024, 16),  # as many as fit together
+    (1, 17, 1024, 17), (600, 4, 1024, 1), (520, 16, 1280, 7), (2000, 8, 512, 1),
+])
+def test_blocks_of_one_chunk_of_keys_of_known_sizes(plan, S, blocks, slots, want):
+    assert plan.split_blocks(C.c_int64(S), C.c_int64(blocks), C.c_int64(slots)) == want
