@@ -6,6 +6,7 @@
 
 #include "common.hpp"
 #include "launch.hpp"
+#include "score_plan.hpp"
 
 namespace thin {
 
@@ -1971,18 +1972,10 @@ __global__ __launch_bounds__(64) void gram16_kernel(const T* rows, float* out) {
 #ifndef SCORE_IL
 #define SCORE_IL 16
 #endif
-// Float score launches of at most this many units of 32 x 32 take a wave per
-// unit: 16 buckets of 1024 rows (8448 units, first round) 77 -> 61 us, of 512
-// rows 38 -> 24 us (d = 64).  Beyond, the device is full either way and the
-// workgroups of eight waves read each row once for 256 others.  bf16 rows stay
-// with those at every size: their products are eight times as fast and the
-// launch is all latency (32 buckets of 512 rows: 15 us against 19).
-constexpr int64_t kUnitLaunchMax = 16384;
-
 template <typename T, int D>
 hipError_t launch_scores_td(const HalveArgs& a0, int64_t nbk, hipStream_t st) {
   if constexpr (Elem<T>::bytes == 4) {
-    if (score_units(a0.N) * nbk <= kUnitLaunchMax) {
+    if (score_units(a0.N) * nbk <= unit_launch_max(D, a0.N, nbk, a0.rowh2_write != 0)) {
       HalveArgs u = a0;
       u.nbk = nbk;
       u.ipb = (int32_t)score_units(a0.N);

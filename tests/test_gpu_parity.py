@@ -219,6 +219,25 @@ def test_score_unit_and_chunk_edges(cfg):
     _check_compress(w, K, V, U, idx, tr, range(min(w.S, 4)))
 
 
+# Float launches on both sides of the unit launches' line at d = 128 (one wave
+# of them per SIMD): 70 first-round buckets of 404 rows take workgroups, 24 of
+# 260 units; of the second rounds of 202 rows, 120 buckets and 40.
+UNIT_LINE_128 = [
+    dict(B=7, H=10, n=404, n_out=202, g=0, d=128, dtype="fp32", kind="gauss_d4"),
+    dict(B=4, H=6, n=260, n_out=130, g=0, d=128, dtype="fp32", kind="gauss_d4"),
+    dict(B=6, H=20, n=404, n_out=101, g=2, d=128, dtype="fp32", kind="heavy_tail_mean"),
+    dict(B=4, H=10, n=404, n_out=101, g=2, d=128, dtype="fp32", kind="gauss_d4"),
+]
+
+
+@pytest.mark.parametrize("cfg", UNIT_LINE_128, ids=lambda c: f"S{c['B'] * c['H']}-n{c['n']}-o{c['n_out']}")
+def test_float_scores_of_wide_rows_as_units_and_workgroups(cfg):
+    w = W.custom("line", seed=23, **cfg)
+    Q, K, V = W.make_qkv(w)
+    plan, U, idx, tr = _compress_gpu(w, Q, K, V)
+    _check_compress(w, K, V, U, idx, tr, range(min(w.S, 4)))
+
+
 @pytest.mark.parametrize("cfg", CUSTOM, ids=lambda c: f"n{c['n']}-o{c['n_out']}-g{c['g']}-d{c['d']}-{c['dtype']}")
 def test_custom_shapes_parity(cfg):
     w = W.custom("custom", seed=11, **cfg)

@@ -1,0 +1,50 @@
+"""Launch rules of the Halve rounds (csrc/score_plan.hpp, host arithmetic only),
+compiled for the CPU."""
+import ctypes as C
+import os
+import subprocess
+
+import pytest
+
+from paper_2606_10944_amd import build as hip_build
+
+CSRC = os.path.join(hip_build.HERE, "csrc")
+
+SHIM = r"""
+#include "score_plan.hpp"
+extern "C" int64_t unit_launch_max(int64_t d, int64_t N, int64_t nbk, int first) {
+  return thin::unit_launch_max(d, N, nbk, first != 0);
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def plan(tmp_path_factory):
+    d = tmp_path_factory.mktemp("plan")
+    (d / "shim.cpp").write_text(SHIM)
+    so = d / "shim.so"
+    subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-shared", "-fPIC", "-I", CSRC,
+                    str(d / "shim.cpp"), "-o", str(so)], check=True)
+    lib = C.CDLL(str(so))
+    lib.unit_launch_max.restype = C.c_int64
+    return lib
+
+
+def _units(N):
+    NC, nb = -(-N // 32), -(-N // 64)
+    return 2 * (nb * NC - nb * (nb - 1))
+
+
+# Launches measured in both forms (whole calls, float rows), and which was faster.
+@pytest.mark.parametrize("d,N,buckets,first,units", [
+    (64, 1024, 24, True, True), (64, 512, 64, True, True), (64, 512, 100, True, False),
+    (64, 800, 48, True, False), (64, 512, 64, False, False), (64, 320, 64, False, True),
+    (64, 2048, 6, True, True), (32, 5600, 1, True, True), (32, 512, 100, True, False),
+    (128, 256, 33, True, True), (128, 256, 100, True, False), (128, 512, 64, True, False),
+    (128, 800, 32, True, False), (128, 1024, 16, True, False), (128, 1024, 8, True, True),
+    (128, 2048, 6, True, False), (128, 4096, 1, True, True), (128, 512, 100, False, False),
+    (128, 200, 300, True, False), (128, 512, 16, True, True),
+])
+def test_float_rounds_take_units_where_those_are_faster(plan, d, N, buckets, first, units):
+    most = plan.unit_launch_max(C.c_int64(d), C.c_int64(N), C.c_int64(buckets), int(first))
+    assert (_units(N) * buckets <= most) == units, (_units(N) * buckets, most)
