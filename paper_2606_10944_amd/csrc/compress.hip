@@ -469,6 +469,7 @@ constexpr int kScoreRowsStaged = kScoreChunkMax * 32;  // rows of a streamed chu
 // consecutive lanes fall in different banks.
 constexpr int kETileStride = 36;
 constexpr int kETileLds = 8 * kETileStride;
+constexpr size_t kCuLds = (size_t)160 << 10;  // LDS of a gfx950 CU
 
 template <typename T, int D, int W>
 struct ScoreShape {
@@ -675,11 +676,21 @@ __device__ __forceinline__ float4 score_e(const float* f0, const float* f1, bool
 // LOCAL: the whole round for buckets of at most GT*16 rows in one launch:
 // one workgroup per bucket computes the bucket's scores into LDS (its own
 // chunk is the whole bucket), then takes the decisions from LDS with the same
-// arithmetic as halve_pass_kernel (the scores never leave the CU).
+// arithmetic as halve_pass_kernel (the scores never leave the CU).  Its rows are
+// in order within a half-block (frag_row's order serves stores to the score
+// array), so that a 16-row column tile past the bucket has nothing to do.
+// STAGED: of those, every row tile in LDS at once (local_staged) instead of a
+// ring: no barrier per tile, and a bucket of at most half the blocks spreads a
+// half-block's tiles over several waves.  (An instantiation each: together they
+// take 88 registers at d = 32, two workgroups per CU; apart 80, three.)  Local
+// launches of float rows, d = 128, against rows in frag_row's order and both
+// forms in one kernel: 16 buckets of 66 rows 25.5 -> 23.1 us, 600 of 16 rows 28.5
+// -> 20.3; d = 32, 600 of 64 rows 19.2 -> 15.6.
 // OWN_ONLY: a launch of own chunks only (an instantiation without the
 // streamed code, which needs fewer registers).
-template <typename T, int D, bool LOCAL, bool OWN_ONLY, int W>
-__global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(W == 8 ? 4 : 2)))
+template <typename T, int D, bool LOCAL, bool OWN_ONLY, int W, bool STAGED = false>
+__global__ __launch_bounds__(64 * W)
+__attribute__((amdgpu_waves_per_eu(LOCAL && Frag<T, D>::NV <= 2 ? 6 : W == 8 ? 4 : 2)))
 void pair_scores_kernel(HalveArgs a) {
   using SS = ScoreShape<T, D, W>;
   constexpr int NV = SS::NV, NBW = SS::BLOCKS, GT = SS::GT, CH = SS::CHUNKS;
@@ -754,11 +765,11 @@ void pair_scores_kernel(HalveArgs a) {
   const float c2 = (float)(kLog2e * inv_sqrt_d);
 
   extern __shared__ __align__(16) unsigned char smem[];
-  // own chunks: ring (LOCAL with stage_all: every row tile) | (LOCAL) every score tile of the bucket | pair scales of
-  // the group's rows [GT * 16] | half-blocks' largest row scales | (LOCAL)
-  // pair terms and the decisions' state
-  const bool stage_all = LOCAL && a.stage_all;
-  float* s_e = reinterpret_cast<float*>(smem + (stage_all ? 2 * NC * CH * 1024 : SS::OWN_RING));
+  // own chunks: ring (STAGED: every row tile) | (LOCAL) every score tile of the
+  // bucket | pair scales of the group's rows [GT * 16] | half-blocks' largest row
+  // scales | (LOCAL) pair terms and the decisions' state
+  static_assert(LOCAL || !STAGED, "only local launches stage every tile");
+  float* s_e = reinterpret_cast<float*>(smem + (STAGED ? NT * CH * 1024 : SS::OWN_RING));
   float* s_h2 = s_e + (LOCAL ? (int)panel_tiles(nb, NT, 4) : 0) * kETileLds;
   float* s_mh = own ? s_h2 + GT * 16
                     : reinterpret_cast<float*>(smem + SS::STAGES * SS::STAGE) +
@@ -777,19 +788,23 @@ void pair_scores_kernel(HalveArgs a) {
   int32_t* s_row = reinterpret_cast<int32_t*>(s_he + 32 * a.ch * NBW);
 
   // ---- this wave's half-block: rows, fragments and, in chunk 0, pair terms ----
-  // With stage_all and at most half the blocks, parts waves share a
-  // half-block and take every parts-th of its column tiles; the later parts go
-  // through the half-blocks in reverse, so that a SIMD (waves w and w + 4)
-  // gets a long and a short one.
+  // STAGED with at most half the blocks: parts waves share a half-block (no more
+  // than it has column tiles: a further wave would only read its rows again) and
+  // take every parts-th tile; the later parts go through the half-blocks in
+  // reverse, so that a SIMD (waves w and w + 4) gets a long and a short one.
   const int nhb = 2 * nb;
-  const int parts = stage_all && nhb <= W / 2 ? W / nhb : 1;
-  const int pass = parts > 1 ? wave / nhb : 0;
-  const int hbw = parts > 1 ? (pass & 1 ? nhb - 1 - wave % nhb : wave % nhb) : wave;  // local half-block
-  const int part = pass;
+  const int parts = STAGED && 2 * nhb <= W ? min(W / nhb, NC) : 1;
+  const int part = parts > 1 ? wave / nhb : 0;
+  const int hbw = part & 1 ? nhb - 1 - wave % nhb : part ? wave % nhb : wave;  // local half-block
   const int lblk = hbw >> 1, half = hbw & 1;
   const int blk = grp * NBW + lblk;
-  const bool hb_ok = blk < nb && part < parts;
+  // (LOCAL: a half-block without rows takes no part either)
+  const bool hb_ok = blk < nb && part < parts && (!LOCAL || hbw < NC);
   const bool odd = (m16 & 1) != 0;
+  // Row of the half-block that lane m16 of 16-row tile rt holds.  LOCAL keeps its
+  // scores in LDS and the rows in order: a 16-row column tile past the bucket
+  // then has nothing to do.
+  auto row_of = [&](int rt) { return LOCAL ? 16 * rt + m16 : frag_row(rt, m16); };
   // Streamed chunk: column row o of the chunk in fragment order (tile o / 32,
   // 16-row half o / 16 & 1, lane o % 16); this thread's are o = threadIdx.x +
   // 64 W k.  Their indices are requested first, then their scale exponents
@@ -810,7 +825,7 @@ void pair_scores_kernel(HalveArgs a) {
   float arh[2];
 #pragma unroll
   for (int rt = 0; rt < 2; ++rt) {
-    const int j = blk * 64 + half * 32 + frag_row(rt, m16);
+    const int j = blk * 64 + half * 32 + row_of(rt);
     const bool valid = hb_ok && j < N;
     ar[rt] = valid ? (rows_in ? (int64_t)rows_in[j] : row_base + j) : -1;
     arh[rt] = (!own && valid) ? a.rowh2[s * a.n + ar[rt]] : 0.0f;
@@ -859,7 +874,7 @@ void pair_scores_kernel(HalveArgs a) {
         float rh2, h2f, lbt;
         frag_pair_terms<T, D>(Ak[rt], Av[rt], vm2d, inv_sqrt_d, rh2, h2f, lbt);
         arh[rt] = ar[rt] >= 0 ? rh2 : 0.0f;
-        const int j = blk * 64 + half * 32 + frag_row(rt, m16);
+        const int j = blk * 64 + half * 32 + row_of(rt);
         if (g == 0) s_h2[(2 * hbw + rt) * 16 + m16] = j < N ? h2f : 0.0f;
         if (g == 0 && j < N && (j & 1) == 0) {
           if (LOCAL) {
@@ -883,15 +898,14 @@ void pair_scores_kernel(HalveArgs a) {
   // the largest row scale of each half-block (rows past the bucket: 0, and
   // every row scale is >= 0), published in LDS before the tile loop's first
   // barrier
-  if (part == 0) {
-    const float mh = wave_max_f(fmaxf(arh[0], arh[1]));
-    if (lane == 0) s_mh[2 * lblk + half] = mh;
-  }
+  const float mh = wave_max_f(fmaxf(arh[0], arh[1]));
+  if (lane == 0) s_mh[wave] = part == 0 ? mh : 0.0f;  // (later parts: half-blocks without rows)
   // This wave's scores against 16 pairs (one column tile jc) of its block's
   // panel: pair q of the tile (of this lane), then pairs i = 4g .. 4g+3 of
   // the half-block.  The panel ends after 8 pairs of the last tile when NT is
   // odd.
-  const int q = 4 * (m16 >> 2) + 2 * (odd ? 1 : 0) + ((m16 >> 1) & 1);
+  const int q = LOCAL ? (odd ? 8 : 0) + (m16 >> 1)
+                      : 4 * (m16 >> 2) + 2 * (odd ? 1 : 0) + ((m16 >> 1) & 1);
   float* ew = nullptr;
   if constexpr (!LOCAL)
     ew = a.E + (bl * a.e_tiles + panel_tiles(blk, NT, 4) - 4 * blk) * 256 + q * 16 + 4 * g;
@@ -984,9 +998,11 @@ void pair_scores_kernel(HalveArgs a) {
       const float4 e = score_e(fa, fb, odd);
       if constexpr (LOCAL) {
         if (in_panel(jc0 + tt)) {
+          // (pairs 2 g, 2 g + 1 of either 16-row tile)
           float* col = s_e + (panel_tiles(blk, NT, 4) + 2 * (jc0 + tt) + (q >> 3) - 4 * blk) * kETileLds +
-                       (q & 7) * kETileStride;
-          *reinterpret_cast<float4*>(col + 16 * half + 4 * g) = e;
+                       (q & 7) * kETileStride + 16 * half + 2 * g;
+          *reinterpret_cast<float2*>(col) = make_float2(e.x, e.y);
+          *reinterpret_cast<float2*>(col + 8) = make_float2(e.z, e.w);
         }
       } else if (in_panel(jc0 + tt)) {
         *e_tile(jc0 + tt) = e;
@@ -1011,21 +1027,23 @@ void pair_scores_kernel(HalveArgs a) {
     };
     // a half-block takes part from its block's diagonal on
     const int first = hb_ok ? 2 * lblk : GT;
-    if (stage_all) {
-      if constexpr (LOCAL) {
-        if (hbw < ntile) {  // (a half-block past the bucket has no tile)
-          commit(2 * hbw, 2 * hbw);
-          commit(2 * hbw + 1, 2 * hbw + 1);
-        }
-        __syncthreads();
-        for (int tt = first + part; tt < ntile; tt += parts) {
-          float fa[4], fb[4];
-          form(2 * tt, smem + 2 * tt * CH * 1024, fa);
+    if constexpr (STAGED) {
+      if (hb_ok) {
+        commit(2 * hbw, 2 * hbw);
+        if (2 * hbw + 1 < NT) commit(2 * hbw + 1, 2 * hbw + 1);
+      }
+      __syncthreads();
+      for (int tt = first + part; tt < ntile; tt += parts) {
+        float fa[4], fb[4];
+        form(2 * tt, smem + 2 * tt * CH * 1024, fa);
+        if (2 * tt + 1 < NT) {
           form(2 * tt + 1, smem + (2 * tt + 1) * CH * 1024, fb);
           put(tt, fa, fb);
+        } else {
+          put(tt, fa, fa);
         }
-        __syncthreads();
       }
+      __syncthreads();
     } else {
       commit(0, 0);
       commit(1, 1);
@@ -1038,7 +1056,12 @@ void pair_scores_kernel(HalveArgs a) {
         if (i + 2 < 2 * ntile) commit(i + 2, (st + 2) % 3);
         if (tt >= first) {
           float f[4];
-          form(i, smem + st * CH * 1024, f);
+          if (LOCAL && i >= NT) {  // a 16-row tile past the bucket
+#pragma unroll
+            for (int k = 0; k < 4; ++k) f[k] = 0.0f;
+          } else {
+            form(i, smem + st * CH * 1024, f);
+          }
           if (u == 0) {
 #pragma unroll
             for (int k = 0; k < 4; ++k) f0[k] = f[k];
@@ -2079,7 +2102,6 @@ hipError_t launch_local_td(const HalveArgs& a0, int64_t nbk, hipStream_t st) {
   }
   constexpr int WO = score_waves<T, D>();
   using SS = ScoreShape<T, D, WO>;
-  auto kern = pair_scores_kernel<T, D, true, true, WO>;
   const int64_t NT = (a0.N + 15) / 16, nb = (a0.N + 63) / 64, P = a0.N / 2;
   // ring, score tiles, pair scale exponents of the rows, half-block row scale
   // maxima, pair terms [2][P], then (8-byte aligned) the decisions' thresholds
@@ -2087,14 +2109,11 @@ hipError_t launch_local_td(const HalveArgs& a0, int64_t nbk, hipStream_t st) {
   const size_t rest = (size_t)panel_tiles(nb, NT, 4) * kETileLds * 4 + SS::GT * 16 * 4 +
                       2 * SS::BLOCKS * 4 + 2 * P * 4 + 8 + 2 * 64 * SS::BLOCKS * 8 +
                       SS::BLOCKS * 4 + WO * 4;
-  // Every row tile staged at once (no barrier per tile, and buckets of at most
-  // half the blocks spread a half-block's tiles over several waves) where that
-  // costs no resident workgroup: launches of at most one per CU, or LDS for two
-  // per CU all the same.  1 to 32 buckets of 128 rows (float, d = 64) 20.3 ->
-  // 18.1 us, of 256 rows (bf16, d = 64) 19.1 -> 17.5 us, 64 rows 13.2 -> 12.3.
-  const size_t all = (size_t)((a0.N + 31) / 32) * 2 * SS::CHUNKS * 1024 + rest;
-  const bool stage_all = all <= 80 * 1024 || (nbk <= 256 && all <= 160 * 1024);
-  const size_t lds = stage_all ? all : SS::OWN_RING + rest;
+  const size_t all = (size_t)NT * SS::CHUNKS * 1024 + rest;
+  const bool staged = local_staged(nbk, (int64_t)all, SS::NV <= 2 ? 3 : 2);
+  const size_t lds = staged ? all : SS::OWN_RING + rest;
+  auto kern = staged ? pair_scores_kernel<T, D, true, true, WO, true>
+                     : pair_scores_kernel<T, D, true, true, WO, false>;
   if (lds > 64 * 1024) {
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
@@ -2102,7 +2121,6 @@ hipError_t launch_local_td(const HalveArgs& a0, int64_t nbk, hipStream_t st) {
   }
   HalveArgs a = a0;
   a.ch = kScoreChunk;
-  a.stage_all = stage_all;
   a.e_tiles = 0;
   hipLaunchKernelGGL(kern, dim3((unsigned)nbk), dim3(64 * WO), lds, st, a);
   return hipGetLastError();
@@ -2245,7 +2263,6 @@ hipError_t launch_local(int dtype, int64_t d, const HalveArgs& a, int64_t nbk, h
 #define PASS_NCB_L 3
 #define PASS_FD_L 2
 #endif
-constexpr size_t kPassMaxLds = (size_t)160 << 10;  // LDS of a gfx950 CU
 hipError_t launch_decide(const HalveArgs& a0, int64_t nbk, hipStream_t st) {
   const HalveArgs a = with_layout(a0);
   // bulk waves x prefetched chunks x 64 pairs should cover the pairs after
@@ -2257,9 +2274,9 @@ hipError_t launch_decide(const HalveArgs& a0, int64_t nbk, hipStream_t st) {
   // the large shape's column buffers take 9 KiB of LDS per bulk wave: past
   // the 160 KiB of a CU (buckets above 4096 rows) eight bulk waves run, past
   // that the medium shape
-  if (PassLds<PASS_BW_L, PASS_NCB_L, PASS_FD_L>::bytes((int)(a.N / 2)) <= kPassMaxLds)
+  if (PassLds<PASS_BW_L, PASS_NCB_L, PASS_FD_L>::bytes((int)(a.N / 2)) <= kCuLds)
     return launch_pass_w<PASS_BW_L, PASS_NCB_L, PASS_FD_L, true>(a, nbk, st);
-  if (PassLds<8, 3, 2>::bytes((int)(a.N / 2)) <= kPassMaxLds)
+  if (PassLds<8, 3, 2>::bytes((int)(a.N / 2)) <= kCuLds)
     return launch_pass_w<8, 3, 2, true>(a, nbk, st);
   return launch_pass_w<PASS_BW_M, PASS_NCB_M, PASS_FD_M, true>(a, nbk, st);
 }

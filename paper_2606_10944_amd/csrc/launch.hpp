@@ -32,7 +32,6 @@ struct HalveArgs {
   int32_t ch;                 // column tiles per score workgroup (set by launch_scores)
   float* rowh2;               // [S, n] scale exponent of every row, written by the first round
   int32_t rowh2_write;        // this round writes rowh2 (and reads it only after writing)
-  int32_t stage_all;          // local launch: every row tile staged at once (set by launch_local)
   int32_t own;                // the launch holds the groups' own chunks (set by launch_scores)
   int64_t nbk;                // buckets of a score launch (set by launch_scores)
   int32_t ipb;                // score workgroups per bucket in a launch (set by launch_scores)

@@ -31,4 +31,16 @@ inline int64_t unit_launch_max(int64_t d, int64_t N, int64_t nbk, bool first_rou
   return std::min(kMost, std::max(wide, 36864 / nbk));
 }
 
+// A local launch of nbk buckets stages every row tile of a bucket at once, where
+// that takes `lds` bytes per workgroup and the registers let by_registers
+// workgroups share a CU, if that costs no resident workgroup: the launch fits the
+// device all the same, or LDS holds as many as the registers.  1 to 32 buckets of
+// 128 rows (float, d = 64) 20.3 us in a ring, 18.1 staged; of 256 rows (bf16, d =
+// 64) 19.1, 17.5; 600 buckets of 160 rows (bf16, d = 64), two staged workgroups
+// per CU against three, 23.5, 27.6.
+inline bool local_staged(int64_t nbk, int64_t lds, int64_t by_registers) {
+  const int64_t fit = ((int64_t)160 << 10) / lds;
+  return fit >= 1 && (nbk <= 256 * fit || fit >= by_registers);
+}
+
 }  // namespace thin

@@ -219,6 +219,26 @@ def test_score_unit_and_chunk_edges(cfg):
     _check_compress(w, K, V, U, idx, tr, range(min(w.S, 4)))
 
 
+# Local launches: buckets whose last 16-row or 32-row tile is nearly or wholly
+# empty (2 .. 98 rows: one half-block to four, shared by waves or not), with every
+# tile staged (3 slices) and in a ring (300 or 600 slices, past what the device
+# holds staged).
+LOCAL_EDGES = [dict(H=3, n=N, d=d, dtype=t) for d, t in ((32, "fp32"), (128, "fp32"), (64, "bf16"),
+                                                         (128, "bf16"))
+               for N in (2, 16, 18, 34, 50, 66, 82, 98)]
+LOCAL_EDGES += [dict(H=600, n=146, d=64, dtype="bf16"), dict(H=300, n=226, d=128, dtype="bf16"),
+                dict(H=300, n=114, d=128, dtype="fp32"), dict(H=300, n=194, d=32, dtype="fp32"),
+                dict(H=300, n=178, d=64, dtype="fp32")]
+
+
+@pytest.mark.parametrize("c", LOCAL_EDGES, ids=lambda c: f"S{c['H']}-n{c['n']}-d{c['d']}-{c['dtype']}")
+def test_local_launch_edges(c):
+    w = W.custom("local", B=1, n_out=c["n"] // 2, g=0, kind="gauss_d4", seed=29, **c)
+    Q, K, V = W.make_qkv(w)
+    plan, U, idx, tr = _compress_gpu(w, Q, K, V)
+    _check_compress(w, K, V, U, idx, tr, sorted({0, 1, w.S // 2, w.S - 1}))
+
+
 # Float launches on both sides of the unit launches' line at d = 128 (one wave
 # of them per SIMD): 70 first-round buckets of 404 rows take workgroups, 24 of
 # 260 units; of the second rounds of 202 rows, 120 buckets and 40.

@@ -15,6 +15,9 @@ SHIM = r"""
 extern "C" int64_t unit_launch_max(int64_t d, int64_t N, int64_t nbk, int first) {
   return thin::unit_launch_max(d, N, nbk, first != 0);
 }
+extern "C" int local_staged(int64_t nbk, int64_t lds, int64_t by_registers) {
+  return thin::local_staged(nbk, lds, by_registers);
+}
 """
 
 
@@ -48,3 +51,15 @@ def _units(N):
 def test_float_rounds_take_units_where_those_are_faster(plan, d, N, buckets, first, units):
     most = plan.unit_launch_max(C.c_int64(d), C.c_int64(N), C.c_int64(buckets), int(first))
     assert (_units(N) * buckets <= most) == units, (_units(N) * buckets, most)
+
+
+@pytest.mark.parametrize("buckets,lds,by_registers,staged", [
+    (1, 160 << 10, 2, True), (256, 160 << 10, 2, True), (257, 160 << 10, 2, False),
+    (512, 80 << 10, 2, True), (100000, 80 << 10, 2, True),   # as many as the registers allow
+    (512, 80 << 10, 3, True), (600, 64 << 10, 3, False),     # two where three fit
+    (100000, 53 << 10, 3, True), (1, (160 << 10) + 256, 2, False),
+])
+def test_local_launches_stage_all_rows_where_it_costs_no_workgroup(plan, buckets, lds,
+                                                                  by_registers, staged):
+    assert bool(plan.local_staged(C.c_int64(buckets), C.c_int64(lds),
+                                  C.c_int64(by_registers))) == staged
