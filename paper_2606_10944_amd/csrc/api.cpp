@@ -975,8 +975,16 @@ int pf_run(int64_t n_out, int32_t mbar, int64_t n, const float* draws, int64_t n
             h->piece.push_back(n_out);
             const int64_t gdone = (x.nE - n_out) / n_out;
             if (gdone > 0) {
-              h->segs.push_back({dev(reg(lv, x.mp - 1)), rst(lv, x.mp - 1), 0, gdone * n_out,
-                                 0.0f});
+              // the groups' coresets: the last depth's outputs, or (no Compress2)
+              // the points Subsample kept
+              if (x.mp > 0) {
+                h->segs.push_back({dev(reg(lv, x.mp - 1)), rst(lv, x.mp - 1), 0, gdone * n_out,
+                                   0.0f});
+              } else {
+                int32_t* base = dev(kept_off);
+                h->segs.push_back({base ? base + h->kept_base[lv] : nullptr, n, 0, gdone * n_out,
+                                   0.0f});
+              }
               h->piece.push_back(n_out);
             }
           }
@@ -1391,8 +1399,9 @@ int thin_express_prefill(int32_t dtype, int64_t B, int64_t H, int64_t n, int64_t
         return thin::launch_rows_copy(dev(L.enode[lv]), n_out, dev(L.ein), 4 * n_out, n_out, S,
                                       st);
       }));
+      const int32_t* groups = mp > 0 ? dev(L.region[lv][mp - 1]) : kept + h.kept_base[lv];
       ok(observed(THIN_KERNEL_EXPRESS, -1, st, [&] {
-        return thin::launch_rows_copy(dev(L.region[lv][mp - 1]), L.rstride[lv][mp - 1],
+        return thin::launch_rows_copy(groups, mp > 0 ? L.rstride[lv][mp - 1] : n,
                                       dev(L.ein) + n_out, 4 * n_out, 3 * n_out, S, st);
       }));
       in = dev(L.ein);

@@ -310,3 +310,18 @@ def test_static_compress_rejects_what_does_not_fit_before_any_launch():
     assert rc == _lib.THIN_EWORKSPACE
     assert L.thin_compress_static(FAKE, FAKE, 1, 1, 1, 1000, 80, 8, 1, FAKE, 1 << 20, FAKE,
                                   None, None) == _lib.THIN_EINVAL  # d unsupported
+
+
+@pytest.mark.skipif(__import__("torch").cuda.is_available(), reason="made-up device addresses")
+def test_prefill_without_compress2_ends_normally():
+    """mbar = 0 (Subsample only) past the first level: the host counters have no
+    Compress2 outputs to point at; without a GPU the call ends in the first
+    copy's error."""
+    p = _lib.thin_express_prefill_plan(1, 1, 1000, 64, 16, 0)
+    staging = (C.c_char * p["host_staging_bytes"])()
+    draws = (C.c_float * p["subsample_draws"])()
+    rc = _lib.lib().thin_express_prefill(1, 1, 1, 1000, 64, 16, 0, 0.5, 0, FAKE, FAKE, FAKE, FAKE,
+                                         1 << 30, draws, p["subsample_draws"], FAKE, 0,
+                                         C.c_void_p(0x100000), p["workspace_bytes"], staging,
+                                         p["host_staging_bytes"], None, None)
+    assert rc == 5  # THIN_EHIP

@@ -153,6 +153,20 @@ def _check_prefill(w, Q, K, V, U, n_out, mbar, halve, draws, slices):
         assert bad.size == 0, (s, bad[:10], err[bad[:10]])
 
 
+# mbar = 0: Subsample alone, without Compress2; E and the groups' coresets are the
+# points it keeps.
+NO_COMPRESS2 = [
+    dict(B=1, H=2, d=64, dtype="bf16", n_out=8, mbar=0, n=900, halve="kh"),
+    dict(B=1, H=1, d=32, dtype="fp32", n_out=16, mbar=0, n=700, halve="uniform"),
+]
+
+
+@pytest.mark.parametrize("c", NO_COMPRESS2, ids=lambda c: f"o{c['n_out']}-n{c['n']}-{c['dtype']}-{c['halve']}")
+def test_express_without_compress2(c):
+    test_express_decode_parity(c)
+    test_express_prefill_parity(c)
+
+
 def test_express_prefill_parity_at_the_benchmarked_setting():
     """The masked-prefill benchmark's setting (n_out = 256, mbar = 6 = h - 2,
     65536 points, d = 128, bf16) on two slices, every point's output: the
