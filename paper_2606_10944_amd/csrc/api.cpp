@@ -16,7 +16,6 @@
 
 namespace {
 
-constexpr int64_t kMaxBucket = 8192;  // the decision pass keeps a bucket's per-pair alpha in LDS
 constexpr int64_t kMaxRows = (int64_t)1 << 30;
 constexpr int64_t kMaxSlices = 65535;  // the per-slice kernels index slices by grid y
 
@@ -255,7 +254,7 @@ int compress_impl(const void* K, const void* V, int32_t dtype, int64_t B, int64_
   // the rows between the sinks and the window are thinned as a dataset of their own
   const int64_t nm = n - n_sinks - n_window;
   Levels lv;
-  if (!make_levels(nm, n_out, g, &lv) || lv.max_bucket > kMaxBucket) return THIN_EINVAL;
+  if (!make_levels(nm, n_out, g, &lv) || lv.max_bucket > thin::kMaxBucket) return THIN_EINVAL;
   if (!K || !V || !idx_out) return THIN_EINVAL;
   const int64_t S = B * H;
   const int64_t Utot = S * lv.U;
@@ -398,7 +397,7 @@ int compress_fixed(const void* K, const void* V, int32_t dtype, int64_t B, int64
   int rc = check_shape(B, H, n, d);
   if (rc) return rc;
   Levels lv;
-  if (!make_levels(n, n_out, g, &lv) || lv.max_bucket > kMaxBucket) return THIN_EINVAL;
+  if (!make_levels(n, n_out, g, &lv) || lv.max_bucket > thin::kMaxBucket) return THIN_EINVAL;
   const int64_t S = B * H;
   // the largest single bucket's scores (0 if every round is local), and
   // every region but the scores
@@ -678,7 +677,7 @@ int64_t seg_total(const thin::ExpressSegs& g) {
 int ex_check(int64_t B, int64_t H, int64_t d, int64_t n_out, int32_t mbar, int64_t n_max,
              int64_t* u_slice, int64_t* kmax, int64_t* draws) {
   if (B < 1 || H < 1 || B * H > kMaxSlices || !supported_d(d)) return THIN_EINVAL;
-  if (n_out < 1 || 4 * n_out > kMaxBucket || mbar < 0 || mbar > kExMaxL - 2) return THIN_EINVAL;
+  if (n_out < 1 || 4 * n_out > thin::kMaxBucket || mbar < 0 || mbar > kExMaxL - 2) return THIN_EINVAL;
   if (n_max < 1 || n_max > kMaxRows) return THIN_EINVAL;
   thin_express x{};
   x.n_out = n_out;
@@ -710,7 +709,7 @@ int thin_plan(int64_t B, int64_t H, int64_t n, int64_t d, int64_t n_out, int32_t
   int rc = check_shape(B, H, n, d);
   if (rc) return rc;
   Levels lv;
-  if (!make_levels(n, n_out, g, &lv) || lv.max_bucket > kMaxBucket) return THIN_EINVAL;
+  if (!make_levels(n, n_out, g, &lv) || lv.max_bucket > thin::kMaxBucket) return THIN_EINVAL;
   const int64_t S = B * H;
   memset(plan, 0, sizeof(*plan));
   plan->n_kept = lv.n_kept;

@@ -1541,20 +1541,20 @@ struct PassLds {
   static constexpr size_t kSlot = BP * 8 + 2 * BP * 4 + 2 * BP * CW * 16;
   static constexpr size_t kColBuf = COAL ? 64 * QW * 16 : 0;
   static_assert(2 + BW <= 16, "counter block");
-  __host__ __device__ static size_t mask_off(int P) { return ((size_t)P * 8 + 15) & ~(size_t)15; }
-  __host__ __device__ static size_t flag_off(int P) {
+  __host__ __device__ static constexpr size_t mask_off(int P) { return ((size_t)P * 8 + 15) & ~(size_t)15; }
+  __host__ __device__ static constexpr size_t flag_off(int P) {
     return mask_off(P) + (((size_t)(P + BP - 1) / BP * 4 + 15) & ~(size_t)15);
   }
-  __host__ __device__ static size_t slot_off(int P) { return flag_off(P) + 64; }
-  __host__ __device__ static size_t colbuf_off(int P) { return slot_off(P) + NSLOT * kSlot; }
+  __host__ __device__ static constexpr size_t slot_off(int P) { return flag_off(P) + 64; }
+  __host__ __device__ static constexpr size_t colbuf_off(int P) { return slot_off(P) + NSLOT * kSlot; }
   // pair scale exponents [P] f32 | largest row scale of every block [nblk] f32
-  __host__ __device__ static size_t h2_off(int P) { return colbuf_off(P) + BW * kColBuf; }
-  __host__ __device__ static size_t mb_off(int P) { return h2_off(P) + (((size_t)P * 4 + 15) & ~(size_t)15); }
+  __host__ __device__ static constexpr size_t h2_off(int P) { return colbuf_off(P) + BW * kColBuf; }
+  __host__ __device__ static constexpr size_t mb_off(int P) { return h2_off(P) + (((size_t)P * 4 + 15) & ~(size_t)15); }
   // rows of bulk sums completed per 64-pair chunk [nch] i32
-  __host__ __device__ static size_t chunk_off(int P) {
+  __host__ __device__ static constexpr size_t chunk_off(int P) {
     return mb_off(P) + (((size_t)(P + BP - 1) / BP * 4 + 15) & ~(size_t)15);
   }
-  __host__ __device__ static size_t bytes(int P) {
+  __host__ __device__ static constexpr size_t bytes(int P) {
     return chunk_off(P) + (((size_t)(P + 63) / 64 * 4 + 15) & ~(size_t)15);
   }
 };
@@ -2271,14 +2271,9 @@ hipError_t launch_decide(const HalveArgs& a0, int64_t nbk, hipStream_t st) {
   if (later <= 64) return launch_pass_w<1, 1, PASS_FD_S>(a, nbk, st);
   if (later <= 256) return launch_pass_w<2, 2, PASS_FD_S>(a, nbk, st);
   if (later <= 512) return launch_pass_w<PASS_BW_M, PASS_NCB_M, PASS_FD_M>(a, nbk, st);
-  // the large shape's column buffers take 9 KiB of LDS per bulk wave: past
-  // the 160 KiB of a CU (buckets above 4096 rows) eight bulk waves run, past
-  // that the medium shape
-  if (PassLds<PASS_BW_L, PASS_NCB_L, PASS_FD_L>::bytes((int)(a.N / 2)) <= kCuLds)
-    return launch_pass_w<PASS_BW_L, PASS_NCB_L, PASS_FD_L, true>(a, nbk, st);
-  if (PassLds<8, 3, 2>::bytes((int)(a.N / 2)) <= kCuLds)
-    return launch_pass_w<8, 3, 2, true>(a, nbk, st);
-  return launch_pass_w<PASS_BW_M, PASS_NCB_M, PASS_FD_M, true>(a, nbk, st);
+  using Large = PassLds<PASS_BW_L, PASS_NCB_L, PASS_FD_L>;
+  static_assert(Large::bytes(kMaxBucket / 2) <= kCuLds, "the large shape takes every bucket");
+  return launch_pass_w<PASS_BW_L, PASS_NCB_L, PASS_FD_L, true>(a, nbk, st);
 }
 
 hipError_t launch_vmax(int dtype, const void* V, int64_t S, int64_t n, int64_t ld, int64_t d,

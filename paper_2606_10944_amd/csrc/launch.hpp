@@ -6,6 +6,8 @@
 
 namespace thin {
 
+constexpr int64_t kMaxBucket = 8192;  // the decision pass keeps a bucket's per-pair alpha in LDS
+
 // One Halve round over buckets b0 .. b0 + nbk - 1 (bucket = slice * G + t).
 struct HalveArgs {
   const void* K;
