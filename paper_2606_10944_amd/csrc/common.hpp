@@ -150,20 +150,6 @@ __device__ __forceinline__ floatx4_t mma_word<float>(const uint4& a, const uint4
   return acc;
 }
 
-// acc += A_word x B_word using only k-slot 0 of lane group 0 (one MFMA).
-template <typename T>
-__device__ __forceinline__ floatx4_t mma_aug(const uint4& a, const uint4& b, floatx4_t acc);
-
-template <>
-__device__ __forceinline__ floatx4_t mma_aug<bf16_t>(const uint4& a, const uint4& b, floatx4_t acc) {
-  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a),
-                                                 __builtin_bit_cast(bf16x8_t, b), acc, 0, 0, 0);
-}
-template <>
-__device__ __forceinline__ floatx4_t mma_aug<float>(const uint4& a, const uint4& b, floatx4_t acc) {
-  return __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a.x), __uint_as_float(b.x), acc, 0, 0, 0);
-}
-
 // 64 lanes x 16 bytes from global memory straight into LDS: lane l's 16 bytes
 // at g go to LDS byte lds + 16 l (lds uniform over the wave).  Counted in
 // vmcnt, which the caller waits on: the compiler does not see the copy, only

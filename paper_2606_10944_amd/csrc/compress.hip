@@ -512,13 +512,9 @@ constexpr int score_waves() {
 // pair i >= p has been added; decisions past the block's npb pairs are
 // dropped.  With NEAR, en[i] = E(i, q) for a pair q of the next block, and
 // near receives q's signed sum over the block (float32, in ascending i).
-#ifndef DECIDE_ASM
-#define DECIDE_ASM 1
-#endif
 template <bool NEAR>
 __device__ __forceinline__ uint32_t decide_block(double alpha, double thr, const float* ef,
                                                  const float* en, int npb, float& near) {
-#if DECIDE_ASM
   // One step: compare (vector, into VCC), test bit i of VCC (scalar, into
   // SCC), select +-1.0 as a float64 pair on SCC, FMA; then, off the chain,
   // the float32 +-1 for the signed sum and the decision shifted into a
@@ -545,19 +541,6 @@ __device__ __forceinline__ uint32_t decide_block(double alpha, double thr, const
     if (NEAR) near = __builtin_fmaf(en[i], sf, near);
   }
   uint32_t smask = __builtin_bitreverse32(rmask);
-#else
-  uint32_t smask = 0;
-#pragma unroll
-  for (int i = 0; i < 32; ++i) {
-    const double e = (double)ef[i];
-    const uint32_t d = (uint32_t)(__ballot(alpha < thr) >> i) & 1u;
-    smask |= d << i;
-    // +-1 built as bits (the sign bit from d): scalar integer operations
-    // only, no select between two vector values
-    alpha = __builtin_fma(e, __hiloint2double((int)(0x3ff00000u | (d << 31)), 0), alpha);
-    if (NEAR) near = __builtin_fmaf(en[i], __uint_as_float(0x3f800000u | (d << 31)), near);
-  }
-#endif
   if (npb < 32) smask &= (1u << npb) - 1u;
   return smask;
 }
