@@ -194,10 +194,12 @@ hipError_t observed(int32_t kernel, int32_t round, hipStream_t st, F&& launch) {
 }
 
 // One KH round over the S*G buckets described by `a`: one local launch for
-// buckets up to the local kernel's size (however many: with 4096 buckets of
+// buckets up to the local kernel's size, however many (with 4096 buckets of
 // 256 rows the local launch beats scores + decisions by ~5 %, with 16384 of
-// 16 rows or 4096 of 64 rows by 2-2.5x), else pair scores then decisions, in
-// as many launches as the score region (e_bytes) needs.
+// 16 rows or 4096 of 64 rows by 2-2.5x), but for float rounds of few buckets of
+// 129 to 256 rows (halve_spread), where the score region has room for all their
+// scores; else pair scores then decisions, in as many launches as the score
+// region (e_bytes) needs.
 hipError_t kh_round(int32_t dtype, int64_t d, thin::HalveArgs a, int64_t buckets, size_t e_bytes,
                     int32_t r, hipStream_t st) {
   if (a.N <= thin::halve_local_rows(dtype, d) &&

@@ -1405,9 +1405,9 @@ __global__ __launch_bounds__(64 * kTinyWaves) void tiny_halve_kernel(HalveArgs a
 //    against the next block's pairs, the row indices, and the thresholds
 //    a(1 - 2u), which depend on no decision (the running maximum of b over
 //    the bucket is carried from block to block);
-//  - wave 0 (decider) takes the decisions of a block two at a time (the
-//    second decision is evaluated for both outcomes of the first), publishes
-//    them, then adds the block's scores to the next block's pairs itself;
+//  - wave 0 (decider) takes the decisions of a block one after the other
+//    (decide_block), with the block's signed scores against the next block's
+//    pairs summed beside them, and publishes them;
 //  - waves 2.. (bulk) add each decided block's scores to all pairs two or
 //    more blocks later.  Each pair belongs to one bulk wave (64-pair chunks,
 //    dealt round robin), which adds the blocks in order; the column chunks
@@ -1512,9 +1512,10 @@ struct PassLds {
   // last decided block, last staged block, rows completed by each bulk wave |
   // NSLOT input slots, each: thresholds [BP] f64, rows [2][BP] i32, own
   // scores [BP][CW] and next-block scores [BP][CW] 16-byte words | with
-  // COAL, per bulk wave a column buffer [64][CW] 16-byte words.  A column of
-  // BP scores is QW words plus one of padding (CW): reads of whole columns
-  // by consecutive lanes then fall in different banks.  COAL: the bulk waves
+  // COAL, per bulk wave a column buffer [2][64][QW / 2] of 16-byte words, the
+  // four words of a column's half permuted (PASS_TURN).  A slot's column of BP
+  // scores is QW words plus one of padding (CW): reads of whole columns by
+  // consecutive lanes then fall in different banks.  COAL: the bulk waves
   // load their chunks coalesced and transpose them in LDS (with six bulk
   // waves, on the largest buckets, the loads limit the bulk); else each lane
   // loads its own column: less LDS, and the decider's LDS accesses do not
@@ -1783,12 +1784,12 @@ __global__ __launch_bounds__(64 * (BW + 2)) void halve_pass_kernel(HalveArgs a) 
       anear = ldexp((double)near, (int)scale_shift(mBm, s_h2[min((m + 1) * BP + pl, P - 1)]));
     }
   } else if (wave == 1) {
-    // ---- fetcher: block m's inputs into slot m % 3 ----
+    // ---- fetcher: block m's inputs into slot m % NSLOT ----
     // Lane l fetches word l%QW of the columns of pairs l/QW + 8r (r < 4) of
     // the block's own scores and of its scores against the next block; lanes
     // < BP also the pair terms, uniform and rows of pair l.  Lanes past a
-    // block's last pair read that pair's inputs.  One block is fetched while
-    // the previous one is staged.
+    // block's last pair read that pair's inputs.  The loads of FD blocks are in
+    // flight.
     __builtin_amdgcn_s_setprio(2);
     u32x4 fo[FD][4], fn[FD][4];
     float flbt[FD], fh2[FD], fu[FD];
@@ -1856,9 +1857,9 @@ __global__ __launch_bounds__(64 * (BW + 2)) void halve_pass_kernel(HalveArgs a) 
     // chunk): each consumed slot is refilled at once with the item NCB later,
     // so the loads run ahead whatever the decisions.  Lane l sums column l of
     // the chunk in ascending order (the order of the decider's sums); with
-    // COAL the chunk is loaded a score tile (8 columns, 1 KiB) per
-    // instruction, 8 lanes to a column, and turned through the wave's LDS
-    // column buffer.  After row b of chunk c the wave publishes b + 1 in
+    // COAL the chunk is loaded 16 pairs x 16 scores (1 KiB in a row) per
+    // instruction, 4 lanes to a pair, and turned through the wave's LDS column
+    // buffer (PASS_LOAD, PASS_TURN).  After row b of chunk c the wave publishes b + 1 in
     // s_chunk[c] (rows completed).  With helpers, a chunk a helper has
     // claimed starts from the helper's partial alpha over rows
     // 0 .. hand_row(c) (taken from galpha once the chunk's flag is "done")
@@ -1890,9 +1891,8 @@ __global__ __launch_bounds__(64 * (BW + 2)) void halve_pass_kernel(HalveArgs a) 
       ic = live ? fc : nch;
       ih = live && fh;
       fh = false;
-      // COAL: word lane % QW of column 8 k + lane / QW of the chunk; else
-      // word k of column lane (past the stream's end: valid columns, never
-      // used)
+      // COAL: as PASS_LOAD says; else word k of column lane (past the stream's
+      // end: valid columns, never used)
       if constexpr (L::COAL) {
 #pragma unroll
         for (int k = 0; k < 8; ++k) dst[k] = PASS_LOAD(live ? fb : 0, live ? 64 * fc : 0, k);
