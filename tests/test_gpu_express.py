@@ -3,6 +3,7 @@ CPU oracle: every point's output (max-abs 2e-3 for bf16 inputs, 1e-5 for
 fp32) and the final weighted cache (indices bit-exact, KH decisions in
 follow mode at a 1e-5 relative margin as for the compress path; uniform
 halving bit-exact including its swap bits)."""
+import ctypes as C
 from concurrent.futures import ThreadPoolExecutor
 
 import numpy as np
@@ -13,6 +14,7 @@ import oracle
 from paper_2606_10944_amd import (ExpressCache, thin_express_plan, thin_express_prefill,
                                   thin_express_prefill_plan, workspace_status)
 from paper_2606_10944_amd import workloads as W
+from paper_2606_10944_amd._lib import lib
 
 pytestmark = pytest.mark.gpu
 DEV = torch.device("cuda:0")
@@ -82,6 +84,23 @@ def test_express_decode_parity(c):
         err = np.abs(r["O"] - O[b, h]).max()
         assert err <= tol, (s, err)
     print(f"near ties {near}")
+
+
+# Float KH calls that no local launch takes: Halve phases of 256 and 512 points,
+# Compress2 groups of 256 (several per prefill launch, each with a v_max of its
+# own), scores by units of 32 x 32.
+FLOAT_ROUNDS = [
+    dict(B=1, H=2, d=64, dtype="fp32", n_out=64, mbar=1, n=700, halve="kh"),
+    dict(B=1, H=2, d=64, dtype="fp32", n_out=128, mbar=1, n=2100, halve="kh"),
+    dict(B=2, H=1, d=128, dtype="fp32", n_out=128, mbar=2, n=2100, halve="kh"),
+    dict(B=1, H=2, d=32, dtype="fp32", n_out=128, mbar=1, n=2100, halve="kh"),
+]
+
+
+@pytest.mark.parametrize("c", FLOAT_ROUNDS, ids=lambda c: f"o{c['n_out']}-mbar{c['mbar']}-d{c['d']}")
+def test_express_float_rounds(c):
+    test_express_decode_parity(c)
+    test_express_prefill_parity(c)
 
 
 # A step's columns of V over four, two and one workgroups per slice (up to 64,
@@ -180,3 +199,59 @@ def test_express_prefill_parity_at_the_benchmarked_setting():
     draws = torch.from_numpy(np.random.default_rng(8).random(
         max(plan["subsample_draws"], 1)).astype(np.float32))
     _check_prefill(w, Q, K, V, U, n_out, mbar, "kh", draws, range(w.S))
+
+
+class _Seg(C.Structure):
+    _fields_ = [("src", C.c_void_p), ("stride", C.c_int64), ("start", C.c_int64),
+                ("len", C.c_int64), ("logw", C.c_float)]
+
+
+class _Segs(C.Structure):
+    _fields_ = [("seg", _Seg * 34), ("n", C.c_int)]
+
+
+@pytest.mark.parametrize("nseg,d,dtype", [(12, 64, "bf16"), (13, 64, "bf16"), (13, 128, "fp32"),
+                                          (33, 32, "bf16"), (34, 128, "bf16")])
+def test_decode_attention_of_many_segments(nseg, d, dtype):
+    """The step's attention over up to as many segments as an Express cache can
+    have.  More than 12 take an argument of another size, which through the public
+    calls only caches of over four million points reach (Compress2 depth 11), so
+    the library's launcher is called itself."""
+    launch = getattr(lib(), "_ZN4thin23launch_decode_attentionEiliPKvS1_S1_RKNS_11ExpressSegsE"
+                            "lllPfPvPiliP12ihipStream_t")
+    launch.restype = C.c_int
+    launch.argtypes = [C.c_int, C.c_int64, C.c_int, C.c_void_p, C.c_void_p, C.c_void_p,
+                       C.POINTER(_Segs), C.c_int64, C.c_int64, C.c_int64, C.c_void_p, C.c_void_p,
+                       C.c_void_p, C.c_int64, C.c_int, C.c_void_p]
+    S, n = 3, 700
+    gen = torch.Generator().manual_seed(nseg)
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    q, K, V = (torch.randn(S, r, d, generator=gen).to(dt) for r in (1, n, n))
+    lens = [0, 1] + [1 + (7 * k) % 23 for k in range(nseg - 2)]
+    segs = _Segs(n=nseg)
+    rows, logw, lists = [], [], []
+    for k, ln in enumerate(lens):
+        w = -0.25 * (k % 5)
+        if k % 3 == 1:  # rows start .. start + len - 1
+            segs.seg[k] = _Seg(None, 0, 11 * k, ln, w)
+            r = torch.arange(11 * k, 11 * k + ln, dtype=torch.int32).expand(S, ln)
+        else:
+            r = torch.randint(0, n, (S, ln + 3), generator=gen, dtype=torch.int32)
+            lists.append(r.to(DEV))
+            segs.seg[k] = _Seg(lists[-1].data_ptr(), ln + 3, 0, ln, w)
+            r = r[:, :ln]
+        rows.append(r)
+        logw += [w] * ln
+    rows, m = torch.cat(rows, dim=1).long(), sum(lens)
+    qd, Kd, Vd = q.to(DEV), K.to(DEV), V.to(DEV)
+    O = torch.full((S, d), float("nan"), device=DEV)
+    rc = launch(0 if dtype == "fp32" else 1, d, 0, qd.data_ptr(), Kd.data_ptr(), Vd.data_ptr(),
+                C.byref(segs), S, n, m, None, O.data_ptr(), None, 0, 0,
+                torch.cuda.current_stream().cuda_stream)
+    assert rc == 0
+    torch.cuda.synchronize()
+    for s in range(S):
+        x = K[s].double()[rows[s]] @ q[s, 0].double() / d ** 0.5 + torch.tensor(logw).double()
+        ref = torch.softmax(x, 0) @ V[s].double()[rows[s]]
+        err = (ref - O[s].cpu().double()).abs().max().item()
+        assert err <= (2e-3 if dtype == "bf16" else 1e-5), (s, err)
