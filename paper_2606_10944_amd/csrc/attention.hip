@@ -564,13 +564,9 @@ __global__ __launch_bounds__(64 * WR) void coreset_attn_res_kernel(
 }
 
 constexpr int64_t kDeviceCus = 256;
-// Waves per workgroup of the resident kernel, up to 128 keys and above
-#ifndef ATTN_RES_WAVES
-#define ATTN_RES_WAVES 4
-#endif
-#ifndef ATTN_RES_WAVES_BIG
-#define ATTN_RES_WAVES_BIG 8
-#endif
+// waves per workgroup of the resident kernel, up to 128 keys and above
+constexpr int kResWaves = 4;
+constexpr int kResWavesBig = 8;
 
 template <int D, int NKT, int QTR, int WR, int H, typename TO, bool W>
 hipError_t launch_attn_res_w(const void* Q, const void* K, const void* V, const int32_t* idx,
@@ -620,10 +616,10 @@ hipError_t launch_attn_res_big(const void* Q, const void* K, const void* V, cons
     static_assert(ResLds<D, NKT>::bytes > 80 * 1024, "one workgroup per CU");
     const TilePlan plan = attn_tile_plan(S, n_q, kDeviceCus);
     if (plan.tiles == 2)
-      return launch_attn_res<D, NKT, 2, ATTN_RES_WAVES_BIG, 2, TO>(Q, K, V, idx, logw, S, n, n_q, n_out, O, st, plan.split.run);
-    return launch_attn_res<D, NKT, 1, ATTN_RES_WAVES_BIG, 1, TO>(Q, K, V, idx, logw, S, n, n_q, n_out, O, st, plan.split.run);
+      return launch_attn_res<D, NKT, 2, kResWavesBig, 2, TO>(Q, K, V, idx, logw, S, n, n_q, n_out, O, st, plan.split.run);
+    return launch_attn_res<D, NKT, 1, kResWavesBig, 1, TO>(Q, K, V, idx, logw, S, n, n_q, n_out, O, st, plan.split.run);
   } else {
-    return launch_attn_res<D, NKT, 1, ATTN_RES_WAVES_BIG, 1, TO>(Q, K, V, idx, logw, S, n, n_q, n_out, O, st);
+    return launch_attn_res<D, NKT, 1, kResWavesBig, 1, TO>(Q, K, V, idx, logw, S, n, n_q, n_out, O, st);
   }
 }
 
@@ -632,10 +628,10 @@ hipError_t launch_attn_res_d(int64_t n_out, const void* Q, const void* K, const 
                              const int32_t* idx, const float* logw, int64_t S, int64_t n,
                              int64_t n_q, void* O, hipStream_t st, bool* used) {
   *used = true;
-  if (n_out <= 32) return launch_attn_res<D, 2, 1, ATTN_RES_WAVES, 1, TO>(Q, K, V, idx, logw, S, n, n_q, n_out, O, st);
-  if (n_out <= 64) return launch_attn_res<D, 4, 1, ATTN_RES_WAVES, 1, TO>(Q, K, V, idx, logw, S, n, n_q, n_out, O, st);
-  if (n_out <= 96) return launch_attn_res<D, 6, 1, ATTN_RES_WAVES, 1, TO>(Q, K, V, idx, logw, S, n, n_q, n_out, O, st);
-  if (n_out <= 128) return launch_attn_res<D, 8, 1, ATTN_RES_WAVES, 1, TO>(Q, K, V, idx, logw, S, n, n_q, n_out, O, st);
+  if (n_out <= 32) return launch_attn_res<D, 2, 1, kResWaves, 1, TO>(Q, K, V, idx, logw, S, n, n_q, n_out, O, st);
+  if (n_out <= 64) return launch_attn_res<D, 4, 1, kResWaves, 1, TO>(Q, K, V, idx, logw, S, n, n_q, n_out, O, st);
+  if (n_out <= 96) return launch_attn_res<D, 6, 1, kResWaves, 1, TO>(Q, K, V, idx, logw, S, n, n_q, n_out, O, st);
+  if (n_out <= 128) return launch_attn_res<D, 8, 1, kResWaves, 1, TO>(Q, K, V, idx, logw, S, n, n_q, n_out, O, st);
   // (192 = n_out 128 plus 32 sinks and a 32-row window)
   if (n_out <= 192) return launch_attn_res_big<D, 12, TO>(Q, K, V, idx, logw, S, n, n_q, n_out, O, st);
   if (n_out <= 256) return launch_attn_res_big<D, 16, TO>(Q, K, V, idx, logw, S, n, n_q, n_out, O, st);

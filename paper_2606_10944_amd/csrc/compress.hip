@@ -458,10 +458,8 @@ __host__ __device__ inline int half_run(int u, int NT) { return 2 * u + 1 < NT ?
 // rows x 64 slices 455 -> 383 us.
 constexpr int kScoreChunk = 16;
 constexpr int kScoreChunkMax = 32;
-#ifndef SCORE_MIN_WGS
-#define SCORE_MIN_WGS 128
-#endif
-constexpr int64_t kScoreMinWorkgroups = SCORE_MIN_WGS;  // half the CUs
+constexpr int64_t kScoreMinWorkgroups = 128;  // half the CUs
+constexpr int64_t kScoreSets = 16;  // buckets of an XCD whose workgroups are interleaved
 constexpr int64_t kScoreLongWorkgroups = 1024;         // four per CU
 constexpr int kScoreRowsStaged = kScoreChunkMax * 32;  // rows of a streamed chunk, at most
 // A score tile (8 column pairs x 32 row pairs) in the local kernel's LDS:
@@ -1278,10 +1276,7 @@ __global__ __launch_bounds__(64 * kUnitWaves) void score_units_kernel(HalveArgs 
 // leaves most of them idle (the prefill's Compress2 calls are 16-row buckets,
 // 98304 of them in one launch).  RT = 16-row tiles per bucket (N <= 16 RT).
 constexpr int kTinyWaves = 8;
-#ifndef TINY_MIN_BUCKETS
-#define TINY_MIN_BUCKETS 1024
-#endif
-constexpr int64_t kTinyMinBuckets = TINY_MIN_BUCKETS;  // launches with fewer take the local kernel
+constexpr int64_t kTinyMinBuckets = 1024;  // launches with fewer take the local kernel
 constexpr int kTinyStride = 33;  // floats per score row in LDS (rows i, columns p)
 
 template <typename T, int D, int RT>
@@ -1439,10 +1434,7 @@ __device__ __forceinline__ void publish(int* flag, int value) {
 // workgroups, the last kPassHand rows before the chunk's first block by the
 // bucket's own bulk waves (the hand-over then has kPassHand + 1 blocks of
 // decisions to arrive before the decider needs the chunk).
-#ifndef PASS_HAND
-#define PASS_HAND 10
-#endif
-constexpr int kPassHand = PASS_HAND;
+constexpr int kPassHand = 10;
 __device__ __forceinline__ int hand_row(int c) { return 2 * c - 2 - kPassHand; }
 // Every access to the words the helpers share with the bucket's workgroup
 // (decisions, flags, partials) is a read-modify-write atomic at agent scope:
@@ -1975,9 +1967,6 @@ __global__ __launch_bounds__(64) void gram16_kernel(const T* rows, float* out) {
 // Buckets interleaved per XCD in a score launch (at most the XCD's share):
 // enough to stagger the workgroups' ends, few enough that their rows stay in
 // the XCD's L2.
-#ifndef SCORE_IL
-#define SCORE_IL 16
-#endif
 template <typename T, int D>
 hipError_t launch_scores_td(const HalveArgs& a0, int64_t nbk, hipStream_t st) {
   if constexpr (Elem<T>::bytes == 4) {
@@ -2034,7 +2023,7 @@ hipError_t launch_scores_td(const HalveArgs& a0, int64_t nbk, hipStream_t st) {
     x.own = own;
     x.nbk = nbk;
     x.ipb = (int32_t)((own ? groups : 0) + (stream ? streamed(a.ch) : 0));
-    x.il = (int32_t)std::min<int64_t>(SCORE_IL, (nbk + 7) / 8);
+    x.il = (int32_t)std::min<int64_t>(kScoreSets, (nbk + 7) / 8);
     const int64_t per_xcd = ((nbk + 7) / 8 + x.il - 1) / x.il * x.il;
     const int64_t wgs = 8 * per_xcd * x.ipb;
     // a launch of own chunks only takes the own-only instantiation
@@ -2233,30 +2222,17 @@ hipError_t launch_local(int dtype, int64_t d, const HalveArgs& a, int64_t nbk, h
 // (64 buckets of 2048 rows on the long workload), where ten bulk waves keep
 // the decider fed (round 3 there: 69.7 -> 58.7 us against six); a deeper
 // fetcher gained nothing.
-#ifndef PASS_FD_S
-#define PASS_FD_S 2
-#endif
-#ifndef PASS_BW_M
-#define PASS_BW_M 6
-#define PASS_NCB_M 3
-#define PASS_FD_M 2
-#endif
-#ifndef PASS_BW_L
-#define PASS_BW_L 10
-#define PASS_NCB_L 3
-#define PASS_FD_L 2
-#endif
 hipError_t launch_decide(const HalveArgs& a0, int64_t nbk, hipStream_t st) {
   const HalveArgs a = with_layout(a0);
   // bulk waves x prefetched chunks x 64 pairs should cover the pairs after
   // the first two blocks
   const int64_t later = a.N / 2 - 64;
-  if (later <= 64) return launch_pass_w<1, 1, PASS_FD_S>(a, nbk, st);
-  if (later <= 256) return launch_pass_w<2, 2, PASS_FD_S>(a, nbk, st);
-  if (later <= 512) return launch_pass_w<PASS_BW_M, PASS_NCB_M, PASS_FD_M>(a, nbk, st);
-  using Large = PassLds<PASS_BW_L, PASS_NCB_L, PASS_FD_L>;
+  if (later <= 64) return launch_pass_w<1, 1, 2>(a, nbk, st);
+  if (later <= 256) return launch_pass_w<2, 2, 2>(a, nbk, st);
+  if (later <= 512) return launch_pass_w<6, 3, 2>(a, nbk, st);
+  using Large = PassLds<10, 3, 2>;
   static_assert(Large::bytes(kMaxBucket / 2) <= kCuLds, "the large shape takes every bucket");
-  return launch_pass_w<PASS_BW_L, PASS_NCB_L, PASS_FD_L, true>(a, nbk, st);
+  return launch_pass_w<10, 3, 2, true>(a, nbk, st);
 }
 
 hipError_t launch_vmax(int dtype, const void* V, int64_t S, int64_t n, int64_t ld, int64_t d,

@@ -106,10 +106,7 @@ __global__ void express_keys_kernel(ExpressSegs segs, int64_t m, int64_t out_str
 // writes the output row itself (one launch per step); else it writes its
 // unnormalised partial (max, sum, acc[D]) and a second kernel merges them.
 // ---------------------------------------------------------------------------
-#ifndef DEC_WAVES
-#define DEC_WAVES 16
-#endif
-constexpr int kDecWaves = DEC_WAVES;
+constexpr int kDecWaves = 16;
 constexpr int kDecUnroll = 8;
 constexpr int64_t kDecMaxWorkgroups = 256;  // one per CU
 

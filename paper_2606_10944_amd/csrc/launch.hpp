@@ -160,10 +160,7 @@ hipError_t launch_express_keys(const ExpressSegs& segs, int64_t S, int64_t m, in
 // the output itself, else a second launch merges their partials (S * split *
 // (d + 2) floats in `part`).  The last launch also writes app_val to
 // app[s * app_stride] when app is non-null.
-#ifndef DEC_KPG
-#define DEC_KPG 1024
-#endif
-constexpr int kDecodeKeysPerGroup = DEC_KPG;
+constexpr int kDecodeKeysPerGroup = 1024;
 constexpr int kDecodeMaxSplit = 16;
 int decode_attention_split(int64_t m);
 hipError_t launch_decode_attention(int dtype, int64_t d, int out_dtype, const void* Q,
