@@ -1071,6 +1071,9 @@ void pair_scores_kernel(HalveArgs a) {
     // then V words), c = wave, wave + W, ...; lane l of word v brings the
     // row's 16-byte word 4 v + l / 16.
     constexpr int L = SS::LPT, NS = SS::STAGES;
+    // The waits below count operations: a wave's copies of a tile must be L (or
+    // none, in waves that copy nothing), its stores of a tile one.
+    static_assert(2 * CH % W == 0 || 2 * CH < W, "as many copies in every wave that copies");
     const uint32_t ring = lds_offset(smem);
     auto issue = [&](int tt, int st) {
 #pragma unroll
