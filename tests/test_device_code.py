@@ -51,3 +51,24 @@ def test_copy_to_lds_tells_the_compiler_that_it_changes_m0(tmp_path):
     text = _assembly(tmp_path, M0_PROBE)
     ops = re.findall(r"^\s*(s_mov_b32 m0|global_load_lds_dwordx4)", text, re.M)
     assert ops == ["s_mov_b32 m0", "global_load_lds_dwordx4"] * 3, ops
+
+
+def test_decision_pass_loads_do_not_wait_for_those_in_flight(tmp_path):
+    """The decision pass keeps several blocks' loads in flight.  A load address
+    that the compiler forms in a branch ends in a wait for all of them, right
+    before the next load."""
+    try:
+        hip_build.hipcc()
+    except RuntimeError:
+        pytest.skip("no hipcc")
+    with open(os.path.join(CSRC, "compress.hip")) as f:
+        text = _assembly(tmp_path, f.read())
+    kernels = re.findall(r"^_Z\S*halve_pass_kernel\S*:[^\n]*\n(.*?)^\.Lfunc_end", text, re.M | re.S)
+    assert len(kernels) == 5
+    for k in kernels:
+        ops = [x.split(";")[0].strip() for x in k.split("\n")]
+        ops = [x for x in ops if x and not x.startswith(".") and not x.endswith(":")]
+        for i, op in enumerate(ops):
+            if op.startswith("global_load_dwordx4"):
+                before = ops[max(0, i - 8): i]
+                assert not any("vmcnt(0)" in x for x in before), before
