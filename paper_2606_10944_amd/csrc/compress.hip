@@ -1305,6 +1305,10 @@ __global__ __launch_bounds__(64 * kTinyWaves) void tiny_halve_kernel(HalveArgs a
   __shared__ float s_h2p[kTinyWaves][32], s_lbt[kTinyWaves][32];
   float* e = s_e[wave];
 
+  // v_max of the slice (requested before the rows, whose wait then covers it:
+  // 8192 buckets of 16 bf16 rows, d = 128, 18.4 -> 16.4 us) or, below, of the bucket's
+  // own rows
+  float vmax = a.vmax_own ? 0.0f : __uint_as_float(a.vmax_bits[a.vmax_per_bucket ? bucket : s]);
   // rows and their fragments
   int64_t ar[RT];
   uint4 Ak[RT][NV], Av[RT][NV];
@@ -1319,13 +1323,7 @@ __global__ __launch_bounds__(64 * kTinyWaves) void tiny_halve_kernel(HalveArgs a
     load_frag<T, D>(K, valid ? ar[rt] : 0, g, valid, Ak[rt]);
     load_frag<T, D>(V, valid ? ar[rt] : 0, g, valid, Av[rt]);
   }
-  // v_max of the slice, or of the bucket's own rows
-  float vmax;
-  if (a.vmax_own) {
-    vmax = __uint_as_float(wave_max_u(frag_absmax<T>(Av)));
-  } else {
-    vmax = __uint_as_float(a.vmax_bits[a.vmax_per_bucket ? bucket : s]);
-  }
+  if (a.vmax_own) vmax = __uint_as_float(wave_max_u(frag_absmax<T>(Av)));
   const float vm2f = vmax * vmax;
   const double vm2d = (double)vmax * (double)vmax;
   // pair terms; the block's largest row scale (rows past the bucket: 0)
