@@ -65,7 +65,7 @@ template <typename T, int D, typename TO, bool W, int QT, bool ONE>
 __global__ __launch_bounds__(64 * WAVES) void coreset_attn_kernel(
     const T* __restrict__ Q, const T* __restrict__ K, const T* __restrict__ V,
     const int32_t* __restrict__ idx, const float* __restrict__ logw, int64_t n, int64_t n_q,
-    int n_out, TO* __restrict__ O) {
+    int n_out, int extra, TO* __restrict__ O) {
   constexpr int NV = Frag<T, D>::NV;
   constexpr bool BF = Elem<T>::bytes == 2;
   using L = AttnLds<T, D>;
@@ -76,7 +76,15 @@ __global__ __launch_bounds__(64 * WAVES) void coreset_attn_kernel(
 
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int m16 = lane & 15, g = lane >> 4;
-  const int64_t s = blockIdx.y;
+  // the slice, and which of its workgroups this is; ONE with `extra` workgroups
+  // per slice that have a block more than the others: dealt so that those come first
+  int64_t s = blockIdx.y;
+  int64_t first = blockIdx.x + (int64_t)gridDim.x * blockIdx.z;
+  if (ONE && extra) {
+    const Share sh = share_of(blockIdx.x + gridDim.x * blockIdx.y, gridDim.y, gridDim.x, extra);
+    s = sh.slice;
+    first = sh.part;
+  }
   const float* Ws = W ? logw + s * (int64_t)n_out : nullptr;
   const float sqrt_d = (float)sqrt((double)D);
   const T* Ks = K + s * n * D;
@@ -88,7 +96,6 @@ __global__ __launch_bounds__(64 * WAVES) void coreset_attn_kernel(
   // ONE: a coreset of one chunk, staged for the first of the workgroup's blocks
   // of queries (as many apart as there are workgroups) and kept; else one block.
   const int64_t nqb = (n_q + 16 * QT * WAVES - 1) / (16 * QT * WAVES);
-  const int64_t first = blockIdx.x + (int64_t)gridDim.x * blockIdx.z;
   for (int64_t qb = first; qb < nqb; qb += (int64_t)gridDim.x * gridDim.z) {
     const int64_t q0 = qb * (16 * QT * WAVES) + wave * 16 * QT;
     uint4 Bq[QT][NV];
@@ -1279,9 +1286,10 @@ hipError_t launch_attn_t(const void* Q, const void* K, const void* V, const int3
   const int64_t blocks = (n_q + per - 1) / per;
   auto launch = [&](auto kern, int64_t wgs) {
     const GridRows g = grid_rows(wgs, 64 * WAVES);
+    const int extra = g.rows == 1 ? (int)(blocks % wgs) : 0;
     hipLaunchKernelGGL(kern, dim3((unsigned)g.x, (unsigned)S, (unsigned)g.rows), dim3(64 * WAVES),
                        0, st, (const T*)Q, (const T*)K, (const T*)V, idx, logw, n, n_q, (int)n_out,
-                       (TO*)O);
+                       extra, (TO*)O);
   };
   // One chunk of float keys: several blocks of queries per workgroup.  (bf16
   // rows come here with d = 32 or more than 256 keys only; over one chunk of

@@ -66,6 +66,21 @@ inline int64_t split_blocks(int64_t S, int64_t blocks, int64_t slots) {
   return best;
 }
 
+// Workgroup `id` of S * parts, where `extra` of a slice's parts have a block more
+// than the others: those come first.  Workgroups go to the CUs in turn, so every
+// CU gets as many of them (slice after slice, part after part, they all fell on
+// the same CUs where 256 is about a multiple of the parts; float rows, 16 keys: 20
+// x 4097 queries, d = 64, 24.8 -> 19.7 us, d = 32 13.5 -> 11.9), and the longest
+// start first.
+struct Share {
+  uint32_t slice, part;
+};
+constexpr Share share_of(uint32_t id, uint32_t S, uint32_t parts, uint32_t extra) {
+  const uint32_t longer = S * extra;
+  if (id < longer) return {id / extra, id % extra};
+  return {(id - longer) / (parts - extra), extra + (id - longer) % (parts - extra)};
+}
+
 // Attention over 129 to 256 keys of d = 128 (one workgroup per CU): a step is
 // 128 queries with one query tile per wave, or 256 with two, which read each
 // fragment of the coreset once for both and so take 1.75 times as long as one

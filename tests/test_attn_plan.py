@@ -27,6 +27,11 @@ void tile_plan(int64_t S, int64_t n_q, int64_t slots, int64_t* out) {
 int64_t split_blocks(int64_t S, int64_t blocks, int64_t slots) {
   return thin::split_blocks(S, blocks, slots);
 }
+void share_of(uint32_t id, uint32_t S, uint32_t parts, uint32_t extra, uint32_t* out) {
+  const thin::Share s = thin::share_of(id, S, parts, extra);
+  out[0] = s.slice;
+  out[1] = s.part;
+}
 }
 """
 
@@ -141,3 +146,23 @@ def test_blocks_of_one_chunk_of_keys_fill_the_device(plan, S, slots):
 ])
 def test_blocks_of_one_chunk_of_keys_of_known_sizes(plan, S, blocks, slots, want):
     assert plan.split_blocks(C.c_int64(S), C.c_int64(blocks), C.c_int64(slots)) == want
+
+
+@pytest.mark.parametrize("S,n_q,slots", [(20, 4097, 1024), (20, 4097, 1280), (40, 2049, 1280),
+                                         (50, 1500, 1024), (100, 1000, 1280), (3, 300 * 64 + 1, 512),
+                                         (40, 33 * 64, 1024), (1, 4097 * 64, 1024)])
+def test_shares_of_one_chunk_of_keys_are_dealt_evenly(plan, S, n_q, slots):
+    """Every part of every slice once, and no CU (workgroups in turn) with more
+    than one longer share beyond the others'."""
+    blocks = _ceil(n_q, 64)
+    parts = plan.split_blocks(C.c_int64(S), C.c_int64(blocks), C.c_int64(slots))
+    extra = blocks % parts
+    assert extra > 0
+    out = (C.c_uint32 * 2)()
+    seen, longer = set(), [0] * 256
+    for i in range(S * parts):
+        plan.share_of(C.c_uint32(i), C.c_uint32(S), C.c_uint32(parts), C.c_uint32(extra), out)
+        seen.add((out[0], out[1]))
+        longer[i % 256] += out[1] < extra
+    assert seen == {(s, p) for s in range(S) for p in range(parts)}
+    assert max(longer) - min(longer) <= 1
