@@ -2,6 +2,7 @@
 // moves, the per-call v_max of a Halve call and the layout of the weighted
 // key list a point attends over (Alg. 5).  The Halve calls themselves are
 // the KH rounds of compress.hip, one bucket per slice.
+#include "attn_plan.hpp"
 #include "common.hpp"
 #include "launch.hpp"
 
@@ -33,9 +34,11 @@ constexpr int kVmaxWaves = 16;
 template <typename T>
 __global__ __launch_bounds__(64 * kVmaxWaves) void vmax_rows_kernel(
     const T* V, int64_t ld, int64_t d, const int32_t* idx, int64_t in_stride, int64_t N, int64_t G,
-    uint32_t* vmax_bits) {
+    int64_t calls, uint32_t* vmax_bits) {
   constexpr int kU = 8;
-  const int64_t s = blockIdx.x / G, t = blockIdx.x % G;
+  const int64_t c = blockIdx.x + (int64_t)gridDim.x * blockIdx.y;
+  if (c >= calls) return;
+  const int64_t s = c / G, t = c % G;
   const int64_t wpr = d * Elem<T>::bytes / 16;
   const u32x4* base = reinterpret_cast<const u32x4*>(V + s * ld * d);
   const int32_t* rows = idx + s * in_stride + t * N;
@@ -77,7 +80,7 @@ __global__ __launch_bounds__(64 * kVmaxWaves) void vmax_rows_kernel(
   __syncthreads();
   if (wave == 0) {
     const float call = wave_max(lane < kVmaxWaves ? part[lane] : 0.0f);
-    if (lane == 0) vmax_bits[blockIdx.x] = __float_as_uint(call);
+    if (lane == 0) vmax_bits[c] = __float_as_uint(call);
   }
 }
 
@@ -557,13 +560,14 @@ hipError_t launch_vmax_rows(int dtype, const void* V, int64_t ld, int64_t d, con
   // a call's words are counted in 32 bits
   const int64_t words = N * d * (dtype == 0 ? 4 : 2) / 16;
   if (words >= ((int64_t)1 << 31)) return hipErrorInvalidValue;
-  const dim3 grid((unsigned)(S * G)), block(64 * kVmaxWaves);
+  const GridRows g = grid_rows(S * G, 64 * kVmaxWaves);
+  const dim3 grid((unsigned)g.x, (unsigned)g.rows), block(64 * kVmaxWaves);
   if (dtype == 0)
     hipLaunchKernelGGL((vmax_rows_kernel<float>), grid, block, 0, st, (const float*)V, ld, d, idx,
-                       in_stride, N, G, vmax_bits);
+                       in_stride, N, G, S * G, vmax_bits);
   else
     hipLaunchKernelGGL((vmax_rows_kernel<bf16_t>), grid, block, 0, st, (const bf16_t*)V, ld, d, idx,
-                       in_stride, N, G, vmax_bits);
+                       in_stride, N, G, S * G, vmax_bits);
   return hipGetLastError();
 }
 
