@@ -1276,11 +1276,13 @@ template <typename T, int D, typename TO>
 hipError_t launch_attn_t(const void* Q, const void* K, const void* V, const int32_t* idx,
                          const float* logw, int64_t S, int64_t n, int64_t n_q, int64_t n_out,
                          void* O, hipStream_t st) {
-  // Float rows: one 16-query tile per wave, whose registers let four workgroups
-  // share a CU (16 slices x 4096 queries x 64 keys, d = 64: 17.3 us with two
-  // tiles, 16.5 with one; 8 x 2048, d = 128: 17.7, 11.8).  bf16 rows: two, so
-  // that a chunk's staging, which turns V, serves twice the queries (8 x 3000
-  // x 400 keys, d = 128: 38 us, 45 with one).
+  // Float rows: one 16-query tile per wave, whose registers let more workgroups
+  // share a CU, though every 64 queries then stage the coreset (us with two tiles
+  // | one: d = 64, 8 x 1024 queries over 128 keys 16.4 | 10.4, 32 x 16384 over 256
+  // 349 | 326; d = 128, 8 x 1024 over 48 16.6 | 10.9, 100 x 4096 over 256 828 | 693;
+  // d = 32 within 3 % where the queries fill the device: 32 x 16384 over 256 176 |
+  // 181).  bf16 rows: two, so that a chunk's staging, which turns V, serves twice
+  // the queries (8 x 3000 x 400 keys, d = 128: 38 us, 45 with one).
   constexpr int QT = Elem<T>::bytes == 4 ? 1 : 2;
   constexpr int64_t per = 16 * QT * WAVES;
   const int64_t blocks = (n_q + per - 1) / per;
