@@ -382,7 +382,7 @@ def prefill_main(args):
         "config": {"workload": "express-prefill", "B": w.B, "H": w.H, "n": w.n, "d": w.d,
                    "n_out": c["n_out"], "mbar": c["mbar"], "delta": 0.5, "halve": "kh"},
         "roofline": {
-            "kernel": "prefill_attn_kernel (block-causal weighted attention of every point)",
+            "kernel": "prefill_attn_bf16_kernel (block-causal weighted attention of every point)",
             "bound": "hbm", "achieved": gbs, "peak": HBM_PEAK_GBS, "unit": "GB/s",
             "frac": gbs / HBM_PEAK_GBS, "traffic": None, "algorithmic_bytes_per_launch": att_bytes,
             "ms_per_launch": att_ms, "mfma_tflops": tfl,

@@ -925,7 +925,7 @@ __global__ __launch_bounds__(64 * PF_WAVES) __attribute__((amdgpu_waves_per_eu(4
 // reads (2048 cycles of the CU's LDS per workgroup and chunk, about what the
 // matrix cores and the vector ALU each need).  Against the kernel above with
 // V turned in registers and nothing in flight during a chunk: 65536 points x
-// 32 slices, d = 128: 3660 -> 2270 us (2054 with the order of tiles below).
+// 32 slices, d = 128: 3660 -> 2270 us (2050 to 2180 with the order of tiles below).
 // ---------------------------------------------------------------------------
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ uint2 read_tr16(uint32_t lds) {
@@ -986,7 +986,8 @@ __global__ __launch_bounds__(64 * PF_WAVES) __attribute__((amdgpu_waves_per_eu(4
   const int m16 = lane & 15, g = lane >> 4;
   // Workgroups are dealt to the eight XCDs in turn; each XCD takes a contiguous
   // eighth of the tiles, slice after slice, so that the cache pieces a slice's
-  // tiles share stay in one L2 (65536 points x 32 slices 2318 -> 2054 us).
+  // tiles share stay in one L2 (65536 points x 32 slices 2318 -> 2054 us at best,
+  // 2165 on average over several runs).
   const int64_t per = (work + 7) >> 3;
   const int64_t at = (int64_t)(blockIdx.x & 7) * per + (blockIdx.x >> 3) +
                      (int64_t)(gridDim.x >> 3) * blockIdx.y;
