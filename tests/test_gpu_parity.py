@@ -712,3 +712,26 @@ def test_compress_without_room_for_spread_rounds():
         got.append((idx.cpu(), ("scores", 2) in [(k, r) for k, r, _ in lt.records()]))
     assert torch.equal(got[0][0], got[1][0])
     assert got[0][1] and not got[1][1]
+
+
+@pytest.mark.parametrize("out", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("d,n_out", [(64, 16), (64, 200), (128, 100), (128, 192), (128, 256)])
+@pytest.mark.parametrize("n_q", [1, 15, 17, 64, 65, 129, 4097])
+def test_attention_of_a_partly_filled_last_tile(d, n_out, n_q, out):
+    """Query counts at the edges of a wave's tile and a workgroup's step: every
+    row as in a call whose tiles are full (the same products in the same order),
+    and nothing behind the last row."""
+    gen = torch.Generator().manual_seed(n_q + n_out)
+    full = (n_q + 255) // 256 * 256
+    Q = torch.randn(1, 3, full, d, generator=gen).bfloat16().to(DEV)
+    K, V = (torch.randn(1, 3, 500, d, generator=gen).bfloat16().to(DEV) for _ in range(2))
+    idx = torch.randint(0, 500, (1, 3, n_out), generator=gen, dtype=torch.int32).to(DEV)
+    room = torch.full((3 * n_q * d + 4096,), 7.0, dtype=out, device=DEV)
+    O = room[: 3 * n_q * d].view(1, 3, n_q, d)
+    thin_attention(Q[:, :, :n_q].contiguous(), K, V, idx, O=O)
+    want = thin_attention(Q, K, V, idx, out_dtype=out)[:, :, :n_q]
+    torch.cuda.synchronize()
+    assert (room[3 * n_q * d:] == 7.0).all()
+    # (one or two tiles per wave by the sizes: passes over the keys may differ)
+    tol = 1e-5 if out == torch.float32 else 2e-2
+    assert (O.float() - want.float()).abs().max().item() <= tol
