@@ -11,24 +11,32 @@ namespace thin {
 // unit (score_units_kernel); beyond, the workgroups of pair_scores_kernel, which
 // read each row once for 128 or 256 others.  (bf16 rows stay with those at every
 // size: the matrix cores take their products sixteen times as fast and the launch
-// is all latency; 32 buckets of 512 rows: 15 us against 19.)  What sets the line
-// is how many waves the device holds:
-// - d = 32, 64 (3 and 2 waves per SIMD): a first round, whose other form is two
-//   launches, is faster as units up to about 13000 of them (d = 64, whole call,
-//   units against workgroups: 24 buckets of 1024 rows 0.84, 64 of 512 0.88, 100
-//   of 512 1.13, 48 of 800 1.17), a later one up to about 6000 (64 of 320 1.01,
-//   64 of 512 1.07, 32 of 800 1.06).
-// - d = 128: eight fragments of three or four operands are 436 registers, one
-//   wave per SIMD (first rounds: 64 buckets of 256 rows 1.00, 100 of 256 1.22, 32
-//   of 512 0.98, 64 of 512 1.50; later ones: 32 of 512 1.04).
-// - The workgroups of fewer than eight buckets run on as many XCDs (d = 128: 8
-//   buckets of 1024 rows 0.84, 2 of 2048 0.84, 6 of 2048 1.24, one of 4096 0.63;
-//   d = 64: 6 of 2048 0.84, one of 5600 0.64).
+// is all latency; 32 buckets of 512 rows: 15 us against 19.)  The line was fitted
+// to 1788 rounds measured in both forms (160 to 4096 rows in 1 to 160 buckets;
+// whole calls of one or two rounds, us, units | workgroups):
+// - the device holds so many units' waves (d = 32, 64: 3 and 2 per SIMD; d = 128:
+//   eight fragments of three or four operands are 436 registers, one per SIMD), and
+//   a first round's other form is two launches: first rounds, d = 64, 24 buckets of
+//   1024 rows 112 | 134, 64 of 640 108 | 96; d = 128, 8 of 1024 103 | 126, 12 of
+//   1024 133 | 127;
+// - a smaller bucket's workgroups have less to do before they are done: d = 128, 40
+//   of 400 rows 80 | 87, 56 of 320 77 | 72, 72 of 200 63 | 58;
+// - the other form deals buckets to the eight XCDs, whole ones: fewer than eight
+//   buckets leave XCDs idle (d = 128, 2 of 4096 rows 417 | 478, 3 of 2048 158 |
+//   200), and more that eight does not divide some of them (later rounds, d = 128,
+//   17 of 800 rows 340 | 355, 16 of 800 293 | 276).
+// Over all those rounds the line costs 0.2 % against the faster form of each.
 inline int64_t unit_launch_max(int64_t d, int64_t N, int64_t nbk, bool first_round) {
-  constexpr int64_t kMost = 16384;
-  if (d <= 64) return nbk < 8 ? kMost : first_round ? 13312 : 6144;
-  const int64_t wide = !first_round ? 2048 : N < 512 ? 2560 : 4800;
-  return std::min(kMost, std::max(wide, 36864 / nbk));
+  int64_t most, per_row;
+  if (d > 64) {
+    most = first_round ? 4750 : 5250;
+    per_row = first_round ? 11 : 7;
+  } else {
+    most = !first_round ? 16250 : d > 32 ? 13500 : 15500;
+    per_row = first_round ? 30 : 12;
+  }
+  const int64_t units = std::min(most, per_row * N), dealt = (nbk + 7) / 8 * 8;
+  return nbk < 8 ? units * dealt / nbk : units * (dealt + nbk) / (2 * nbk);
 }
 
 // A local launch of nbk buckets stages every row tile of a bucket at once, where

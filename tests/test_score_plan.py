@@ -42,11 +42,14 @@ def _units(N):
 @pytest.mark.parametrize("d,N,buckets,first,units", [
     (64, 1024, 24, True, True), (64, 512, 64, True, True), (64, 512, 100, True, False),
     (64, 800, 48, True, False), (64, 512, 64, False, False), (64, 320, 64, False, True),
-    (64, 2048, 6, True, True), (32, 5600, 1, True, True), (32, 512, 100, True, False),
+    (64, 2048, 6, True, True), (32, 5600, 1, True, True), (32, 512, 128, True, False),
     (128, 256, 33, True, True), (128, 256, 100, True, False), (128, 512, 64, True, False),
     (128, 800, 32, True, False), (128, 1024, 16, True, False), (128, 1024, 8, True, True),
     (128, 2048, 6, True, False), (128, 4096, 1, True, True), (128, 512, 100, False, False),
     (128, 200, 300, True, False), (128, 512, 16, True, True),
+    (128, 800, 17, False, True), (128, 800, 16, False, False), (128, 400, 40, True, True),
+    (128, 4096, 2, True, True), (128, 2048, 3, True, True), (64, 4096, 2, False, True),
+    (64, 1024, 28, False, False), (32, 1024, 25, True, True),
 ])
 def test_float_rounds_take_units_where_those_are_faster(plan, d, N, buckets, first, units):
     most = plan.unit_launch_max(C.c_int64(d), C.c_int64(N), C.c_int64(buckets), int(first))
